@@ -44,7 +44,7 @@ struct Bucket {
     double *d_obs = nullptr;         // n*16
     double *d_m2 = nullptr;          // n*M
     double *d_acc = nullptr;         // n*acc_width(M)
-    double *d_accsum = nullptr;      // acc_width(M)
+    double *d_accsum = nullptr;      // acc_width(M), part of dm_ctx::d_accsum
     double *d_tumble = nullptr;      // 2n: tumbling state, step of the last tumble + 1
     double *d_ring = nullptr;        // n * 2^(K-1) * 9: past (L, u_m, d) for the correlations
     double *d_ccount = nullptr;      // n: samples written to the ring
@@ -81,6 +81,7 @@ struct dm_ctx {
     int nonlinear = 1, sample_every = 0, check_finite = 0;
     int64_t step = 0;
     int *d_flag = nullptr;
+    double *d_accsum = nullptr;      // the buckets' summed accumulators, one after another
     // fused paths: one launch over all buckets, and the captured graph of
     // one sampling block (fused launch, step-counter advance, observables)
     dm::FusedPlan plan;
@@ -147,7 +148,7 @@ void free_bucket(Bucket &b)
 {
     void *ptrs[] = {b.d_ids, b.d_off,  b.d_Ainv, b.d_Apos, b.d_Afwd, b.d_E,   b.d_C,
                     b.d_W,   b.d_R64, b.d_r,    b.d_F,    b.d_dH,   b.d_obs, b.d_m2,
-                    b.d_acc, b.d_accsum, b.d_cm0, b.d_tumble, b.d_chiT, b.d_mcstep,
+                    b.d_acc, b.d_cm0, b.d_tumble, b.d_chiT, b.d_mcstep,
                     b.d_mcacc, b.d_ring, b.d_ccount, b.d_wlc};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -519,12 +520,21 @@ int dm_init_chains(dm_ctx **out, int32_t n_chains, const int32_t *beads, const d
         for (Bucket &b : ctx->buckets) free_bucket(b);
         if (ctx->d_flag) (void)hipFree(ctx->d_flag);
         if (ctx->d_step) (void)hipFree(ctx->d_step);
+        if (ctx->d_accsum) (void)hipFree(ctx->d_accsum);
         delete ctx;
         g_init_error = msg;
         return code;
     };
     if ((rc = dalloc(ctx, &ctx->d_flag, 1))) return bail(rc);
     if ((rc = dalloc(ctx, &ctx->d_step, 1))) return bail(rc);
+    size_t wsum = 0;
+    for (const Bucket &b : ctx->buckets) wsum += (size_t)dm::acc_width(b.M);
+    if ((rc = dalloc(ctx, &ctx->d_accsum, wsum))) return bail(rc);
+    wsum = 0;
+    for (Bucket &b : ctx->buckets) {
+        b.d_accsum = ctx->d_accsum + wsum;
+        wsum += (size_t)dm::acc_width(b.M);
+    }
     std::vector<double> phi, tmp;
     for (Bucket &b : ctx->buckets) {
         const size_t MM = (size_t)b.M * b.M, S = (size_t)3 * b.M * b.n;
@@ -537,7 +547,6 @@ int dm_init_chains(dm_ctx **out, int32_t n_chains, const int32_t *beads, const d
             (rc = dalloc(ctx, &b.d_obs, (size_t)16 * b.n)) ||
             (rc = dalloc(ctx, &b.d_m2, (size_t)b.M * b.n)) ||
             (rc = dalloc(ctx, &b.d_acc, (size_t)dm::acc_width(b.M) * b.n)) ||
-            (rc = dalloc(ctx, &b.d_accsum, (size_t)dm::acc_width(b.M))) ||
             (rc = dalloc(ctx, &b.d_tumble, (size_t)2 * b.n)) ||
             (rc = dalloc(ctx, &b.d_cm0, (size_t)3 * b.n)))
             return bail(rc);
@@ -958,16 +967,20 @@ int dm_observables(dm_ctx *ctx, int32_t which, double *out_host, size_t out_len)
         o += ctx->total / 3;
     }
     if (which & DM_OBS_ACCUM) {
+        size_t total = 0;
         for (Bucket &b : ctx->buckets) {
             const int w = dm::acc_width(b.M);
             DM_HIP(ctx, dm::launch_reduce_chains(b.d_acc, b.d_accsum, w, b.n, ctx->stream));
-            DM_HIP(ctx, hipMemcpyAsync(o, b.d_accsum, sizeof(double) * w, hipMemcpyDeviceToHost,
-                                       ctx->stream));
-            DM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+            total += (size_t)w;
+        }
+        DM_HIP(ctx, hipMemcpyAsync(o, ctx->d_accsum, sizeof(double) * total,
+                                   hipMemcpyDeviceToHost, ctx->stream));
+        DM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        for (Bucket &b : ctx->buckets) {
             o[DM_ACC_M] = b.M;
             o[DM_ACC_NCHAINS] = b.n;
             o[DM_ACC_NSAMPLES] = b.n ? o[DM_ACC_NSAMPLES] / b.n : 0.0;
-            o += w;
+            o += dm::acc_width(b.M);
         }
     }
     if (which & DM_OBS_RESET) {
@@ -1158,6 +1171,7 @@ int dm_destroy(dm_ctx *ctx)
     for (Bucket &b : ctx->buckets) free_bucket(b);
     if (ctx->d_flag) (void)hipFree(ctx->d_flag);
     if (ctx->d_step) (void)hipFree(ctx->d_step);
+    if (ctx->d_accsum) (void)hipFree(ctx->d_accsum);
     delete ctx;
     return DM_OK;
 }

@@ -105,7 +105,7 @@ hipError_t launch_chain_obs(const double *pos, const double *R, double *obs,
                             const int64_t *step_dev, double *ring, double *ccount,
                             int K, int M, int nch, int accumulate, hipStream_t st);
 
-// out[j] = sum_c acc[c*width + j], summed over chains in order.
+// out[j] = sum_c acc[c*width + j], in a fixed order of the chains.
 hipError_t launch_reduce_chains(const double *acc, double *out, int width,
                                 int nch, hipStream_t st);
 
