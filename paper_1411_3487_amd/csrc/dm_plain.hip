@@ -207,8 +207,7 @@ __device__ __forceinline__ void bond_g(const double *__restrict__ x, int M, int 
     const double ux = x[m] - x[m - 1];
     const double uy = x[M + m] - x[M + m - 1];
     const double uz = x[2 * M + m] - x[2 * M + m - 1];
-    const double l = sqrt(ux * ux + uy * uy + uz * uz);
-    const double f = 1.0 / l - lin;
+    const double f = rsqrt64(ux * ux + uy * uy + uz * uz) - lin;
     g[0] = ux * f;
     g[1] = uy * f;
     g[2] = uz * f;
@@ -361,12 +360,13 @@ __global__ __launch_bounds__(1024) void euler_f64_kernel(double *__restrict__ po
             for (int j = 0; j < 5; ++j) {
                 const int m = n0 + j;
                 const bool ok = (m >= 1) && (m <= M - 1);
-                const double l = sqrt(u[0][j + 1] * u[0][j + 1] + u[1][j + 1] * u[1][j + 1] +
-                                      u[2][j + 1] * u[2][j + 1]);
+                // (|u| - 1) / |u| = 1 - 1/|u|
+                const double f = 1.0 - rsqrt64(u[0][j + 1] * u[0][j + 1] +
+                                               u[1][j + 1] * u[1][j + 1] +
+                                               u[2][j + 1] * u[2][j + 1]);
 #pragma unroll
                 for (int a = 0; a < 3; ++a)
-                    h[a][j] = ok ? (l - 1.0) * u[a][j + 1] / l - nu * (u[a][j] + u[a][j + 2])
-                                 : 0.0;
+                    h[a][j] = ok ? f * u[a][j + 1] - nu * (u[a][j] + u[a][j + 2]) : 0.0;
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {

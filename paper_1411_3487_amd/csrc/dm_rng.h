@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dm_math.h"
+
 namespace dm {
 
 enum : uint32_t {
@@ -80,8 +82,21 @@ __host__ __device__ __forceinline__ Block4 noise_bits(uint64_t seed, uint32_t bl
 
 // Box-Muller pair `second` (0: words 0, 1; 1: words 2, 3) of a block in
 // FP64: uniforms (x + 1/2) 2^-32, z = sqrt(-2 ln u_a) (cos, sin)(2 pi u_b).
+// On the device with the functions of dm_math.h, which know their arguments'
+// ranges: within 3.4e-16 of the exact normal relative to its radius (7.1e-16
+// with the C library's functions on 2 pi u_b).  The kernels that draw FP64
+// noise are bound by its arithmetic: a bead-space Euler step of 4096 chains of
+// 256 beads (3.1e6 normals) takes 8.1 us, 24 us with the library functions,
+// a mode update of the same ensemble 14 us, 20.6 us.
 __host__ __device__ __forceinline__ void normal_pair_f64(const Block4 &b, int second, double z[2])
 {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double ra = sqrt64(neg2log_u32(b.v[2 * second]));
+    double c, s;
+    sincos_u32(b.v[2 * second + 1], c, s);
+    z[0] = ra * c;
+    z[1] = ra * s;
+#else
     const double scale = 2.3283064365386962890625e-10;  // 2^-32
     const double two_pi = 6.283185307179586476925286766559;
     const double ua = ((double)b.v[2 * second] + 0.5) * scale;
@@ -89,6 +104,7 @@ __host__ __device__ __forceinline__ void normal_pair_f64(const Block4 &b, int se
     const double ra = sqrt(-2.0 * log(ua));
     z[0] = ra * cos(two_pi * ub);
     z[1] = ra * sin(two_pi * ub);
+#endif
 }
 
 // Four N(0,1) in FP64: the block's two Box-Muller pairs.
