@@ -62,8 +62,9 @@ extern "C" {
 #define DM_ESTATE     -5   /* call out of order (e.g. stepping before set_params) */
 
 /* Arithmetic of the mode step. */
-#define DM_FP64    0  /* plain form: dense phi products on FP64 MFMA, separate
-                         force-stencil and mode-update kernels, FP64 state */
+#define DM_FP64    0  /* FP64 throughout: a persistent kernel on FP64 MFMA up to
+                         512 beads; for longer chains dense phi products and
+                         separate force-stencil and mode-update kernels */
 #define DM_FP32    1  /* fused persistent kernel, FP32 MFMA transforms, FP32
                          internal modes, FP64 centre of mass */
 #define DM_BF16X3  2  /* fused persistent kernel, transforms as three BF16 MFMA
@@ -163,12 +164,11 @@ typedef struct {
                                 copy of the state and keeps the combination
                                 with the shortest schedule (see
                                 dm_get_tiling); 0: fixed shapes */
-    int32_t use_graphs;      /* sample_every > 0 (at most 256 on DM_FP64), 1:
-                                whole sampling blocks (the fused launch, or
-                                the FP64 plain form's four launches per step
-                                and length, the step counter and the
-                                observables) are captured once as a HIP graph
-                                and replayed.  On the fused paths, when the
+    int32_t use_graphs;      /* sample_every > 0 (at most 256 on DM_FP64 with
+                                chains beyond 512 beads), 1: whole sampling
+                                blocks (the launches of the steps, the step
+                                counter and the observables) are captured
+                                once as a HIP graph and replayed.  On the fused paths, when the
                                 launch leaves compute units idle, runs of
                                 several blocks take each block's sample from
                                 a snapshot of its state on a second stream
@@ -347,17 +347,16 @@ int dm_coarse_grain_time(double r, double y, int32_t k, double *c_k);
 
 /* For callers that cannot allocate device memory (code under HIP graph
    capture, tight serving loops, harnesses that forbid hipMalloc): the FP64
-   plain-form mode step of dm_step_modes for one chain length, without a
-   context.  R_dev (device, caller-owned, 16-byte aligned) holds n_chains
+   mode step of dm_step_modes for one chain length, without a context.  R_dev (device, caller-owned, 16-byte aligned) holds n_chains
    chains of M mode amplitudes R_p in the SoA layout (3*M doubles per
    chain, p = 0..M-1) and is advanced in place by n_steps steps at Philox
    steps step0 .. step0 + n_steps - 1; chain j draws its noise as chain index
    chain0 + j, so a call reproduces dm_step_modes on those chains of a
    context.  Reduced units: T_star, nu, dtau (= Delta tau), gamma_dot; tables
    and coefficients are built on the device at every call.  No allocation:
-   the tables, the chain indices and the two work buffers live in one fixed
-   device array of DM_STATIC_SCRATCH_BYTES per GPU, held from the first use
-   until the process ends; it needs 8 (2 M^2 + 3 M + 6 M n_chains) +
+   the tables, the chain indices and (beyond 512 beads) two work buffers live
+   in one fixed device array of DM_STATIC_SCRATCH_BYTES per GPU, held from the
+   first use until the process ends; a call is admitted if it holds 8 (2 M^2 + 3 M + 6 M n_chains) +
    4 n_chains bytes (each part rounded up to 256), e.g. 4096 chains of 256
    beads.  Calls that overlap on one GPU share that array and race; calls on
    one stream are ordered.  Asynchronous on hip_stream.  Errors (message in

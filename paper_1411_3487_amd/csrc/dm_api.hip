@@ -13,6 +13,7 @@
 #include "../../include/dnamodes.h"
 #include "dm_fused.h"
 #include "dm_internal.h"
+#include "dm_modes64.h"
 #include "dm_rng.h"
 #include "dm_tables.h"
 
@@ -20,8 +21,9 @@ namespace {
 
 thread_local std::string g_init_error;
 
-// Longest sampling block the FP64 plain form replays as a graph (it holds
-// four kernel nodes per step and length bucket).
+// Longest sampling block with lengths beyond the persistent FP64 stepper
+// that is replayed as a graph (it holds four kernel nodes per step and such
+// length).
 constexpr int kMaxPlainGraphSteps = 256;
 
 struct Bucket {
@@ -33,6 +35,9 @@ struct Bucket {
     // device
     int32_t *d_ids = nullptr;
     int64_t *d_off = nullptr;
+    double *d_X64 = nullptr;         // tables of the persistent FP64 stepper (M <= 512)
+    int jc64 = 0;                    // its coupled mode tiles
+    // dense FP64 steps of longer chains
     double *d_Ainv = nullptr;        // phi with column p = 0 zeroed (inverse, internal)
     double *d_Apos = nullptr;        // phi (inverse, all modes)
     double *d_Afwd = nullptr;        // phi^T (forward)
@@ -85,6 +90,7 @@ struct dm_ctx {
     // fused paths: one launch over all buckets, and the captured graph of
     // one sampling block (fused launch, step-counter advance, observables)
     dm::FusedPlan plan;
+    dm::Modes64Plan plan64;          // FP64: launches of the persistent stepper
     int use_graphs = 0, autotune = 0, corr_lags = 0;
     int64_t *d_step = nullptr;
     hipStream_t cap_stream = nullptr;
@@ -146,7 +152,7 @@ int dalloc(dm_ctx *ctx, T **p, size_t count)
 
 void free_bucket(Bucket &b)
 {
-    void *ptrs[] = {b.d_ids, b.d_off,  b.d_Ainv, b.d_Apos, b.d_Afwd, b.d_E,   b.d_C,
+    void *ptrs[] = {b.d_X64, b.d_ids, b.d_off,  b.d_Ainv, b.d_Apos, b.d_Afwd, b.d_E,   b.d_C,
                     b.d_W,   b.d_R64, b.d_r,    b.d_F,    b.d_dH,   b.d_obs, b.d_m2,
                     b.d_acc, b.d_cm0, b.d_tumble, b.d_chiT, b.d_mcstep,
                     b.d_mcacc, b.d_ring, b.d_ccount, b.d_wlc};
@@ -312,8 +318,10 @@ int capture_overlap(dm_ctx *ctx, int steps)
     return DM_OK;
 }
 
-// One FP64 plain-form mode step of one bucket on stream st at Philox step
-// k, or (step_dev non-null, inside a captured block) *step_dev + k.
+// FP64 mode steps of one bucket whose chains are too long for the persistent
+// stepper: dense transforms, force stencil and mode update as four launches
+// per step, at Philox step k, or (step_dev non-null, inside a captured block)
+// *step_dev + k.
 int plain_step(dm_ctx *ctx, Bucket &b, int64_t k, hipStream_t st,
                const int64_t *step_dev = nullptr)
 {
@@ -329,7 +337,24 @@ int plain_step(dm_ctx *ctx, Bucket &b, int64_t k, hipStream_t st,
     return DM_OK;
 }
 
-// Capture one sampling block of `steps` fused steps: the launch reads its
+// n FP64 mode steps of every bucket, first Philox step k (+ *step_dev).
+int advance64(dm_ctx *ctx, int64_t k, int64_t n, hipStream_t st,
+              const int64_t *step_dev = nullptr)
+{
+    constexpr int64_t kPerLaunch = 1 << 16;
+    for (int64_t s = 0; s < n; s += kPerLaunch)
+        DM_HIP(ctx, dm::modes64_launch(ctx->plan64, ctx->seed, k + s, step_dev,
+                                       (int)std::min(kPerLaunch, n - s), ctx->nonlinear, st));
+    for (Bucket &b : ctx->buckets)
+        if (!dm::modes64_supports(b.M))
+            for (int64_t s = 0; s < n; ++s) {
+                int rc = plain_step(ctx, b, k + s, st, step_dev);
+                if (rc) return rc;
+            }
+    return DM_OK;
+}
+
+// Capture one sampling block of `steps` steps: the launches read their
 // Philox step from ctx->d_step, a one-thread kernel advances it, then the
 // observables are accumulated.  No memset nodes (plain kernels only).
 int capture_block(dm_ctx *ctx, int steps)
@@ -344,11 +369,7 @@ int capture_block(dm_ctx *ctx, int steps)
         e = dm::fused_launch(ctx->plan, ctx->seed, 0, ctx->d_step, steps, ctx->nonlinear,
                              ctx->cap_stream);
     } else {
-        // the plain form's four launches per step and bucket, each update
-        // reading its Philox step from the device counter
-        for (int s = 0; s < steps && rc == DM_OK; ++s)
-            for (Bucket &b : ctx->buckets)
-                if (rc == DM_OK) rc = plain_step(ctx, b, s, ctx->cap_stream, ctx->d_step);
+        rc = advance64(ctx, 0, steps, ctx->cap_stream, ctx->d_step);
     }
     if (e == hipSuccess && rc == DM_OK)
         e = dm::fused_advance_step(ctx->d_step, steps, ctx->cap_stream);
@@ -375,6 +396,27 @@ int capture_block(dm_ctx *ctx, int steps)
 
 int build_plan(dm_ctx *ctx)
 {
+    if (!fused_precision(ctx->precision)) {
+        std::vector<dm::Modes64Args> bs;
+        for (Bucket &b : ctx->buckets) {
+            if (!dm::modes64_supports(b.M)) continue;
+            dm::Modes64Args a;
+            a.X = b.d_X64;
+            a.E = b.d_E;
+            a.C = b.d_C;
+            a.W = b.d_W;
+            a.R = b.d_R64;
+            a.ids = b.d_ids;
+            a.n = b.n;
+            a.M = b.M;
+            a.jc = b.jc64;
+            a.lin = 1.0 - 2.0 * ctx->nu;
+            a.gdt = ctx->gamma_dot * b.dtau;
+            bs.push_back(a);
+        }
+        DM_HIP(ctx, dm::modes64_plan(ctx->plan64, bs, std::max(1, ctx->ncu), ctx->stream));
+        return DM_OK;
+    }
     std::vector<const dm::FusedBucket *> fb;
     for (Bucket &b : ctx->buckets) fb.push_back(&b.fused);
     DM_HIP(ctx, dm::fused_plan(ctx->plan, fb, 0, ctx->stream));
@@ -539,21 +581,29 @@ int dm_init_chains(dm_ctx **out, int32_t n_chains, const int32_t *beads, const d
     for (Bucket &b : ctx->buckets) {
         const size_t MM = (size_t)b.M * b.M, S = (size_t)3 * b.M * b.n;
         if ((rc = dalloc(ctx, &b.d_ids, b.n)) || (rc = dalloc(ctx, &b.d_off, b.n)) ||
-            (rc = dalloc(ctx, &b.d_Ainv, MM)) || (rc = dalloc(ctx, &b.d_Apos, MM)) ||
+            (rc = dalloc(ctx, &b.d_Apos, MM)) ||
             (rc = dalloc(ctx, &b.d_Afwd, MM)) || (rc = dalloc(ctx, &b.d_E, b.M)) ||
             (rc = dalloc(ctx, &b.d_C, b.M)) || (rc = dalloc(ctx, &b.d_W, b.M)) ||
             (rc = dalloc(ctx, &b.d_R64, S)) || (rc = dalloc(ctx, &b.d_r, S)) ||
-            (rc = dalloc(ctx, &b.d_F, S)) || (rc = dalloc(ctx, &b.d_dH, S)) ||
             (rc = dalloc(ctx, &b.d_obs, (size_t)16 * b.n)) ||
             (rc = dalloc(ctx, &b.d_m2, (size_t)b.M * b.n)) ||
             (rc = dalloc(ctx, &b.d_acc, (size_t)dm::acc_width(b.M) * b.n)) ||
             (rc = dalloc(ctx, &b.d_tumble, (size_t)2 * b.n)) ||
             (rc = dalloc(ctx, &b.d_cm0, (size_t)3 * b.n)))
             return bail(rc);
+        const bool resident64 = precision == DM_FP64 && dm::modes64_supports(b.M);
+        const bool dense64 = precision == DM_FP64 && !resident64;
+        if (resident64 &&
+            (rc = dalloc(ctx, &b.d_X64, dm::modes64_table_bytes(b.M) / sizeof(double))))
+            return bail(rc);
+        if (dense64 && ((rc = dalloc(ctx, &b.d_Ainv, MM)) || (rc = dalloc(ctx, &b.d_F, S)) ||
+                        (rc = dalloc(ctx, &b.d_dH, S))))
+            return bail(rc);
         dm::rouse_matrix(b.M, phi);
-        std::vector<double> ainv(phi), afwd(MM);
+        std::vector<double> ainv, afwd(MM);
+        if (dense64) ainv = phi;
         for (int n = 0; n < b.M; ++n) {
-            ainv[(size_t)n * b.M] = 0.0;
+            if (dense64) ainv[(size_t)n * b.M] = 0.0;
             for (int p = 0; p < b.M; ++p) afwd[(size_t)p * b.M + n] = phi[(size_t)n * b.M + p];
         }
         std::vector<double> pos, cm0((size_t)3 * b.n, 0.0);
@@ -571,7 +621,8 @@ int dm_init_chains(dm_ctx **out, int32_t n_chains, const int32_t *beads, const d
         };
         up(b.d_ids, b.ids.data(), sizeof(int32_t) * b.n);
         up(b.d_off, b.user_off.data(), sizeof(int64_t) * b.n);
-        up(b.d_Ainv, ainv.data(), sizeof(double) * MM);
+        if (dense64) up(b.d_Ainv, ainv.data(), sizeof(double) * MM);
+        if (e == hipSuccess && resident64) e = dm::modes64_build_tables(b.d_X64, b.M, ctx->stream);
         up(b.d_Apos, phi.data(), sizeof(double) * MM);
         up(b.d_Afwd, afwd.data(), sizeof(double) * MM);
         if (pos0) up(b.d_r, pos.data(), sizeof(double) * S);
@@ -661,6 +712,7 @@ int dm_set_params(dm_ctx *ctx, const dm_params *p)
                                             ctx->stream));
         DM_HIP(ctx, hipStreamSynchronize(ctx->stream));  // host tables go out of scope
         b.dtau = dtau[i];
+        b.jc64 = dm::modes64_coupled_tiles(b.M, nu, T_star, dtau[i]);
         b.zeta_l = mc.zeta_l;
     }
     ctx->T_star = T_star;
@@ -714,6 +766,8 @@ int dm_set_params(dm_ctx *ctx, const dm_params *p)
         if (p->tiles_per_wg || p->table_mode)
             for (Bucket &b : ctx->buckets)
                 dm::fused_force_shape(b.fused, p->table_mode, p->tiles_per_wg);
+    }
+    {
         int rc = build_plan(ctx);
         if (rc) return rc;
     }
@@ -728,10 +782,10 @@ int dm_step_modes(dm_ctx *ctx, int64_t n_steps)
     if (n_steps < 0) return fail(ctx, DM_EINVAL, "n_steps must be >= 0");
     int64_t done = 0;
     const bool fused = fused_precision(ctx->precision);
-    // the plain form captures its launches one by one: blocks of at most
-    // kMaxPlainGraphSteps steps
+    bool dense = false;  // dense FP64 steps are captured launch by launch
+    for (const Bucket &b : ctx->buckets) dense = dense || (!fused && !dm::modes64_supports(b.M));
     const bool graphs = ctx->use_graphs && ctx->sample_every > 0 &&
-                        (fused || ctx->sample_every <= kMaxPlainGraphSteps);
+                        (!dense || ctx->sample_every <= kMaxPlainGraphSteps);
     while (done < n_steps) {
         const int se = ctx->sample_every;
         if (graphs && ctx->step % se == 0 && n_steps - done >= se) {
@@ -781,11 +835,8 @@ int dm_step_modes(dm_ctx *ctx, int64_t n_steps)
             DM_HIP(ctx, dm::fused_launch(ctx->plan, ctx->seed, ctx->step, nullptr, (int)chunk,
                                          ctx->nonlinear, ctx->stream));
         } else {
-            for (int64_t s = 0; s < chunk; ++s)
-                for (Bucket &b : ctx->buckets) {
-                    int rc = plain_step(ctx, b, ctx->step + s, ctx->stream);
-                    if (rc) return rc;
-                }
+            int rc = advance64(ctx, ctx->step, chunk, ctx->stream);
+            if (rc) return rc;
         }
         ctx->step += chunk;
         done += chunk;
@@ -1168,6 +1219,7 @@ int dm_destroy(dm_ctx *ctx)
     if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
     if (ctx->ev_join) (void)hipEventDestroy(ctx->ev_join);
     dm::fused_plan_free(ctx->plan);
+    dm::modes64_plan_free(ctx->plan64);
     for (Bucket &b : ctx->buckets) free_bucket(b);
     if (ctx->d_flag) (void)hipFree(ctx->d_flag);
     if (ctx->d_step) (void)hipFree(ctx->d_step);

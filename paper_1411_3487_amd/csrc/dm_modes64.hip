@@ -1,0 +1,548 @@
+// dm_modes64.hip -- FP64 mode stepper: a workgroup keeps a tile of chains in
+// its LDS and registers and runs all steps of a launch (gfx950).
+//
+// Each step is the one of the reduced-precision stepper, in FP64 throughout:
+//   u = chi R, g_n = u_n (1/|u_n| - (1-2nu)), Delta H = chi^T g,
+//   R <- E R + C Delta H + W eta (+ shear)          (Eqs. e5, e4, e11, d3, d6, f2, btum)
+// with chi_{n,p} = phi_{n,p} - phi_{n-1,p} = sigma_p sin(p n pi/M),
+// sigma_p = -2 sqrt(2/M) sin(p pi/2M), and its mirror symmetry
+// chi_{M-n,p} = (-1)^{p+1} chi_{n,p}: for half-bond rows b = n - 1 < H = M/2
+//   S_b = sum_{p odd} chi R_p, A_b = sum_{p even} chi R_p,
+//   u_{b+1} = S + A, u_{M-1-b} = S - A,
+//   Delta H_{p odd} = sum_b chi (g + g'), Delta H_{p even} = sum_b chi (g - g')
+// (the middle bond of an even chain, its own mirror, enters g + g' twice: its
+// column of the coupling table is halved).  Half the matrix products of the
+// dense form, no pass over HBM inside a launch, one launch for all steps.
+//
+// What bounds it: FP64 matrix products and vector work share the FP64 units
+// of a SIMD (78.6 TFLOP/s either way), so a step costs the products of u =
+// chi R (3 M^2 flops per chain), those of the coupled mode tiles and the
+// noise in series, about 9 + 5 + 5 us of a step at 4096 chains of 256 beads.
+//
+// Tiles.  The columns of every product are (chain, component) pairs, 16 to a
+// v_mfma_f64_16x16x4_f64.
+//   NT = 3: 16 chains, one column tile per component.  A lane holds x, y, z
+//     of a bond, so bond lengths are lane-local, and each table fragment
+//     serves 48 columns.  The amplitudes and the forces share one LDS buffer
+//     (98 KB at M = 256).
+//   NT = 1: 5 chains, column 3 chain + component (the last is unused); bond
+//     lengths are summed over three lanes by DPP.  For launches that would
+//     leave compute units idle at 16 chains per workgroup, and for chains of
+//     257..512 beads, whose 16-chain state does not fit the LDS.
+// Wavefront w owns mode tile T = w, w + P, ... (32 modes: 16 odd, 16 even)
+// and half-bond row tile I = w, w + P, ....
+//
+// Orders.  A result tile has row l/16 + 4 r, column l%16 in lane l, element r.
+// Row i of a table tile stands for index 16 T + 4 (i % 4) + i / 4, so lane
+// group g = l/16 holds the four consecutive indices 4 g + r: with both
+// parities the eight modes 32 T + 8 g .. + 7, two Philox blocks per
+// component.  The products run over K slab pairs q of 8 indices; lane group g
+// supplies 8 q + 2 g + e for the product e = 0, 1, so both operands are read
+// as 16-byte pairs, and the LDS buffers [parity][t][index/2][column][2] give
+// every wavefront read one contiguous kilobyte.
+#include "dm_modes64.h"
+
+#include <algorithm>
+#include <cmath>
+
+#include "dm_internal.h"
+#include "dm_rng.h"
+
+namespace dm {
+namespace {
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kSmallTile = 5, kLargeTile = 16;  // chains of NT = 1 and NT = 3
+
+struct Item64 {
+    int bucket, tile;
+};
+
+struct Launch64 {
+    const Modes64Args *buckets;  // null: `one` for every item
+    const Item64 *items;         // null: item i is tile i of `one`
+    Modes64Args one;
+    const int64_t *step;         // added to step0 when non-null
+    int64_t step0;
+    uint64_t seed;
+    int n_steps, nonlinear;
+};
+
+__host__ __device__ inline int half_tiles(int M) { return ((M + 1) / 2 + 15) / 16; }
+
+// Lane moves inside a 16-lane row, out-of-row sources read 0 (row_shl:n gives
+// lane i the value of lane i + n).
+template <int CTRL>
+__device__ __forceinline__ double dpp64(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+constexpr int kShl1 = 0x101, kShl2 = 0x102, kShr1 = 0x111, kShr2 = 0x112;
+
+// Sum over the three component lanes of this lane's chain, in one order for
+// all three (alpha = column % 3).
+__device__ __forceinline__ double chain_sum(double v, int alpha)
+{
+    const double s = v + dpp64<kShl1>(v) + dpp64<kShl2>(v);  // complete at alpha == 0
+    const double s1 = dpp64<kShr1>(s), s2 = dpp64<kShr2>(s);
+    return alpha == 0 ? s : (alpha == 1 ? s1 : s2);
+}
+
+// One mirror pair of 16-row products: odd and even accumulators of NT column
+// tiles over Q slab pairs.  X: fragments [q][parity][lane]; B: LDS operands,
+// [parity][t] at stride bs, [q][lane] inside.  Both operands are loaded two
+// slab pairs ahead (the fragments come from L2).
+template <int NT>
+__device__ __forceinline__ void mirror_product(const f64x2 *__restrict__ X, const f64x2 *B, int bs,
+                                               int Q, f64x4 (&so)[NT], f64x4 (&se)[NT])
+{
+    f64x2 x[2][2], b[2][2][NT];
+    auto load = [&](int k, int q) {
+#pragma unroll
+        for (int par = 0; par < 2; ++par) {
+            x[k][par] = X[(size_t)(2 * q + par) * 64];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) b[k][par][t] = B[(par * NT + t) * bs + q * 64];
+        }
+    };
+#pragma unroll
+    for (int t = 0; t < NT; ++t) so[t] = se[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    load(0, 0);
+    load(1, 1);
+    for (int q = 0; q < Q; q += 2) {  // Q is even
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    so[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[k][0][e], b[k][0][t][e], so[t],
+                                                                 0, 0, 0);
+                    se[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[k][1][e], b[k][1][t][e], se[t],
+                                                                 0, 0, 0);
+                }
+            load(k, min(q + k + 2, Q - 1));
+        }
+    }
+}
+
+template <int NT, int P, int NU>
+__global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
+{
+    extern __shared__ double lds[];
+    const Item64 it = la.items ? la.items[blockIdx.x] : Item64{0, (int)blockIdx.x};
+    const Modes64Args a = la.buckets ? la.buckets[it.bucket] : la.one;
+    const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int M = a.M, H = M / 2, RT = half_tiles(M), Hp = 16 * RT, Q = 2 * RT;
+    const int bs = Hp * 8;  // f64x2 of one (parity, column tile) buffer
+    double *cf = lds;                                  // [E, C, W][parity][Hp]
+    f64x2 *Rb = reinterpret_cast<f64x2 *>(lds + 6 * Hp);  // [parity][t][index/2][column]
+    f64x2 *Gb = NT == 1 ? Rb + 2 * bs : Rb;            // [sum, difference][t][index/2][column]
+    for (int i = threadIdx.x; i < 6 * Hp; i += 64 * P) {
+        const int kind = i / (2 * Hp), par = (i / Hp) % 2, p = 2 * (i % Hp) + (par == 0 ? 1 : 0);
+        const double *src = kind == 0 ? a.E : kind == 1 ? a.C : a.W;
+        cf[i] = p < M && !(kind == 1 && p == 0) ? src[p] : 0.0;
+    }
+    // chain and component of this lane's column(s)
+    const int alpha = NT == 1 ? col % 3 : 0;
+    const int j = NT == 1 ? kSmallTile * it.tile + col / 3 : kLargeTile * it.tile + col;
+    const bool valid = j < a.n && (NT == 3 || col < 15);
+    const uint32_t chain = valid ? (uint32_t)a.ids[j] : 0u;
+    double *Rj = a.R + (size_t)3 * M * (valid ? j : 0);
+    const f64x2 *X1 = reinterpret_cast<const f64x2 *>(a.X) + lane;
+    const f64x2 *X2 = X1 + (size_t)RT * Q * 128;
+
+    // amplitudes of the own mode tiles: [parity odd, even][component][r]
+    double R[NU][2][NT][4];
+#pragma unroll
+    for (int ii = 0; ii < NU; ++ii)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int par = 0; par < 2; ++par) {
+                    const int p = 32 * (wave + P * ii) + 8 * g + 2 * r + (par == 0 ? 1 : 0);
+                    R[ii][par][t][r] =
+                        valid && p < M ? Rj[(size_t)(NT == 1 ? alpha : t) * M + p] : 0.0;
+                }
+    // values v[r] of index tile T into a buffer
+    auto put = [&](f64x2 *buf, int par, int t, int T, const double (&v)[4]) {
+        f64x2 *d = buf + (par * NT + t) * bs + (8 * T + 2 * g) * 16 + col;
+        d[0] = f64x2{v[0], v[1]};
+        d[16] = f64x2{v[2], v[3]};
+    };
+    auto put_state = [&]() {
+#pragma unroll
+        for (int ii = 0; ii < NU; ++ii) {
+            const int T = wave + P * ii;
+            if (T < RT)
+#pragma unroll
+                for (int par = 0; par < 2; ++par)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) put(Rb, par, t, T, R[ii][par][t]);
+        }
+    };
+    if (la.nonlinear) put_state();
+    __syncthreads();
+
+    const int64_t k0 = la.step0 + (la.step ? *la.step : 0);
+    for (int s = 0; s < la.n_steps; ++s) {
+        const int64_t k = k0 + s;
+        // ---- bonds of the own half-bond rows and their forces
+        double Gs[NT][4], Gd[NT][4];
+        if (la.nonlinear) {
+#pragma unroll
+            for (int ii = 0; ii < NU; ++ii) {
+                const int I = wave + P * ii;
+                if (I >= RT) continue;
+                f64x4 so[NT], se[NT];
+                mirror_product<NT>(X1 + (size_t)I * Q * 128, Rb + lane, bs, Q, so, se);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    // rows and columns of padding have u = 0: a small number
+                    // under their root (a true bond of length 0 gives NaN)
+                    const double pad = valid && 16 * I + 4 * g + r < H ? 0.0 : 1e-300;
+                    double up[NT], um[NT], qp = pad, qm = pad;
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        up[t] = so[t][r] + se[t][r];
+                        um[t] = so[t][r] - se[t][r];
+                        qp = fma64(up[t], up[t], qp);
+                        qm = fma64(um[t], um[t], qm);
+                    }
+                    if constexpr (NT == 1) {
+                        qp = chain_sum(qp, alpha);
+                        qm = chain_sum(qm, alpha);
+                        if (!valid) qp = qm = 1.0;
+                    }
+                    const double fp = rsqrt64(qp) - a.lin, fm = rsqrt64(qm) - a.lin;
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        const double gm = um[t] * fm;
+                        Gs[t][r] = fma64(up[t], fp, gm);
+                        Gd[t][r] = fma64(up[t], fp, -gm);
+                    }
+                }
+                if constexpr (NT == 1) {
+                    put(Gb, 0, 0, I, Gs[0]);
+                    put(Gb, 1, 0, I, Gd[0]);
+                }
+            }
+        }
+        if constexpr (NT == 3) {
+            static_assert(NT == 1 || NU == 1, "the forces of one row tile stay in registers");
+            if (la.nonlinear) {
+                __syncthreads();  // every wavefront has read the amplitudes
+                if (wave < RT)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        put(Gb, 0, t, wave, Gs[t]);
+                        put(Gb, 1, t, wave, Gd[t]);
+                    }
+            }
+        }
+        // ---- E R + W eta (+ shear) of the own modes
+#pragma unroll
+        for (int ii = 0; ii < NU; ++ii) {
+            const int T = wave + P * ii;
+            if (T >= RT) continue;
+            const double *Eo = cf + 16 * T + 4 * g, *Ee = Eo + Hp;
+            const double *Wo = Eo + 4 * Hp, *We = Eo + 5 * Hp;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const uint32_t comp = (uint32_t)(NT == 1 ? alpha : t);
+                double z[8];
+                normals4_f64(noise_bits(la.seed, (uint32_t)(8 * T + 2 * g), chain, k, comp,
+                                        kTagMode),
+                             z);
+                normals4_f64(noise_bits(la.seed, (uint32_t)(8 * T + 2 * g + 1), chain, k, comp,
+                                        kTagMode),
+                             z + 4);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    double sh_o = 0.0, sh_e = 0.0;
+                    if (a.gdt != 0.0) {  // R^y before its own update, for the x amplitudes
+                        if constexpr (NT == 1) {
+                            const double yo = dpp64<kShl1>(R[ii][0][0][r]),
+                                         ye = dpp64<kShl1>(R[ii][1][0][r]);
+                            sh_o = alpha == 0 ? a.gdt * yo : 0.0;
+                            sh_e = alpha == 0 ? a.gdt * ye : 0.0;
+                        } else if (t == 0) {
+                            sh_o = a.gdt * R[ii][0][1][r];
+                            sh_e = a.gdt * R[ii][1][1][r];
+                        }
+                    }
+                    R[ii][0][t][r] =
+                        fma64(Eo[r], R[ii][0][t][r] + sh_o, Wo[r] * z[2 * r + 1]);
+                    R[ii][1][t][r] = fma64(Ee[r], R[ii][1][t][r] + sh_e, We[r] * z[2 * r]);
+                }
+            }
+        }
+        if (la.nonlinear) {
+            __syncthreads();  // forces written (NT = 1: and the amplitudes read)
+            // ---- coupling of the own modes
+#pragma unroll
+            for (int ii = 0; ii < NU; ++ii) {
+                const int T = wave + P * ii;
+                if (T >= a.jc) continue;
+                f64x4 so[NT], se[NT];
+                mirror_product<NT>(X2 + (size_t)T * Q * 128, Gb + lane, bs, Q, so, se);
+                const double *Co = cf + 2 * Hp + 16 * T + 4 * g, *Ce = Co + Hp;
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        R[ii][0][t][r] = fma64(Co[r], so[t][r], R[ii][0][t][r]);
+                        R[ii][1][t][r] = fma64(Ce[r], se[t][r], R[ii][1][t][r]);
+                    }
+            }
+            if constexpr (NT == 3) __syncthreads();  // every wavefront has read the forces
+            put_state();
+            __syncthreads();
+        }
+    }
+    if (!valid) return;
+#pragma unroll
+    for (int ii = 0; ii < NU; ++ii)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int par = 0; par < 2; ++par) {
+                    const int p = 32 * (wave + P * ii) + 8 * g + 2 * r + (par == 0 ? 1 : 0);
+                    if (p < M) Rj[(size_t)(NT == 1 ? alpha : t) * M + p] = R[ii][par][t][r];
+                }
+}
+
+// Fragments of both products: [product][tile][q][parity][lane][2].  Product
+// 0 (u = chi R): row = half-bond, K = mode; product 1 (coupling): row = mode,
+// K = half-bond.  chi_{n,p} = sigma_p sin(pi (p n mod 2M) / M), exact zeros
+// at multiples of M.
+__global__ __launch_bounds__(256) void modes64_table_kernel(double *__restrict__ X, int M)
+{
+    const int RT = half_tiles(M), Q = 2 * RT, H = M / 2;
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (size_t)2 * RT * Q * 256) return;
+    const int e = (int)(i % 2), lane = (int)(i / 2 % 64), par = (int)(i / 128 % 2);
+    const int q = (int)(i / 256 % Q), T = (int)(i / 256 / Q % RT), prod = (int)(i / 256 / Q / RT);
+    const int row = lane % 16, ri = 16 * T + 4 * (row % 4) + row / 4;
+    const int ki = 8 * q + 2 * (lane / 16) + e;
+    const int b = prod == 0 ? ri : ki, jm = prod == 0 ? ki : ri;
+    const int n = b + 1, p = 2 * jm + (par == 0 ? 1 : 0);
+    double v = 0.0;
+    if (b < H && p < M && p > 0) {
+        const int m = (int)((long)p * n % (2L * M));
+        const double sigma = -2.0 * sqrt(2.0 / M) * sinpi((double)p / (2.0 * M));
+        v = m == 0 || m == M ? 0.0 : sigma * sinpi((double)m / (double)M);
+        if (prod == 1 && 2 * n == M) v *= 0.5;
+    }
+    X[i] = v;
+}
+
+// Kernel shapes, and the smallest that holds a chain length at NT = 1.
+enum { kS1x2, kS1x4, kS1x8, kS1x8b, kS3x8, kShapes };
+int small_shape(int M)
+{
+    const int RT = half_tiles(M);
+    return RT <= 2 ? kS1x2 : RT <= 4 ? kS1x4 : RT <= 8 ? kS1x8 : kS1x8b;
+}
+constexpr int kLargeMaxM = 256;  // RT <= 8: one row tile per wavefront
+
+size_t lds_bytes(int shape, int M)
+{
+    const size_t Hp = 16 * (size_t)half_tiles(M);
+    return sizeof(double) * (6 * Hp + (shape == kS3x8 ? 6 : 4) * Hp * 16);
+}
+int tile_chains(int shape) { return shape == kS3x8 ? kLargeTile : kSmallTile; }
+
+// 16-chain tiles when they fill the GPU as well as 5-chain tiles do: a
+// 16-chain workgroup takes the time of about 2.6 5-chain ones (it reads each
+// table fragment once for 48 columns), so the rounds of the two shapes are
+// compared at that price.
+bool large_tiles_pay(int M, int n, int ncu)
+{
+    if (M > kLargeMaxM || half_tiles(M) <= 4) return false;
+    const int w3 = (n + kLargeTile - 1) / kLargeTile, w1 = (n + kSmallTile - 1) / kSmallTile;
+    const int r3 = (w3 + ncu - 1) / ncu, r1 = (w1 + ncu - 1) / ncu;
+    return 2.6 * r3 < (double)r1;
+}
+
+hipError_t launch_shape(int shape, size_t lds, int nitems, const Launch64 &la, hipStream_t st)
+{
+    if (nitems <= 0 || la.n_steps <= 0) return hipSuccess;
+    switch (shape) {
+    case kS1x2:
+        hipLaunchKernelGGL((modes64_kernel<1, 2, 1>), dim3(nitems), dim3(128), lds, st, la);
+        break;
+    case kS1x4:
+        hipLaunchKernelGGL((modes64_kernel<1, 4, 1>), dim3(nitems), dim3(256), lds, st, la);
+        break;
+    case kS1x8:
+        hipLaunchKernelGGL((modes64_kernel<1, 8, 1>), dim3(nitems), dim3(512), lds, st, la);
+        break;
+    case kS1x8b:
+        hipLaunchKernelGGL((modes64_kernel<1, 8, 2>), dim3(nitems), dim3(512), lds, st, la);
+        break;
+    case kS3x8:
+        hipLaunchKernelGGL((modes64_kernel<3, 8, 1>), dim3(nitems), dim3(512), lds, st, la);
+        break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+Launch64 launch_args(uint64_t seed, int64_t step0, const int64_t *d_step, int n_steps,
+                     int nonlinear)
+{
+    Launch64 la{};
+    la.step = d_step;
+    la.step0 = step0;
+    la.seed = seed;
+    la.n_steps = n_steps;
+    la.nonlinear = nonlinear;
+    return la;
+}
+
+}  // namespace
+
+size_t modes64_table_bytes(int M)
+{
+    const size_t RT = half_tiles(M);
+    return sizeof(double) * 2 * RT * 2 * RT * 256;
+}
+
+hipError_t modes64_build_tables(double *X, int M, hipStream_t st)
+{
+    const size_t n = modes64_table_bytes(M) / sizeof(double);
+    hipLaunchKernelGGL(modes64_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, X,
+                       M);
+    return hipGetLastError();
+}
+
+// Mode tiles whose coupling can change the update: for modes that
+// equilibrate within a step C_p falls off as exp(-16 nu s^4 dtau) (Eq. f4).
+// |Delta H_p| <= 2 s_p * |g| sqrt(M) (column norm 2 s_p from Eq. e6).  Tiles are
+// kept up to the first whose lowest mode has C_p 2 s_p sqrt(M) < 2^-100 W_p
+// (beyond it the exponential falls further), which leaves out what is below
+// the last bit of the noise term for |g| up to 2^47.  Logarithms, because C_p
+// underflows.
+int modes64_coupled_tiles(int M, double nu, double T_star, double dtau)
+{
+    const int RT = half_tiles(M);
+    for (int T = 1; T < RT; ++T) {
+        const double s = std::sin(3.141592653589793 * 32 * T / (2.0 * M)), s2 = s * s;
+        const double z = 16.0 * nu * s2 * s2, dz = (1.0 - 2.0 * nu) * 4.0 * s2;
+        const double w2 = z > 0.0 ? -T_star * std::expm1(-2.0 * z * dtau) / z
+                                  : 2.0 * T_star * dtau;
+        const double lc = -z * dtau + std::log(-std::expm1(-dz * dtau) / dz);
+        if (lc + std::log(2.0 * s * std::sqrt((double)M)) <
+            -100.0 * 0.6931471805599453 + 0.5 * std::log(w2))
+            return T;
+    }
+    return RT;
+}
+
+void modes64_plan_free(Modes64Plan &p)
+{
+    for (Modes64Group &g : p.groups) {
+        if (g.d_buckets) (void)hipFree(g.d_buckets);
+        if (g.d_items) (void)hipFree(g.d_items);
+    }
+    p.groups.clear();
+}
+
+// Buckets on 16-chain tiles get a launch each.  Those on 5-chain tiles share
+// one launch in the widest of their shapes while it is small (all lengths in
+// flight at once; the spare wavefronts of the shorter chains only wait), and
+// get one launch per shape beyond that, where each fills the GPU by itself.
+hipError_t modes64_plan(Modes64Plan &p, const std::vector<Modes64Args> &bs, int ncu,
+                        hipStream_t st)
+{
+    modes64_plan_free(p);
+    std::vector<int> shape(bs.size());
+    int widest = 0;
+    size_t small_tiles = 0;
+    for (size_t b = 0; b < bs.size(); ++b) {
+        if (large_tiles_pay(bs[b].M, bs[b].n, ncu)) {
+            shape[b] = kS3x8;
+            continue;
+        }
+        shape[b] = small_shape(bs[b].M);
+        widest = std::max(widest, shape[b]);
+        small_tiles += (size_t)(bs[b].n + kSmallTile - 1) / kSmallTile;
+    }
+    if (small_tiles <= 2 * (size_t)ncu)
+        for (int &s : shape)
+            if (s != kS3x8) s = widest;
+    for (int s = 0; s < kShapes; ++s) {
+        std::vector<size_t> in;
+        for (size_t b = 0; b < bs.size(); ++b)
+            if (shape[b] == s) in.push_back(b);
+        if (in.empty()) continue;
+        // longest chains first: an in-order dispatch is then a longest-first
+        // schedule
+        std::stable_sort(in.begin(), in.end(), [&](size_t x, size_t y) { return bs[x].M > bs[y].M; });
+        Modes64Group g;
+        g.shape = s;
+        std::vector<Modes64Args> ba;
+        std::vector<Item64> items;
+        for (size_t b : in) {
+            const int nt = (bs[b].n + tile_chains(s) - 1) / tile_chains(s);
+            for (int t = 0; t < nt; ++t) items.push_back({(int)ba.size(), t});
+            ba.push_back(bs[b]);
+            g.lds = std::max(g.lds, lds_bytes(s, bs[b].M));
+        }
+        g.nitems = (int)items.size();
+        g.single = ba.size() == 1;
+        g.one = ba[0];
+        hipError_t e = hipSuccess;
+        if (!g.single) {
+            if ((e = hipMalloc(&g.d_buckets, sizeof(Modes64Args) * ba.size())) == hipSuccess &&
+                (e = hipMalloc(&g.d_items, sizeof(Item64) * items.size())) == hipSuccess &&
+                (e = hipMemcpyAsync(g.d_buckets, ba.data(), sizeof(Modes64Args) * ba.size(),
+                                    hipMemcpyHostToDevice, st)) == hipSuccess &&
+                (e = hipMemcpyAsync(g.d_items, items.data(), sizeof(Item64) * items.size(),
+                                    hipMemcpyHostToDevice, st)) == hipSuccess)
+                e = hipStreamSynchronize(st);  // the host vectors die here
+        }
+        p.groups.push_back(g);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t modes64_launch(const Modes64Plan &p, uint64_t seed, int64_t step0,
+                          const int64_t *d_step, int n_steps, int nonlinear, hipStream_t st)
+{
+    for (const Modes64Group &g : p.groups) {
+        Launch64 la = launch_args(seed, step0, d_step, n_steps, nonlinear);
+        la.one = g.one;
+        la.buckets = static_cast<const Modes64Args *>(g.d_buckets);
+        la.items = static_cast<const Item64 *>(g.d_items);
+        const hipError_t e = launch_shape(g.shape, g.lds, g.nitems, la, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t modes64_launch_one(const Modes64Args &a, int ncu, uint64_t seed, int64_t step0,
+                              int n_steps, int nonlinear, hipStream_t st)
+{
+    const int shape = large_tiles_pay(a.M, a.n, ncu) ? kS3x8 : small_shape(a.M);
+    Launch64 la = launch_args(seed, step0, nullptr, n_steps, nonlinear);
+    la.one = a;
+    return launch_shape(shape, lds_bytes(shape, a.M),
+                        (a.n + tile_chains(shape) - 1) / tile_chains(shape), la, st);
+}
+
+}  // namespace dm

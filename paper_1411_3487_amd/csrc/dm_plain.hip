@@ -1,5 +1,7 @@
-// dm_plain.hip -- the plain FP64 form of the mode step and the bead-space
-// Euler baseline, as separate kernels (gfx950).
+// dm_plain.hip -- FP64 kernels (gfx950): the dense transforms (positions and
+// initial amplitudes of every path, and the mode step of chains beyond the
+// persistent stepper, with its force stencil and mode update), the bead-space
+// Euler baseline, observables, Monte Carlo and the inextensible limit.
 //
 // Data layout in HBM: a bucket of nch chains of M beads stores positions,
 // forces and mode amplitudes as nch*3 columns of M doubles (SoA, column

@@ -1,11 +1,11 @@
-// dm_static.hip -- the FP64 plain-form mode step without allocation
+// dm_static.hip -- the FP64 mode step without allocation
 // (dm_step_modes_f64_static in dnamodes.h).
 //
 // Callers that may not allocate device memory pass their own mode
 // amplitudes; the transform tables, the one-step coefficients, the chain
-// indices and the two work buffers of the step (positions, reused for the
-// coupling, and forces) live in one file-scope device array, `scratch`,
-// which every GPU the library runs on holds until the process ends.  Its
+// indices and, for chains beyond the persistent stepper (dm_modes64.hip), the
+// two work buffers of the dense step (positions, reused for the coupling,
+// and forces) live in one file-scope device array, `scratch`, which every GPU the library runs on holds until the process ends.  Its
 // device address is taken once per device with hipGetSymbolAddress (the
 // array's name is only a host-side stand-in) and used wherever host code
 // needs it.  The tables are rebuilt on the device at every call, and every
@@ -21,6 +21,7 @@
 
 #include "../../include/dnamodes.h"
 #include "dm_internal.h"
+#include "dm_modes64.h"
 
 namespace dm {
 namespace {
@@ -43,7 +44,7 @@ int fail(int code, const char *fmt, ...)
     return code;
 }
 
-// Bytes of the array used for M beads and n chains (each part 256-aligned):
+// Bytes of the array admitted for M beads and n chains (each part 256-aligned):
 // inverse and forward tables (M x M each), E, C, W (M each), chain indices,
 // and two work buffers of 3 M n doubles.
 size_t part(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
@@ -160,22 +161,53 @@ extern "C" int dm_step_modes_f64_static(double *R_dev, int32_t n_chains, int32_t
         q += part(bytes);
         return p;
     };
-    double *Ainv = (double *)take(8 * mm), *Afwd = (double *)take(8 * mm);
+    hipStream_t st = (hipStream_t)hip_stream;
+    const double lin = 1.0 - 2.0 * nu, gdt = gamma_dot * dtau;
     double *E = (double *)take(8 * (size_t)M), *C = (double *)take(8 * (size_t)M),
            *W = (double *)take(8 * (size_t)M);
     int32_t *ids = (int32_t *)take(4 * (size_t)n_chains);
-    double *rwork = (double *)take(8 * w), *Fwork = (double *)take(8 * w);
-    hipStream_t st = (hipStream_t)hip_stream;
-    hipLaunchKernelGGL(static_phi_kernel, dim3((unsigned)((mm + 255) / 256)), dim3(256), 0, st,
-                       Ainv, Afwd, M);
+    const int nt = M > n_chains ? M : n_chains;
+    hipLaunchKernelGGL(static_coef_kernel, dim3((nt + 255) / 256), dim3(256), 0, st, E, C, W, ids,
+                       M, n_chains, nu, T_star, dtau, chain0);
     hipError_t e = hipGetLastError();
+    if (modes64_supports(M)) {
+        // the persistent stepper needs its tables alone (at most 2 MB; with the
+        // coefficients they fit the array beside any chain count that
+        // static_bytes admits)
+        double *X = (double *)take(modes64_table_bytes(M));
+        Modes64Args a;
+        a.X = X;
+        a.E = E;
+        a.C = C;
+        a.W = W;
+        a.R = R_dev;
+        a.ids = ids;
+        a.n = n_chains;
+        a.M = M;
+        a.jc = modes64_coupled_tiles(M, nu, T_star, dtau);
+        a.lin = lin;
+        a.gdt = gdt;
+        int dev = 0, ncu = 0;
+        if (e == hipSuccess) e = hipGetDevice(&dev);
+        if (e == hipSuccess)
+            e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e == hipSuccess) e = modes64_build_tables(X, M, st);
+        constexpr int64_t kPerLaunch = 1 << 16;
+        for (int64_t s = 0; s < n_steps && e == hipSuccess; s += kPerLaunch)
+            e = modes64_launch_one(a, ncu > 0 ? ncu : 1, seed, step0 + s,
+                                   (int)(n_steps - s < kPerLaunch ? n_steps - s : kPerLaunch),
+                                   nonlinear ? 1 : 0, st);
+        if (e != hipSuccess)
+            return fail(DM_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
+        return DM_OK;
+    }
+    double *Ainv = (double *)take(8 * mm), *Afwd = (double *)take(8 * mm);
+    double *rwork = (double *)take(8 * w), *Fwork = (double *)take(8 * w);
     if (e == hipSuccess) {
-        const int nt = M > n_chains ? M : n_chains;
-        hipLaunchKernelGGL(static_coef_kernel, dim3((nt + 255) / 256), dim3(256), 0, st, E, C, W,
-                           ids, M, n_chains, nu, T_star, dtau, chain0);
+        hipLaunchKernelGGL(static_phi_kernel, dim3((unsigned)((mm + 255) / 256)), dim3(256), 0, st,
+                           Ainv, Afwd, M);
         e = hipGetLastError();
     }
-    const double lin = 1.0 - 2.0 * nu, gdt = gamma_dot * dtau;
     for (int64_t s = 0; s < n_steps && e == hipSuccess; ++s) {
         if (nonlinear) {
             e = launch_gemm_f64(Ainv, R_dev, rwork, M, 3 * n_chains, st);
