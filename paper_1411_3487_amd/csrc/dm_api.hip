@@ -55,11 +55,11 @@ struct Bucket {
     double *d_ccount = nullptr;      // n: samples written to the ring
     // Metropolis sampler (allocated on first use)
     double *d_chiT = nullptr;        // chi_{n,p} at [p][n-1], M x (M-1)
-    double *d_mcstep = nullptr;      // proposal half-widths s_p
+    double *d_mcstep = nullptr;      // proposal half-widths s_p, then zeta^l_p
     int64_t *d_mcacc = nullptr;      // accepted proposals per chain
     double *d_wlc = nullptr;         // scratch of the inextensible limit
     std::vector<double> zeta_l;      // host zeta^l_p of the current parameters
-    std::vector<double> mcstep_h;    // host copy of s_p (kept alive for the upload)
+    std::vector<double> mcstep_h;    // host copy of them (kept alive for the upload)
     double *d_cm0 = nullptr;         // n*3
     dm::FusedBucket fused;           // reduced-precision state and tables
 };
@@ -912,8 +912,8 @@ int dm_step_mc(dm_ctx *ctx, int64_t n_sweeps, double step_scale, int64_t *accept
     if (!(step_scale >= 0.0) || !std::isfinite(step_scale))
         return fail(ctx, DM_EINVAL, "step_scale must be finite and >= 0");
     for (Bucket &b : ctx->buckets)
-        if (48 * (size_t)b.M > 64 * 1024)
-            return fail(ctx, DM_EINVAL, "Monte Carlo needs M <= 1365 (LDS), got %d", b.M);
+        if (b.M > dm::kMcMaxM)
+            return fail(ctx, DM_EINVAL, "Monte Carlo needs M <= 1365, got %d", b.M);
     if (accepted) *accepted = 0;
     if (n_sweeps == 0) return DM_OK;
     const bool fused = fused_precision(ctx->precision);
@@ -926,16 +926,18 @@ int dm_step_mc(dm_ctx *ctx, int64_t n_sweeps, double step_scale, int64_t *accept
                 for (int n = 1; n < M; ++n)
                     chiT[(size_t)p * NB + n - 1] = phi[(size_t)n * M + p] - phi[(size_t)(n - 1) * M + p];
             int rc;
-            if ((rc = dalloc(ctx, &b.d_chiT, chiT.size())) || (rc = dalloc(ctx, &b.d_mcstep, M)) ||
+            if ((rc = dalloc(ctx, &b.d_chiT, chiT.size())) || (rc = dalloc(ctx, &b.d_mcstep, 2 * (size_t)M)) ||
                 (rc = dalloc(ctx, &b.d_mcacc, b.n)))
                 return rc;
             DM_HIP(ctx, hipMemcpy(b.d_chiT, chiT.data(), sizeof(double) * chiT.size(),
                                   hipMemcpyHostToDevice));
         }
-        b.mcstep_h.assign(M, 0.0);
-        for (int p = 1; p < M; ++p)
+        b.mcstep_h.assign(2 * (size_t)M, 0.0);
+        for (int p = 1; p < M; ++p) {
             b.mcstep_h[p] = step_scale * std::sqrt(ctx->T_star / b.zeta_l[p]);
-        DM_HIP(ctx, hipMemcpyAsync(b.d_mcstep, b.mcstep_h.data(), sizeof(double) * M,
+            b.mcstep_h[M + p] = b.zeta_l[p];
+        }
+        DM_HIP(ctx, hipMemcpyAsync(b.d_mcstep, b.mcstep_h.data(), sizeof(double) * 2 * M,
                                    hipMemcpyHostToDevice, ctx->stream));
         if (fused) DM_HIP(ctx, dm::fused_unpack_modes(b.fused, b.d_R64, b.M, b.n, ctx->stream));
     }
@@ -946,8 +948,8 @@ int dm_step_mc(dm_ctx *ctx, int64_t n_sweeps, double step_scale, int64_t *accept
         if (ctx->sample_every > 0)
             chunk = std::min<int64_t>(chunk, ctx->sample_every - ctx->step % ctx->sample_every);
         for (Bucket &b : ctx->buckets) {
-            DM_HIP(ctx, dm::launch_mc(b.d_R64, b.d_chiT, b.d_mcstep, b.d_ids, b.M, b.n, ctx->nu,
-                                      ctx->T_star, ctx->seed, ctx->step, (int)chunk, b.d_mcacc,
+            DM_HIP(ctx, dm::launch_mc(b.d_R64, b.d_chiT, b.d_mcstep, b.d_mcstep + b.M, b.d_ids, b.M,
+                                      b.n, ctx->T_star, ctx->seed, ctx->step, (int)chunk, b.d_mcacc,
                                       ctx->stream));
             if (fused) DM_HIP(ctx, dm::fused_pack_modes(b.fused, b.d_R64, b.M, b.n, ctx->stream));
             h.resize(b.n);

@@ -520,77 +520,156 @@ __global__ __launch_bounds__(64) void chain_obs_kernel(const double *__restrict_
     }
 }
 
+// Sum over the wavefront, in every lane: DPP row shifts and row broadcasts
+// (two 32-bit moves and an add each, no LDS crossbar), then lane 63's value
+// through a scalar register.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xF, true);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xF, true);
+    return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double read_lane(double v, int lane)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_total(double v)
+{
+    v = dpp_add<0x111, 0xF>(v);  // row_shr:1, 2, 4, 8: lane 15 of a row holds its sum
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return read_lane(v, 63);
+}
+
 // Metropolis Monte Carlo in the mode representation, one wavefront per
 // chain (the paper's equilibrium benchmark, Sec. V.B).  A sweep proposes, for
 // p = 1..M-1 and component a = x, y, z in order, R_p^a += delta with delta
 // uniform on (-s_p, s_p), and accepts with probability
-// min(1, exp(-dH'/T*)) for the reduced Hamiltonian of Eq. (b3).  The bond
-// vectors u_n (n = 1..M-1) live in LDS; a move shifts every bond by
-// chi_{n,p} delta along a, so dH' is a sum over bonds of the change of
-// (|u_n| - 1)^2 / 2 and of -nu u_n . u_{n+1}, reduced over the wavefront
-// (every lane ends with the same sum, hence the same decision).  Random
+// min(1, exp(-dH'/T*)) for the reduced Hamiltonian of Eq. (b3).  Random
 // numbers: Philox block (p, chain, sweep, a, tag 2), word 0 for delta, word 1
-// for the acceptance test.
+// for the acceptance test u < exp(-dH'/T*), i.e. dH' < -T* ln u.
+//
+// The quadratic part of H' is diagonal in the modes (Eqs. c6, c9), so
+//   dH' = zeta^l_p (R_p^a delta + delta^2 / 2) - sum_n (|u'_n| - |u_n|):
+// a move costs one square root and about five operations per bond.  It is
+// accepted when sum_n (|u'_n| - |u_n|) > thr with
+//   thr = zeta^l_p (R_p^a delta + delta^2 / 2) + T* ln u,
+// which needs nothing of the bonds: lane i draws delta and thr of proposal i
+// of a batch of 63 (21 modes) and the proposals read them from that lane.
+// The bonds u_n, their squares and lengths stay in registers, BPL bonds
+// n = lane + 64 b per lane; squares and lengths are formed from the bonds
+// anew at every sweep.
+//
+// Bound by the chain of dependent proposals: 0.22 us each at 128 beads, most
+// of it the latency of the square root and of the sum over the wavefront
+// (1.2 us with the bonds in LDS, every lane drawing the same random numbers,
+// two square roots per bond and the sum over the LDS crossbar).
+constexpr int kMcBatch = 21;  // modes of a batch
+template <int BPL>
 __global__ __launch_bounds__(64) void mc_kernel(double *__restrict__ R,
                                                 const double *__restrict__ chiT,
                                                 const double *__restrict__ sstep,
+                                                const double *__restrict__ zeta_l,
                                                 const int32_t *__restrict__ ids, int M,
-                                                double nu, double T_star, uint64_t seed,
-                                                int64_t step0, int n_sweeps,
-                                                int64_t *__restrict__ accepted)
+                                                double T_star, uint64_t seed, int64_t step0,
+                                                int n_sweeps, int64_t *__restrict__ accepted)
 {
-    extern __shared__ double mcl[];  // u[3][M-1], then the amplitudes R[3][M]
+    extern __shared__ double Rl[];  // the amplitudes R[3][M], for the first bonds only
     const int c = blockIdx.x, lane = threadIdx.x, NB = M - 1;
-    double *u = mcl, *Rl = mcl + 3 * NB;
     double *Rc = R + (size_t)c * 3 * M;
     const uint32_t chain = (uint32_t)ids[c];
     for (int i = lane; i < 3 * M; i += 64) Rl[i] = Rc[i];
     __syncthreads();
-    // u_n = sum_{p >= 1} chi_{n,p} R_p
-    for (int n = lane; n < NB; n += 64)
-        for (int a = 0; a < 3; ++a) {
-            double s = 0.0;
-            for (int p = 1; p < M; ++p) s += chiT[(size_t)p * NB + n] * Rl[a * M + p];
-            u[a * NB + n] = s;
+    double u[3][BPL], l2[BPL], l[BPL], ch[BPL], nx[BPL];
+    // chi of mode p at the own bonds, 0 where there is no bond
+    auto load_chi = [&](int p, double (&d)[BPL]) {
+#pragma unroll
+        for (int b = 0; b < BPL; ++b) {
+            const int n = lane + 64 * b;
+            const double v = chiT[(size_t)p * NB + min(n, NB - 1)];
+            d[b] = n < NB ? v : 0.0;
         }
-    __syncthreads();
-    int64_t acc = 0;
-    const double two_m32 = 2.3283064365386962890625e-10;
-    for (int s = 0; s < n_sweeps; ++s) {
-        const int64_t k = step0 + s;
-        for (int p = 1; p < M; ++p) {
-            const double sp = sstep[p];
-            const double *chi = chiT + (size_t)p * NB;
-            for (int a = 0; a < 3; ++a) {
-                const Block4 x = noise_bits(seed, (uint32_t)p, chain, k, (uint32_t)a, kTagMC);
-                const double u0 = ((double)x.v[0] + 0.5) * two_m32;
-                const double u1 = ((double)x.v[1] + 0.5) * two_m32;
-                const double delta = sp * (2.0 * u0 - 1.0);
-                double d = 0.0;
-                for (int n = lane; n < NB; n += 64) {
-                    const double ch = chi[n], ua = u[a * NB + n];
-                    const double ux = u[n], uy = u[NB + n], uz = u[2 * NB + n];
-                    const double l2 = ux * ux + uy * uy + uz * uz;
-                    const double l2n = l2 + ch * delta * (2.0 * ua + ch * delta);
-                    const double lo = sqrt(l2) - 1.0, ln = sqrt(l2n) - 1.0;
-                    d += 0.5 * (ln * ln - lo * lo);
-                    if (n + 1 < NB) {
-                        const double ch1 = chi[n + 1], ua1 = u[a * NB + n + 1];
-                        d -= nu * (delta * (ch * ua1 + ch1 * ua) + delta * delta * ch * ch1);
-                    }
-                }
-                d = wave_sum(d);
-                if (u1 < exp(-d / T_star)) {
-                    __syncthreads();  // every lane has read the old bonds
-                    for (int n = lane; n < NB; n += 64) u[a * NB + n] += chi[n] * delta;
-                    if (lane == 0) Rl[a * M + p] += delta;
-                    ++acc;
-                    __syncthreads();
-                }
-            }
+    };
+    // u_n = sum_{p >= 1} chi_{n,p} R_p
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < BPL; ++b) u[a][b] = 0.0;
+    for (int p = 1; p < M; ++p) {
+        load_chi(p, ch);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const double r = Rl[a * M + p];
+#pragma unroll
+            for (int b = 0; b < BPL; ++b) u[a][b] = fma64(ch[b], r, u[a][b]);
         }
     }
-    for (int i = lane; i < 3 * M; i += 64) Rc[i] = Rl[i];
+    int64_t acc = 0;
+    const double two_m32 = 2.3283064365386962890625e-10;
+    // sqrt64 takes no 0: the offset is below the last bit of any bond
+    constexpr double kTiny = 1e-300;
+    load_chi(1, nx);
+    for (int s = 0; s < n_sweeps; ++s) {
+        const int64_t k = step0 + s;
+#pragma unroll
+        for (int b = 0; b < BPL; ++b) {
+            l2[b] = fma64(u[0][b], u[0][b], fma64(u[1][b], u[1][b], u[2][b] * u[2][b]));
+            l[b] = sqrt64(l2[b] + kTiny);
+        }
+        for (int pb = 1; pb < M; pb += kMcBatch) {
+            const int np = min(kMcBatch, M - pb);
+            const int a0 = lane % 3, p0 = pb + lane / 3;
+            const bool mine = lane < 3 * np;
+            const int pr = mine ? p0 : 1;
+            double *slot = Rc + (size_t)a0 * M + pr;
+            const double r = *slot;
+            const Block4 x = noise_bits(seed, (uint32_t)pr, chain, k, (uint32_t)a0, kTagMC);
+            const double u0 = ((double)x.v[0] + 0.5) * two_m32;
+            const double delta = sstep[pr] * (2.0 * u0 - 1.0);
+            const double thr =
+                zeta_l[pr] * delta * (r + 0.5 * delta) - 0.5 * T_star * neg2log_u32(x.v[1]);
+            uint64_t taken = 0;
+            for (int i = 0; i < np; ++i) {
+                const int p = pb + i;
+#pragma unroll
+                for (int b = 0; b < BPL; ++b) ch[b] = nx[b];
+                load_chi(p + 1 < M ? p + 1 : 1, nx);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const double d = read_lane(delta, 3 * i + a);
+                    double sh[BPL], l2n[BPL], ln[BPL], sum = 0.0;
+#pragma unroll
+                    for (int b = 0; b < BPL; ++b) {
+                        sh[b] = ch[b] * d;
+                        l2n[b] = fma64(sh[b], fma64(2.0, u[a][b], sh[b]), l2[b]);
+                        ln[b] = sqrt64(l2n[b] + kTiny);
+                        sum += ln[b] - l[b];
+                    }
+                    if (wave_total(sum) > read_lane(thr, 3 * i + a)) {
+                        taken |= 1ull << (3 * i + a);
+#pragma unroll
+                        for (int b = 0; b < BPL; ++b) {
+                            u[a][b] += sh[b];
+                            l2[b] = l2n[b];
+                            l[b] = ln[b];
+                        }
+                    }
+                }
+            }
+            if (mine && ((taken >> lane) & 1)) *slot = r + delta;
+            acc += __popcll(taken);
+        }
+    }
     if (lane == 0) accepted[c] = acc;
 }
 
@@ -1204,15 +1283,27 @@ hipError_t launch_wlc(double *pos, double *scr, const int32_t *ids, int M, int n
     return hipGetLastError();
 }
 
-hipError_t launch_mc(double *R, const double *chiT, const double *sstep, const int32_t *ids,
-                     int M, int nch, double nu, double T_star, uint64_t seed, int64_t step0,
-                     int n_sweeps, int64_t *accepted, hipStream_t st)
+hipError_t launch_mc(double *R, const double *chiT, const double *sstep, const double *zeta_l,
+                     const int32_t *ids, int M, int nch, double T_star, uint64_t seed,
+                     int64_t step0, int n_sweeps, int64_t *accepted, hipStream_t st)
 {
     if (nch == 0 || n_sweeps == 0) return hipSuccess;
-    const size_t lds = sizeof(double) * (3 * (size_t)(M - 1) + 3 * (size_t)M);
-    if (M < 2 || lds > 64 * 1024) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(mc_kernel, dim3(nch), dim3(64), lds, st, R, chiT, sstep, ids, M, nu,
-                       T_star, seed, step0, n_sweeps, accepted);
+    const size_t lds = sizeof(double) * 3 * (size_t)M;
+    if (M < 2 || M > kMcMaxM) return hipErrorInvalidValue;
+    const int per_lane = (M - 1 + 63) / 64;
+#define DM_MC(B)                                                                               \
+    hipLaunchKernelGGL(mc_kernel<B>, dim3(nch), dim3(64), lds, st, R, chiT, sstep, zeta_l, ids, \
+                       M, T_star, seed, step0, n_sweeps, accepted)
+    if (per_lane <= 1) DM_MC(1);
+    else if (per_lane <= 2) DM_MC(2);
+    else if (per_lane <= 3) DM_MC(3);
+    else if (per_lane <= 4) DM_MC(4);
+    else if (per_lane <= 6) DM_MC(6);
+    else if (per_lane <= 8) DM_MC(8);
+    else if (per_lane <= 12) DM_MC(12);
+    else if (per_lane <= 16) DM_MC(16);
+    else DM_MC(22);
+#undef DM_MC
     return hipGetLastError();
 }
 
