@@ -950,25 +950,30 @@ __global__ __launch_bounds__(64) void wlc_wave_kernel(double *__restrict__ pos,
     }
 }
 
-// Chains of up to 64 beads: one wavefront per chain with bond n and bead n
-// in lane n and the whole chain in registers -- neighbours by cross-lane
-// reads (executed by every lane, then masked), the tension system by the
-// same cyclic reduction with identity rows in the lanes that hold no bond.
-// The noise blocks are drawn one per lane and handed to the beads that use
-// them.  Four chains per workgroup, one per wavefront, no LDS and no
-// barrier; the positions are rebuilt at the end in the serial order of the
-// other kernels.
-constexpr int kWlcRegMaxM = 64;
+// Chains of up to 256 beads in registers: G = 16, 32 or 64 lanes per chain, four
+// consecutive bonds per lane (lane q of the group holds bonds 4q+1 .. 4q+4 and
+// draws the noise of beads 4q .. 4q+3, one Philox block per component), so
+// most neighbours are in the lane and the others one lane away, by DPP.
+//
+// The tension rows are scaled to the diagonal -2 (by 1/|w|, w = u + u', in the
+// midpoint form, where the couplings become the cosines between midpoint
+// bonds, the same for both rows they join; by 1/(w.u) otherwise).  A lane
+// eliminates its first three tensions by hand (the first and the third
+// without a division), which leaves one tridiagonal row per lane in its
+// fourth; those are solved by parallel cyclic reduction over the lanes of
+// the group, rows kept at unit diagonal (one reciprocal a round), by DPP row
+// shifts where a group is a row of 16 lanes.
+//
+// Bound by FP64 issue: about 350 vector instructions a lane and cycle, two
+// wavefronts a SIMD at 8192 chains of 64 beads, where a step of 8 cycles
+// takes 18 us (86 us with one bond per lane: six rounds of reduction over
+// the LDS crossbar with two divisions each).
+constexpr int kWlcRegMaxM = 256;
 
-__device__ __forceinline__ double lane_read(double v, int src)
-{
-    return __shfl(v, src < 0 ? 0 : (src > 63 ? 63 : src), 64);
-}
-
-// The value of lane - 1 (lane 0 gets 0) or of lane + 1 (lane 63 gets 0): DPP
-// whole-wavefront shifts, two 32-bit moves per double, no LDS crossbar.
+// The value of v `S` lanes before (after) this one in its group, else 0;
+// gl = lane % G.
 template <int CTRL>
-__device__ __forceinline__ double wave_shift(double v)
+__device__ __forceinline__ double lane_shift(double v)
 {
     const uint64_t b = __builtin_bit_cast(uint64_t, v);
     const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF,
@@ -977,163 +982,263 @@ __device__ __forceinline__ double wave_shift(double v)
                                                               0xF, 0xF, true);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
-constexpr int kWaveShr1 = 0x138, kWaveShl1 = 0x130;
-__device__ __forceinline__ double from_prev(double v) { return wave_shift<kWaveShr1>(v); }
-__device__ __forceinline__ double from_next(double v) { return wave_shift<kWaveShl1>(v); }
+template <int G, int S = 1>
+__device__ __forceinline__ double from_prev(double v, int gl)
+{
+    if constexpr (G == 16) {
+        return lane_shift<0x110 + S>(v);  // row_shr
+    } else {
+        const double x = S == 1 ? lane_shift<0x138>(v)  // wave_shr:1
+                                : __shfl(v, (int)(threadIdx.x & 63) - S, 64);
+        return gl >= S ? x : 0.0;
+    }
+}
+template <int G, int S = 1>
+__device__ __forceinline__ double from_next(double v, int gl)
+{
+    if constexpr (G == 16) {
+        return lane_shift<0x100 + S>(v);  // row_shl
+    } else {
+        const double x = S == 1 ? lane_shift<0x130>(v)  // wave_shl:1
+                                : __shfl(v, (int)(threadIdx.x & 63) + S, 64);
+        return gl + S < G ? x : 0.0;
+    }
+}
 
+// 1 / x for normal x: one third-order step from the hardware's reciprocal.
+__device__ __forceinline__ double rcp64(double x)
+{
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma64(-x, y, 1.0);
+    return fma64(y, fma64(e, e, e), y);
+}
+
+// One round of cyclic reduction at distance S of the rows
+// A f_(lane-S) + f_lane + C f_(lane+S) = R.
+template <int G, int S>
+__device__ __forceinline__ void reduce_rows(double &A, double &C, double &R, int gl)
+{
+    const double Al = from_prev<G, S>(A, gl), Cl = from_prev<G, S>(C, gl),
+                 Rl = from_prev<G, S>(R, gl);
+    const double Ar = from_next<G, S>(A, gl), Cr = from_next<G, S>(C, gl),
+                 Rr = from_next<G, S>(R, gl);
+    const double i = rcp64(fma64(-C, Ar, fma64(-A, Cl, 1.0)));
+    R = fma64(-C, Rr, fma64(-A, Rl, R)) * i;
+    A = -A * Al * i;
+    C = -C * Cr * i;
+}
+
+template <int G, bool MID>
 __global__ __launch_bounds__(256) void wlc_reg_kernel(double *__restrict__ pos,
                                                       const int32_t *__restrict__ ids, int M,
                                                       int nch, double T_bar, double dt, int iters,
-                                                      double tol, int midpoint, uint64_t seed,
-                                                      int64_t step0, int n_steps)
+                                                      double tol, uint64_t seed, int64_t step0,
+                                                      int n_steps)
 {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int c = blockIdx.x * 4 + wv;
-    if (c >= nch) return;  // a whole wavefront
-    const int N = M - 1, nq = N / 4 + 1;
-    const bool bond = lane >= 1 && lane <= N;  // this lane's bond n = lane exists
-    const bool bead = lane <= N;
-    double *x = pos + (size_t)c * 3 * M;
-    const uint32_t chain = (uint32_t)ids[c];
+    const int lane = threadIdx.x & 63, gl = lane % G;
+    const int c0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 / G);
+    if (c0 >= nch) return;  // a whole wavefront
+    const int c = c0 + lane / G;
+    const bool live = c < nch;
+    const int N = M - 1, nl = (N + 3) / 4;  // lanes that hold bonds
+    double *x = pos + (size_t)(live ? c : 0) * 3 * M;
+    const uint32_t chain = live ? (uint32_t)ids[c] : 0u;
     const double amp = sqrt(2.0 * T_bar * dt);
-    double U[3] = {0.0, 0.0, 0.0};
-    if (bond) {  // bonds, scaled to unit length
-        double u[3], s2 = 0.0;
+    bool bond[4];
+    double U[3][4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {  // bonds, scaled to unit length
+        const int n = 4 * gl + 1 + m;
+        bond[m] = live && n <= N;
+        double s2 = 0.0;
+#pragma unroll
         for (int a = 0; a < 3; ++a) {
-            u[a] = x[a * M + lane] - x[a * M + lane - 1];
-            s2 += u[a] * u[a];
+            U[a][m] = bond[m] ? x[a * M + n] - x[a * M + n - 1] : 0.0;
+            s2 += U[a][m] * U[a][m];
         }
         const double inv = s2 > 0.0 ? 1.0 / sqrt(s2) : 0.0;
-        for (int a = 0; a < 3; ++a) U[a] = u[a] * inv;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) U[a][m] *= inv;
     }
-    double r0[3] = {x[0], x[M], x[2 * M]};  // used in lane 0
+    double r0[3];  // bead 0, in lane 0 of the group
+#pragma unroll
+    for (int a = 0; a < 3; ++a) r0[a] = live ? x[a * M] : 0.0;
     for (int s = 0; s < n_steps; ++s) {
         const int64_t k = step0 + s;
-        // noise: lane a nq + q draws block q of component a; bead n takes
-        // element n % 4 of block n / 4
-        double zb[4] = {0.0, 0.0, 0.0, 0.0};
-        if (lane < 3 * nq) {
-            const int a = lane / nq, q = lane - a * nq;
-            normals4_f64(noise_bits(seed, (uint32_t)q, chain, k, (uint32_t)a, kTagWLC), zb);
-        }
-        double NZ[3];
+        // noise of bead 0 and noise differences over the own bonds
+        double dz[3][4], z0[3];
+#pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const int src = a * nq + (lane >> 2);
-            const double z0 = lane_read(zb[0], src), z1 = lane_read(zb[1], src),
-                         z2 = lane_read(zb[2], src), z3 = lane_read(zb[3], src);
-            const int e = lane & 3;
-            const double z = e == 0 ? z0 : (e == 1 ? z1 : (e == 2 ? z2 : z3));
-            NZ[a] = bead ? amp * z : 0.0;
+            double z[4];
+            normals4_f64(noise_bits(seed, (uint32_t)gl, chain, k, (uint32_t)a, kTagWLC), z);
+            const double zn = from_next<G>(z[0], gl);
+            z0[a] = amp * z[0];
+            dz[a][0] = amp * (z[1] - z[0]);
+            dz[a][1] = amp * (z[2] - z[1]);
+            dz[a][2] = amp * (z[3] - z[2]);
+            dz[a][3] = amp * (zn - z[3]);
         }
-        double UN[3] = {U[0], U[1], U[2]};
-        double D[3], UM[3], UMl[3], UMr[3], F = 0.0;
+        double UN[3][4], d0[3] = {0.0, 0.0, 0.0};  // d0: displacement of bead 0
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) UN[a][m] = U[a][m];
+        bool active = live;  // this chain's cycle has not converged
         for (int it = 0; it < iters; ++it) {
-            double w[3];
-            {  // midpoint bonds
+            // midpoint bonds; sc scales the tension rows
+            double um[3][4], w[3][4], sc[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
                 double s2 = 0.0;
+#pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    w[a] = U[a] + UN[a];
-                    s2 += w[a] * w[a];
+                    w[a][m] = U[a][m] + UN[a][m];
+                    s2 = fma64(w[a][m], MID ? w[a][m] : U[a][m], s2);
                 }
-                const double inv = bond ? 1.0 / sqrt(s2) : 0.0;
-                for (int a = 0; a < 3; ++a) UM[a] = bond ? (midpoint ? w[a] * inv : U[a]) : 0.0;
-            }
-            double Dl[3];
-            for (int a = 0; a < 3; ++a) {  // bending gradients and bead displacements
-                UMl[a] = from_prev(UM[a]);
-                UMr[a] = from_next(UM[a]);
-                if (lane == 0) UMl[a] = 0.0;
-                if (lane == 63) UMr[a] = 0.0;
-                const double h = bond ? -(UMl[a] + UMr[a]) : 0.0;
-                const double h1 = from_next(h);
-                const double hn1 = lane + 1 <= N ? h1 : 0.0;
-                D[a] = bead ? (hn1 - h) * dt + NZ[a] : 0.0;
-                const double dprev = from_prev(D[a]);
-                Dl[a] = lane >= 1 ? dprev : 0.0;
-            }
-            // row n - 1 of the tension system in lane n; identity elsewhere
-            double ra = 0.0, rb = 1.0, rc = 0.0, rr = 0.0;
-            if (bond) {
-                double wl = 0.0, wm = 0.0, wr = 0.0, wd = 0.0;
-                for (int a = 0; a < 3; ++a) {
-                    wl += w[a] * UMl[a];
-                    wm += w[a] * UM[a];
-                    wr += w[a] * UMr[a];
-                    wd += w[a] * (D[a] - Dl[a]);
-                }
-                ra = wl * dt;
-                rb = -2.0 * wm * dt;
-                rc = wr * dt;
-                rr = -wd;
-            }
-            for (int sd = 1; sd < N; sd *= 2) {
-                const bool hasl = lane - sd >= 1, hasr = lane + sd <= N;
-                double la, lb, lc, lr, qa, qb, qc, qr;
-                if (sd == 1) {  // neighbours by DPP shifts
-                    la = from_prev(ra), lb = from_prev(rb), lc = from_prev(rc), lr = from_prev(rr);
-                    qa = from_next(ra), qb = from_next(rb), qc = from_next(rc), qr = from_next(rr);
+                if constexpr (MID) {
+                    const double inv = bond[m] ? rsqrt64(s2) : 0.0;
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) um[a][m] = w[a][m] * inv;
                 } else {
-                    la = lane_read(ra, lane - sd), lb = lane_read(rb, lane - sd);
-                    lc = lane_read(rc, lane - sd), lr = lane_read(rr, lane - sd);
-                    qa = lane_read(ra, lane + sd), qb = lane_read(rb, lane + sd);
-                    qc = lane_read(rc, lane + sd), qr = lane_read(rr, lane + sd);
-                }
-                double an = 0.0, cn = 0.0, bn = rb, dn = rr;
-                if (hasl) {
-                    const double al = -ra / lb;
-                    an = al * la;
-                    bn += al * lc;
-                    dn += al * lr;
-                }
-                if (hasr) {
-                    const double ga = -rc / qb;
-                    cn = ga * qc;
-                    bn += ga * qa;
-                    dn += ga * qr;
-                }
-                if (bond) {
-                    ra = an;
-                    rb = bn;
-                    rc = cn;
-                    rr = dn;
+                    sc[m] = bond[m] ? rcp64(s2) : 0.0;
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) um[a][m] = U[a][m];
                 }
             }
-            F = bond ? rr / rb : 0.0;
-            const double fl = from_prev(F), fr = from_next(F);
-            double change = 0.0;
-            if (bond) {  // bond update
-                for (int a = 0; a < 3; ++a) {
-                    const double v = U[a] + (D[a] - Dl[a]) +
-                                     ((lane >= 2 ? fl : 0.0) * UMl[a] - 2.0 * F * UM[a] +
-                                      (lane + 1 <= N ? fr : 0.0) * UMr[a]) * dt;
-                    change = fmax(change, fabs(v - UN[a]));
-                    UN[a] = v;
-                }
-            }
-            if (tol > 0.0) {  // the same maximum in every lane: a uniform exit
-                for (int o = 32; o >= 1; o >>= 1) change = fmax(change, __shfl_xor(change, o));
-                if (change <= tol) break;
-            }
-        }
-        {  // bead 0 moves with its own tension, bending and noise
-            const double F1 = lane_read(F, 1);
+            // bending gradients h_n = -(u^m_(n-1) + u^m_(n+1)) of the bonds and
+            // the differences dd of the regular bead displacements over them
+            double ul[3], ur[3], dd[3][4], h1[3];
+#pragma unroll
             for (int a = 0; a < 3; ++a) {
-                const double um1 = lane_read(UM[a], 1);
-                if (lane == 0) r0[a] += D[a] + F1 * um1 * dt;
+                ul[a] = from_prev<G>(um[a][3], gl);
+                ur[a] = from_next<G>(um[a][0], gl);
+                double h[4];
+                h[0] = -(ul[a] + um[a][1]);
+                h[1] = -(um[a][0] + um[a][2]);
+                h[2] = -(um[a][1] + um[a][3]);
+                h[3] = -(um[a][2] + ur[a]);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) h[m] = bond[m] ? h[m] : 0.0;
+                const double hl = from_prev<G>(h[3], gl), hr = from_next<G>(h[0], gl);
+                dd[a][0] = fma64(fma64(-2.0, h[0], hl + h[1]), dt, dz[a][0]);
+                dd[a][1] = fma64(fma64(-2.0, h[1], h[0] + h[2]), dt, dz[a][1]);
+                dd[a][2] = fma64(fma64(-2.0, h[2], h[1] + h[3]), dt, dz[a][2]);
+                dd[a][3] = fma64(fma64(-2.0, h[3], h[2] + hr), dt, dz[a][3]);
+                h1[a] = h[0];
+            }
+            // rows av f_(n-1) - 2 f_n + cv f_(n+1) = rv of the tensions times dt
+            double av[4], cv[4], rv[4];
+            auto dot = [](const double(&p)[3][4], int i, const double(&q)[3][4], int j) {
+                return fma64(p[0][i], q[0][j], fma64(p[1][i], q[1][j], p[2][i] * q[2][j]));
+            };
+            auto dot1 = [](const double(&p)[3][4], int i, const double(&q)[3]) {
+                return fma64(p[0][i], q[0], fma64(p[1][i], q[1], p[2][i] * q[2]));
+            };
+            if constexpr (MID) {
+                cv[0] = dot(um, 0, um, 1);
+                cv[1] = dot(um, 1, um, 2);
+                cv[2] = dot(um, 2, um, 3);
+                cv[3] = dot1(um, 3, ur);
+                av[0] = from_prev<G>(cv[3], gl);
+                av[1] = cv[0];
+                av[2] = cv[1];
+                av[3] = cv[2];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) rv[m] = -dot(um, m, dd, m);
+            } else {
+                av[0] = dot1(w, 0, ul) * sc[0];
+                cv[3] = dot1(w, 3, ur) * sc[3];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    if (m > 0) av[m] = dot(w, m, um, m - 1) * sc[m];
+                    if (m < 3) cv[m] = dot(w, m, um, m + 1) * sc[m];
+                    rv[m] = -dot(w, m, dd, m) * sc[m];
+                }
+            }
+            // f_m = al + be f_(previous lane's fourth) + ga f_3 for m = 0, 1, 2
+            const double i2 = rcp64(fma64(-av[1], cv[0], fma64(-cv[1], av[2], 4.0)));
+            const double al1 = -fma64(2.0, rv[1], fma64(av[1], rv[0], cv[1] * rv[2])) * i2;
+            const double be1 = av[1] * av[0] * i2, ga1 = cv[1] * cv[2] * i2;
+            const double al0 = 0.5 * fma64(cv[0], al1, -rv[0]);
+            const double be0 = 0.5 * fma64(cv[0], be1, av[0]), ga0 = 0.5 * (cv[0] * ga1);
+            const double al2 = 0.5 * fma64(av[2], al1, -rv[2]);
+            const double be2 = 0.5 * (av[2] * be1), ga2 = 0.5 * fma64(av[2], ga1, cv[2]);
+            // the fourth row, the next lane's first tension replaced likewise
+            const double aln = from_next<G>(al0, gl), ben = from_next<G>(be0, gl),
+                         gan = from_next<G>(ga0, gl);
+            const double ib = rcp64(fma64(av[3], ga2, fma64(cv[3], ben, -2.0)));
+            double A = av[3] * be2 * ib, C = cv[3] * gan * ib;
+            double F3 = fma64(-av[3], al2, fma64(-cv[3], aln, rv[3])) * ib;
+            if (1 < nl) reduce_rows<G, 1>(A, C, F3, gl);
+            if (2 < nl) reduce_rows<G, 2>(A, C, F3, gl);
+            if (4 < nl) reduce_rows<G, 4>(A, C, F3, gl);
+            if (8 < nl) reduce_rows<G, 8>(A, C, F3, gl);
+            if constexpr (G > 16) {
+                if (16 < nl) reduce_rows<G, 16>(A, C, F3, gl);
+                if (G > 32 && 32 < nl) reduce_rows<G, 32>(A, C, F3, gl);
+            }
+            const double Fl = from_prev<G>(F3, gl);
+            const double F0 = fma64(ga0, F3, fma64(be0, Fl, al0));
+            const double F1 = fma64(ga1, F3, fma64(be1, Fl, al1));
+            const double F2 = fma64(ga2, F3, fma64(be2, Fl, al2));
+            const double Fr = from_next<G>(F0, gl);
+            // new bonds
+            double change = 0.0;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double p0 = F0 * um[a][0], p1 = F1 * um[a][1], p2 = F2 * um[a][2],
+                             p3 = F3 * um[a][3];
+                double v[4];
+                v[0] = U[a][0] + dd[a][0] + fma64(-2.0, p0, fma64(Fl, ul[a], p1));
+                v[1] = U[a][1] + dd[a][1] + fma64(-2.0, p1, p0 + p2);
+                v[2] = U[a][2] + dd[a][2] + fma64(-2.0, p2, p1 + p3);
+                v[3] = U[a][3] + dd[a][3] + fma64(-2.0, p3, fma64(Fr, ur[a], p2));
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const double nv = bond[m] && active ? v[m] : UN[a][m];
+                    change = fmax(change, fabs(nv - UN[a][m]));
+                    UN[a][m] = nv;
+                }
+                if (active) d0[a] = fma64(h1[a], dt, z0[a]) + p0;
+            }
+            if (tol > 0.0) {  // the chain's largest change, in every lane of its group
+#pragma unroll
+                for (int o = G / 2; o >= 1; o >>= 1)
+                    change = fmax(change, __shfl_xor(change, o, 64));
+                active = active && !(change <= tol);
+                if (!__any(active)) break;
             }
         }
-        for (int a = 0; a < 3; ++a) U[a] = UN[a];
-    }
-    // positions: every lane forms the same serial sums, lane 0 stores them
-    double v[3];
-    for (int a = 0; a < 3; ++a) v[a] = __shfl(r0[a], 0, 64);
-    if (lane == 0)
-        for (int a = 0; a < 3; ++a) x[a * M] = v[a];
-    for (int n = 1; n <= N; ++n)
+#pragma unroll
         for (int a = 0; a < 3; ++a) {
-            v[a] += __shfl(U[a], n, 64);
-            if (lane == 0) x[a * M + n] = v[a];
+            r0[a] += d0[a];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) U[a][m] = UN[a][m];
         }
+    }
+    // positions: the running sums of the bonds, in the lane and then over the
+    // lanes of the group
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        double p[4];
+        p[0] = U[a][0];
+        p[1] = p[0] + U[a][1];
+        p[2] = p[1] + U[a][2];
+        p[3] = p[2] + U[a][3];
+        double run = p[3];  // inclusive sum over the lanes
+        for (int o = 1; o < G; o *= 2) {
+            const double q = __shfl(run, lane - o, 64);
+            if (gl >= o) run += q;
+        }
+        const double before = from_prev<G>(run, gl);
+        const double base = __shfl(r0[a], lane - gl, 64);
+        if (live) {
+            if (gl == 0) x[a * M] = base;
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                if (bond[m]) x[a * M + 4 * gl + 1 + m] = base + (before + p[m]);
+        }
+    }
 }
 
 // out[j] = sum_c acc[c][j]: kRedCols columns per workgroup (one 64-byte run of
@@ -1267,8 +1372,20 @@ hipError_t launch_wlc(double *pos, double *scr, const int32_t *ids, int M, int n
     if (nch == 0 || n_steps == 0) return hipSuccess;
     if (M < 2 || iters < 1) return hipErrorInvalidValue;
     if (M <= kWlcRegMaxM) {
-        hipLaunchKernelGGL(wlc_reg_kernel, dim3((nch + 3) / 4), dim3(256), 0, st, pos, ids, M, nch,
-                           T_bar, dt, iters, tol, midpoint, seed, step0, n_steps);
+        const int G = M <= 64 ? 16 : M <= 128 ? 32 : 64, per_wg = 4 * (64 / G);
+#define DM_WLC(G, MID)                                                                          \
+    hipLaunchKernelGGL((wlc_reg_kernel<G, MID>), dim3((nch + per_wg - 1) / per_wg), dim3(256), 0, \
+                       st, pos, ids, M, nch, T_bar, dt, iters, tol, seed, step0, n_steps)
+        if (midpoint) {
+            if (G == 16) DM_WLC(16, true);
+            else if (G == 32) DM_WLC(32, true);
+            else DM_WLC(64, true);
+        } else {
+            if (G == 16) DM_WLC(16, false);
+            else if (G == 32) DM_WLC(32, false);
+            else DM_WLC(64, false);
+        }
+#undef DM_WLC
         return hipGetLastError();
     }
     const size_t lds = sizeof(double) * wlc_lds_doubles(M);
