@@ -913,7 +913,7 @@ def main():
                    autotune=not args.no_autotune, table_mode=args.table_mode)
     tiling, report = ctx.tiling()[0], ctx.tuning_report()
     shape = {0: "resident" if tiling["resident"] else "streamed", 1: "split",
-             2: "split8"}[int(tiling["split"])]
+             2: "split8", 3: "tile16"}[int(tiling["split"])]
     ctx.step_modes(warmup)
     torch.cuda.synchronize()
     n0 = ctx.accumulators()[0]["n_samples"]
@@ -929,7 +929,9 @@ def main():
     # dominant kernel alone, in the launch shape of the timed loop: one fused
     # launch covers the steps between two observable samples
     ctx.set_params([M], [args.dtau], T_star=T_STAR_DSDNA, nu=NU_DSDNA, sample_every=0,
-                   tiles_per_wg=int(tiling["tpw"]), table_mode=shape)
+                   # (16-chain tiles are the untimed default where the autotuner takes them)
+                   tiles_per_wg=0 if shape == "tile16" else int(tiling["tpw"]),
+                   table_mode="auto" if shape == "tile16" else shape)
     k_launch = se if se > 0 else 100
     # launch durations settle over the first ~20 launches after the
     # autotuner (about 830 -> 750 us at 4096 x 256): 20 untimed launches of
@@ -990,7 +992,8 @@ def main():
         "state_finite": finite,
         "roofline": {"bound": "mfma", "achieved": achieved / 1e12, "peak": peak / 1e12,
                      "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic,
-                     "kernel": f"{'split_wide_kernel' if shape == 'split8' else 'fused_kernel'} "
+                     "kernel": {"split8": "split_wide_kernel",
+                                "tile16": "tile16_kernel"}.get(shape, "fused_kernel") + " "
                                f"({args.precision}), {k_launch} steps per launch",
                      "kernel_ms": kern * 1e3, "flops_per_chain_step": exec_flops},
     }

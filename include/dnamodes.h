@@ -131,12 +131,14 @@ extern "C" {
 #define DM_TI_RT         2  /* 16-row tiles per half transform (fused) */
 #define DM_TI_JC         3  /* coupling row tiles kept (modes p <= 32 JC) */
 #define DM_TI_RESIDENT   4  /* 1: tables held in LDS for a whole launch */
-#define DM_TI_TPW        5  /* tiles of 5 chains per workgroup */
+#define DM_TI_TPW        5  /* tiles (of 5 chains, or of 16) per workgroup */
 #define DM_TI_ITEMS      6  /* workgroups of this bucket per launch */
 #define DM_TI_ITEM_US    7  /* measured us per workgroup-step (autotune), or 0 */
 #define DM_TI_SPLIT      8  /* 1: one tile per workgroup, its bond rows and
                                mode tiles divided among 4 wavefronts; 2: among
-                               8 (two per SIMD; split-BF16, RT = 8 and 16) */
+                               8 (two per SIMD; split-BF16, RT = 8 and 16); 3:
+                               one tile of 16 chains per workgroup among 8
+                               (split-BF16, RT = 6 and 8) */
 
 typedef struct dm_ctx dm_ctx;
 
@@ -191,8 +193,11 @@ typedef struct {
                                 where they exist when the launch has no
                                 more tiles than compute units (of 8
                                 wavefronts when every length has that
-                                form), else resident tables where they
-                                fit.  Results do not depend on the tile
+                                form), else tiles of 16 chains where every
+                                length has them (split-BF16, 130..256 beads)
+                                and they need fewer rounds of the GPU's
+                                compute units, else resident tables where
+                                they fit.  Results do not depend on the tile
                                 shape */
     int32_t corr_lags;       /* 0..14: number of lags of the time
                                 correlations in the accumulators (a ring of

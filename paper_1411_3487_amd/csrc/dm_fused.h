@@ -28,7 +28,9 @@ struct FusedBucket {
     int tpw = 4;             // tiles per workgroup (1..4; 4 when streamed, 1 split)
     int split = 0;           // 1: one tile per workgroup, its rows and modes
                              // divided among 4 wavefronts; 2: among 8
-                             // (split-BF16, RT = 8 and 16, a kernel of its own)
+                             // (split-BF16, RT = 8 and 16, a kernel of its own);
+                             // 3: tiles of 16 chains on 8 wavefronts (split-BF16,
+                             // RT = 6 and 8, a kernel of its own)
     double item_us = 0.0;    // measured time of one workgroup-step (0: model)
     int n = 0;               // chains
     const int32_t *ids = nullptr;  // device: global chain index per local chain
@@ -49,7 +51,8 @@ hipError_t fused_set_coefs(FusedBucket &f, const ModeCoefs &mc, int M, double li
 // One launch over all buckets: a list of workgroup items, longest first.
 struct FusedPlan {
     int bf16 = 0, nitems = 0, nbuckets = 0;
-    int nwide = 0;  // the last nwide items run on 8-wavefront split tiles
+    int nwide = 0, n16 = 0;  // of these on 8-wavefront split tiles and, last, on
+                             // 16-chain tiles
     void *d_buckets = nullptr, *d_items = nullptr;
 };
 // Build the launch for the buckets (all of one precision) with their current
@@ -71,8 +74,13 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
 // measured by the autotuner, else the cost model.
 double fused_item_us(const FusedBucket &f);
 // Force a tile shape where it exists: table_mode 1 resident, 2 streamed,
-// 3 split over 4 wavefronts, 4 split over 8 (0 keeps the current); tpw 1..4
-// where resident (0 keeps the current).
+// 3 split over 4 wavefronts, 4 split over 8, kForceTile16 tiles of 16 chains (0
+// keeps the current); tpw 1..4 where resident (0 keeps the current).
+constexpr int kForceTile16 = 5;
+// Workgroup items of the bucket in its shape, and on 16-chain tiles (-1:
+// the length has none).
+int fused_items(const FusedBucket &f);
+int fused_tile16_items(const FusedBucket &f);
 void fused_force_shape(FusedBucket &f, int table_mode, int tpw);
 // Device step counter of replayed graphs: *d_step = value, *d_step += n.
 hipError_t fused_set_step(int64_t *d_step, int64_t value, hipStream_t st);

@@ -1237,6 +1237,296 @@ void split_wide_kernel(LaunchArgs la)
     }
 }
 
+// ---- Tiles of 16 chains: one column tile of 16 chains per component, so a
+// lane holds x, y and z of a bond and bond lengths need no lane moves; 8
+// wavefronts per workgroup, two per SIMD, one half-bond row tile and mode tile
+// each (RT = 8; RT = 6 leaves two wavefronts idle).  For launches of about as
+// many such workgroups as the GPU has compute units: 4096 chains of 256 beads
+// make exactly 256, where tiles of 5 chains are 820 wavefronts for 1024 SIMDs
+// (5.3 against 7.3 us per step; 4.3 against 5.3 at 192 beads).  Shorter chains
+// leave wavefronts idle and are slower than 5-chain tiles (at RT = 4, with two
+// tiles per workgroup, 4.5 us for 32 chains against 3.5 us for 20).
+//
+// Every wavefront keeps the u = chi R fragments of its row tile in registers
+// for the launch and reads its coupling rows from L2; the amplitudes and the
+// forces go through LDS as in the split tiles, [K slab][odd hi, odd lo, even
+// hi, even lo][component][lane].  The step is bound by vector issue (noise,
+// forces, splits); the matrix products of one wavefront hide behind the
+// vector work of the other on its SIMD, so the two draw their noise at
+// different times: wavefronts 0..3 before the products of u = chi R,
+// wavefronts 4..7 after their update, for the next step.  Normal 0 of a mode
+// tile (for lane group 3 of the tile before) is exchanged in cz, two buffers
+// by step parity, so two barriers a step do.
+//
+// Every accumulator sees the products of the other shapes in their order and
+// every amplitude the same operations: the states are the same bits.
+constexpr int kChains16 = 16;
+constexpr int kLds16 = kKinds * 8 * 4 + 24 * 4 * 64 + 2 * 8 * 3 * 4;  // f32x4, largest RT
+
+template <int RT>
+__device__ __forceinline__ void tile16(const BucketArgs &a, const LaunchArgs &la, int tile0,
+                                       int64_t step0, f32x4 *lds)
+{
+    constexpr int KS = RT / 2, SF = 2 * RT;
+    constexpr int BUF = 12 * KS * 64;  // f32x4 of one exchange buffer
+    static_assert(RT <= 8 && kKinds * RT * 4 + 2 * BUF + 2 * RT * 3 * 4 <= kLds16, "LDS of tile16");
+    const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int J = wave % RT, c0 = kChains16 * tile0;
+    const bool on = wave < RT;  // this wavefront has a row tile and a mode tile
+    const bool early = wave < 4;
+    f32x4 *cf = lds;
+    {
+        const f32x4 *c4 = reinterpret_cast<const f32x4 *>(a.coef);
+        for (int i = threadIdx.x; i < kKinds * RT * 4; i += blockDim.x) cf[i] = c4[i];
+    }
+    f32x4 *Rb = lds + kKinds * RT * 4, *Gb = Rb + BUF;
+    float *cz = reinterpret_cast<float *>(Gb + BUF);
+    constexpr int CZ = RT * 48;  // floats of one cz buffer
+
+    const bool valid = on && c0 + col < a.n;
+    const int j = valid ? c0 + col : 0;
+    const uint32_t chain = valid ? (uint32_t)a.ids[j] : 0u;
+    // the chain's place in the state of 5-chain tiles
+    const int tile5 = j / kChainsPerTile, cl5 = j % kChainsPerTile;
+    f32x4 *Rt = reinterpret_cast<f32x4 *>(a.R) + ((size_t)tile5 * 2 * RT + J) * 64 + 16 * g + 3 * cl5;
+    const __amdgpu_buffer_rsrc_t xrs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.X), 0, a.x_bytes, 0x00020000);
+    const int lane_bytes = lane * 16;
+    auto frag = [&](int F) {
+        return __builtin_bit_cast(f32x4,
+                                  __builtin_amdgcn_raw_buffer_load_b128(xrs, lane_bytes, F * 1024, 0));
+    };
+    f32x4 Ro[3], Re[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        Ro[c] = valid ? Rt[c] : f32x4{0.f, 0.f, 0.f, 0.f};
+        Re[c] = valid ? Rt[RT * 64 + c] : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const bool com_lane = valid && g == 0 && J == 0;
+    double *R0 = a.R0 + (size_t)tile5 * 16 + 3 * cl5;
+    double r0[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) r0[c] = com_lane ? R0[c] : 0.0;
+
+    auto put = [&](f32x4 *buf, int k, int c, const f32x4 v) {
+        bf16x4 h, l;
+        split_half(v, h, l);
+        reinterpret_cast<bf16x4 *>(buf + (((J >> 1) * 4 + k) * 3 + c) * 64 + lane)[J & 1] = h;
+        reinterpret_cast<bf16x4 *>(buf + (((J >> 1) * 4 + k + 1) * 3 + c) * 64 + lane)[J & 1] = l;
+    };
+    auto put_state = [&]() {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            put(Rb, 0, c, Ro[c]);
+            put(Rb, 2, c, Re[c]);
+        }
+    };
+    // normals 32 J + 8 g .. + 7 of every component; normal 0 to the exchange
+    float z[3][8];
+    auto draw = [&](int64_t k, int buf) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            scaled_normals4_f32(noise_bits(la.seed, (uint32_t)(8 * J + 2 * g), chain, k, (uint32_t)c,
+                                           kTagMode),
+                                z[c]);
+            scaled_normals4_f32(noise_bits(la.seed, (uint32_t)(8 * J + 2 * g + 1), chain, k,
+                                           (uint32_t)c, kTagMode),
+                                z[c] + 4);
+            if (lane < 16) cz[buf * CZ + (J * 3 + c) * 16 + lane] = z[c][0];
+        }
+    };
+    f32x4 xu[KS][4];
+    if (on && la.nonlinear) {
+        put_state();
+#pragma unroll
+        for (int q = 0; q < KS; ++q)
+#pragma unroll
+            for (int f = 0; f < 4; ++f) xu[q][f] = frag((q * RT + J) * 4 + f);
+    }
+    if (on && !early) draw(step0, 0);
+    __syncthreads();
+
+    for (int s = 0; s < la.n_steps; ++s) {
+        const int64_t k = step0 + s;
+        if (on && early) draw(k, s & 1);
+        if (on && la.nonlinear) {
+            // ---- u = chi R of the own half-bond rows, component by component
+            // in each K slab, the next operands read one component ahead
+            f32x4 S[3], A[3], bn[4];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) S[c] = A[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int f = 0; f < 4; ++f) bn[f] = Rb[f * 3 * 64 + lane];
+#pragma unroll
+            for (int q = 0; q < KS; ++q)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    f32x4 bc[4];
+#pragma unroll
+                    for (int f = 0; f < 4; ++f) bc[f] = bn[f];
+                    const int u = 3 * q + c + 1;
+                    if (u < 3 * KS) {
+#pragma unroll
+                        for (int f = 0; f < 4; ++f)
+                            bn[f] = Rb[((u / 3 * 4 + f) * 3 + u % 3) * 64 + lane];
+                    }
+                    const bf16x8 boh = __builtin_bit_cast(bf16x8, bc[0]);
+                    const bf16x8 bol = __builtin_bit_cast(bf16x8, bc[1]);
+                    const bf16x8 beh = __builtin_bit_cast(bf16x8, bc[2]);
+                    const bf16x8 bel = __builtin_bit_cast(bf16x8, bc[3]);
+                    S[c] = mfma_bf16(__builtin_bit_cast(bf16x8, xu[q][0]), boh, S[c]);
+                    A[c] = mfma_bf16(__builtin_bit_cast(bf16x8, xu[q][2]), beh, A[c]);
+                    S[c] = mfma_bf16(__builtin_bit_cast(bf16x8, xu[q][0]), bol, S[c]);
+                    A[c] = mfma_bf16(__builtin_bit_cast(bf16x8, xu[q][2]), bel, A[c]);
+                    S[c] = mfma_bf16(__builtin_bit_cast(bf16x8, xu[q][1]), boh, S[c]);
+                    A[c] = mfma_bf16(__builtin_bit_cast(bf16x8, xu[q][3]), beh, A[c]);
+                }
+            // ---- bond forces (the operations of bond_forces, in the lane)
+            constexpr float kTiny3 = 1e-30f / 3.0f;
+            f32x4 Gp[3], Gm[3];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float up[3], um[3], vp[3], vm[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    up[c] = S[c][r] + A[c][r];
+                    um[c] = S[c][r] - A[c][r];
+                    vp[c] = __builtin_fmaf(up[c], up[c], kTiny3);
+                    vm[c] = __builtin_fmaf(um[c], um[c], kTiny3);
+                }
+                const float bp = (vp[0] + vp[1]) + vp[2], bm = (vm[0] + vm[1]) + vm[2];
+                const float tp = __builtin_amdgcn_rsqf(bp) - a.lin;
+                const float tm = __builtin_amdgcn_rsqf(bm) - a.lin;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const float gm = um[c] * tm;
+                    Gp[c][r] = __builtin_fmaf(up[c], tp, gm);
+                    Gm[c][r] = __builtin_fmaf(up[c], tp, -gm);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                put(Gb, 0, c, Gp[c]);
+                put(Gb, 2, c, Gm[c]);
+            }
+        }
+        // coupling rows of the own modes, [odd hi, odd lo, even hi, even lo]
+        const bool couple = on && la.nonlinear && J < a.jc;
+        f32x4 xc[KS][4];
+        if (couple) {
+#pragma unroll
+            for (int q = 0; q < KS; ++q)
+#pragma unroll
+                for (int f = 0; f < 4; ++f)
+                    xc[q][f] = frag((RT + J) * SF + (f >> 1) * RT + 2 * q + (f & 1));
+        }
+        lds_barrier();  // forces and normals 0 written, amplitudes read
+        if (on) {
+            const f32x4 Eo = cf[(kEo * RT + J) * 4 + g], Wo = cf[(kWo * RT + J) * 4 + g];
+            const f32x4 Ee = cf[(kEe * RT + J) * 4 + g], We = cf[(kWe * RT + J) * 4 + g];
+            f32x4 ao[3], ae[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const float zn = __shfl(z[c][0], (lane + 16) & 63, 64);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float ze = r < 3 ? z[c][2 * r + 2] : (g < 3 ? zn : 0.0f);
+                    ao[c][r] = __builtin_fmaf(Eo[r], Ro[c][r], Wo[r] * z[c][2 * r + 1]);
+                    ae[c][r] = __builtin_fmaf(Ee[r], Re[c][r], We[r] * ze);
+                }
+            }
+            if (a.gdt != 0.0) {
+                const f32x4 Go = cf[(kGo * RT + J) * 4 + g], Ge = cf[(kGe * RT + J) * 4 + g];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    ao[0][r] = __builtin_fmaf(Go[r], Ro[1][r], ao[0][r]);
+                    ae[0][r] = __builtin_fmaf(Ge[r], Re[1][r], ae[0][r]);
+                }
+            }
+            if (J == 0) {
+                // centre of mass: free random walk in FP64, shear drift from R_0^y
+                const double r0y = r0[1];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) r0[c] = __builtin_fma(a.W0, (double)z[c][0], r0[c]);
+                r0[0] = __builtin_fma(a.gdt, r0y, r0[0]);
+            }
+            if (couple) {
+                const f32x4 Ce = cf[(kCe * RT + J) * 4 + g];
+                f32x4 gn[4];
+#pragma unroll
+                for (int f = 0; f < 4; ++f) gn[f] = Gb[f * 3 * 64 + lane];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    f32x4 ce = f32x4{0.f, 0.f, 0.f, 0.f};
+                    f32x4 ao2 = f32x4{0.f, 0.f, 0.f, 0.f}, ce2 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int q = 0; q < KS; ++q) {
+                        const bf16x8 gph = __builtin_bit_cast(bf16x8, gn[0]);
+                        const bf16x8 gpl = __builtin_bit_cast(bf16x8, gn[1]);
+                        const bf16x8 gmh = __builtin_bit_cast(bf16x8, gn[2]);
+                        const bf16x8 gml = __builtin_bit_cast(bf16x8, gn[3]);
+                        const int u = c * KS + q + 1;
+                        if (u < 3 * KS) {
+#pragma unroll
+                            for (int f = 0; f < 4; ++f)
+                                gn[f] = Gb[((u % KS * 4 + f) * 3 + u / KS) * 64 + lane];
+                        }
+                        f32x4 &P = (q & 1) ? ao2 : ao[c];
+                        f32x4 &C = (q & 1) ? ce2 : ce;
+                        P = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][0]), gph, P);
+                        C = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][2]), gmh, C);
+                        P = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][0]), gpl, P);
+                        C = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][2]), gml, C);
+                        P = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][1]), gph, P);
+                        C = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][3]), gmh, C);
+                    }
+                    ao[c] += ao2;
+                    ce += ce2;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) ae[c][r] = __builtin_fmaf(Ce[r], ce[r], ae[c][r]);
+                }
+            }
+            // lane group 3's even slot r = 3 takes normal 0 of the next tile
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                if (J + 1 < RT) {
+                    const float zc = cz[(s & 1) * CZ + ((J + 1) * 3 + c) * 16 + col];
+                    ae[c][3] = __builtin_fmaf(g == 3 ? We[3] : 0.0f, zc, ae[c][3]);
+                }
+                Ro[c] = ao[c];
+                Re[c] = ae[c];
+            }
+            if (la.nonlinear) put_state();
+            if (!early && s + 1 < la.n_steps) draw(k + 1, (s + 1) & 1);
+        }
+        lds_barrier();  // amplitudes written
+    }
+    if (!valid) return;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        Rt[c] = Ro[c];
+        Rt[RT * 64 + c] = Re[c];
+    }
+    if (com_lane)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) R0[c] = r0[c];
+}
+
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void tile16_kernel(LaunchArgs la)
+{
+    __shared__ f32x4 lds[kLds16];
+    const Item it = la.items[blockIdx.x];
+    const BucketArgs a = la.buckets[it.bucket];
+    const int64_t step0 = la.step ? *la.step : la.step0;
+    switch (a.variant) {
+    case 17: tile16<6>(a, la, it.tile0, step0, lds); break;
+    case 18: tile16<8>(a, la, it.tile0, step0, lds); break;
+    default: break;
+    }
+}
+
 // Kernel variant of a tile shape: resident tables exist for RT <= 8,
 // streamed ones for RT >= 8, split tiles for RT = 4, 8, 12, 16, and split
 // tiles of 8 wavefronts for RT = 8, 16 in split-BF16.
@@ -1249,6 +1539,13 @@ bool has_split(int RT, int waves, bool bf16)
 }
 // Wavefronts of a bucket's split tiles (split = 1: 4, split = 2: 8).
 static int split_waves(const FusedBucket &f) { return f.split == 2 ? 8 : 4; }
+// Tiles of 16 chains (split = 3): split-BF16, RT = 6 and 8.
+bool has_tile16(int RT, bool bf16) { return bf16 && (RT == 6 || RT == 8); }
+// Chain tiles of a bucket in its shape, and tiles per workgroup.
+static int shape_tiles(const FusedBucket &f)
+{
+    return f.split == 3 ? (f.n + kChains16 - 1) / kChains16 : f.ntiles;
+}
 
 // Slot of mode p >= 1 of (local chain j, component alpha) in the state:
 // odd p at half-mode slot (p - 1)/2, even p at p/2 - 1.
@@ -1762,7 +2059,9 @@ static BucketArgs bucket_args(const FusedBucket &f)
     a.ntiles = f.ntiles;
     a.x_bytes = (int)x_bytes(f.RT);
     a.jc = f.JC;
-    a.variant = f.split ? split_variant(f.RT, split_waves(f)) : variant_of(f.RT, f.resident != 0);
+    a.variant = f.split == 3 ? 14 + f.RT / 2
+                : f.split    ? split_variant(f.RT, split_waves(f))
+                             : variant_of(f.RT, f.resident != 0);
     a.tpw = f.tpw;
     a.lin = f.lin;
     a.W0 = f.W0;
@@ -1773,11 +2072,12 @@ static BucketArgs bucket_args(const FusedBucket &f)
 // Cost model of one workgroup-step when nothing was measured: the MFMA and
 // table work grow as RT^2, the noise and forces as RT; a split tile takes
 // about a third of a wavefront's time for one tile (a quarter on 8
-// wavefronts).
+// wavefronts), a 16-chain tile 0.7 of a wavefront's.
 static double model_us(const FusedBucket &f)
 {
     const double rt = f.RT;
     const double us = 0.12 * rt * rt + 0.3 * rt + (f.resident ? 0.0 : 0.02 * rt * rt);
+    if (f.split == 3) return us / 1.4;
     return f.split == 2 ? us / 4.0 : f.split ? us / 3.0 : us;
 }
 
@@ -1791,7 +2091,7 @@ static std::vector<Item> ordered_items(const std::vector<const FusedBucket *> &b
     for (size_t b = 0; b < bs.size(); ++b) {
         const FusedBucket &f = *bs[b];
         const double c = f.item_us > 0.0 ? f.item_us : model_us(f);
-        for (int t = 0; t < f.ntiles; t += f.tpw) v.push_back({c, Item{(int)b, t}});
+        for (int t = 0; t < shape_tiles(f); t += f.tpw) v.push_back({c, Item{(int)b, t}});
     }
     std::stable_sort(v.begin(), v.end(),
                      [](const std::pair<double, Item> &x, const std::pair<double, Item> &y) {
@@ -1837,29 +2137,37 @@ hipError_t fused_plan(FusedPlan &p, const std::vector<const FusedBucket *> &bs, 
                                                 : reinterpret_cast<const void *>(&fused_kernel<false>));
     if (e != hipSuccess) return e;
     std::vector<BucketArgs> ba;
-    bool wide = false;
+    bool wide = false, t16 = false;
     for (const FusedBucket *f : bs) {
         if (f->bf16 != p.bf16) return hipErrorInvalidValue;
-        const bool ok = f->split ? f->split <= 2 && has_split(f->RT, split_waves(*f), f->bf16 != 0) &&
+        const bool ok = f->split == 3 ? has_tile16(f->RT, f->bf16 != 0) && f->tpw == 1 && !f->resident
+                        : f->split ? f->split <= 2 && has_split(f->RT, split_waves(*f), f->bf16 != 0) &&
                                        f->tpw == 1 && !f->resident
                                  : has_variant(f->RT, f->resident != 0) && f->tpw >= 1 &&
                                        f->tpw <= 4 && (f->resident || f->tpw == 4);
         if (!ok) return hipErrorInvalidValue;
         wide = wide || f->split == 2;
+        t16 = t16 || f->split == 3;
         ba.push_back(bucket_args(*f));
     }
     if (wide && (e = check_private_segment(reinterpret_cast<const void *>(&split_wide_kernel))) !=
                     hipSuccess)
         return e;
+    if (t16 && (e = check_private_segment(reinterpret_cast<const void *>(&tile16_kernel))) !=
+                   hipSuccess)
+        return e;
     std::vector<Item> items = ordered_items(bs);
     if (max_items > 0 && (int)items.size() > max_items) items.resize(max_items);
-    // the items of 8-wavefront split tiles go to their own kernel, after the
-    // others (each part keeps its longest-first order)
-    std::stable_partition(items.begin(), items.end(),
-                          [&](const Item &it) { return bs[it.bucket]->split != 2; });
+    // the items of 8-wavefront split tiles and of 16-chain tiles go to kernels
+    // of their own, after the others (each part keeps its longest-first order)
+    auto part = [&](const Item &it) { return std::max(1, bs[it.bucket]->split); };
+    std::stable_sort(items.begin(), items.end(),
+                     [&](const Item &x, const Item &y) { return part(x) < part(y); });
     p.nitems = (int)items.size();
     p.nwide = (int)std::count_if(items.begin(), items.end(),
-                                 [&](const Item &it) { return bs[it.bucket]->split == 2; });
+                                 [&](const Item &it) { return part(it) == 2; });
+    p.n16 = (int)std::count_if(items.begin(), items.end(),
+                               [&](const Item &it) { return part(it) == 3; });
     p.nbuckets = (int)bs.size();
     if ((e = hipMalloc(&p.d_buckets, sizeof(BucketArgs) * ba.size())) != hipSuccess) return e;
     if ((e = hipMalloc(&p.d_items, sizeof(Item) * std::max<size_t>(1, items.size()))) !=
@@ -1886,7 +2194,7 @@ hipError_t fused_launch(const FusedPlan &p, uint64_t seed, int64_t step0, const 
     la.seed = seed;
     la.n_steps = n_steps;
     la.nonlinear = nonlinear;
-    const int nmain = p.nitems - p.nwide;
+    const int nmain = p.nitems - p.nwide - p.n16;
     if (nmain > 0) {
         if (p.bf16)
             hipLaunchKernelGGL(fused_kernel<true>, dim3(nmain), dim3(256), 0, st, la);
@@ -1896,8 +2204,14 @@ hipError_t fused_launch(const FusedPlan &p, uint64_t seed, int64_t step0, const 
         if (e != hipSuccess) return e;
     }
     if (p.nwide > 0) {
-        la.items += nmain;
+        la.items = static_cast<const Item *>(p.d_items) + nmain;
         hipLaunchKernelGGL(split_wide_kernel, dim3(p.nwide), dim3(512), 0, st, la);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (p.n16 > 0) {
+        la.items = static_cast<const Item *>(p.d_items) + nmain + p.nwide;
+        hipLaunchKernelGGL(tile16_kernel, dim3(p.n16), dim3(512), 0, st, la);
     }
     return hipGetLastError();
 }
@@ -1960,6 +2274,7 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
         }
         if (has_split(f.RT, 4, f.bf16 != 0)) list.push_back({0, 1, 1, 0.0});
         if (has_split(f.RT, 8, f.bf16 != 0)) list.push_back({0, 1, 2, 0.0});
+        if (has_tile16(f.RT, f.bf16 != 0)) list.push_back({0, 1, 3, 0.0});
         for (Cand &c : list) {
             if (e != hipSuccess) break;
             t.resident = c.resident;
@@ -1994,19 +2309,27 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
     size_t combos = 1;
     for (auto &l : cands) combos = std::min<size_t>(combos * std::max<size_t>(1, l.size()), 1 << 20);
     std::vector<int> pick(bs.size(), 0), cur(bs.size(), 0);
-    // the 8-wavefront split tiles run in a kernel of their own after the
-    // others: the two makespans add
+    // the 8-wavefront split tiles and the 16-chain tiles run in kernels of
+    // their own after the others: the makespans add
     auto evaluate = [&](const std::vector<int> &sel) {
-        std::vector<double> cost, wcost;
+        std::vector<double> cost[3];
         for (size_t b = 0; b < bs.size(); ++b) {
             const Cand &c = cands[b][sel[b]];
-            const int ni = (bs[b]->ntiles + c.tpw - 1) / c.tpw;
-            std::vector<double> &v = c.split == 2 ? wcost : cost;
+            FusedBucket f;  // the shape alone
+            f.n = bs[b]->n;
+            f.ntiles = bs[b]->ntiles;
+            f.split = c.split;
+            f.tpw = c.tpw;
+            const int ni = fused_items(f);
+            std::vector<double> &v = cost[std::max(0, c.split - 1)];
             v.insert(v.end(), (size_t)ni, c.us);
         }
-        std::sort(cost.begin(), cost.end(), std::greater<double>());
-        std::sort(wcost.begin(), wcost.end(), std::greater<double>());
-        return makespan(cost, ncu) + makespan(wcost, ncu);
+        double sum = 0.0;
+        for (std::vector<double> &v : cost) {
+            std::sort(v.begin(), v.end(), std::greater<double>());
+            sum += makespan(v, ncu);
+        }
+        return sum;
     };
     if (combos <= 4096) {
         double best = 1e300;
@@ -2028,7 +2351,9 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
         for (size_t b = 0; b < bs.size(); ++b) {
             double best = 1e300;
             for (size_t c = 0; c < cands[b].size(); ++c) {
-                const double per_tile = cands[b][c].us / cands[b][c].tpw;
+                const Cand &k = cands[b][c];
+                const double per_tile =
+                    k.us / (k.split == 3 ? (double)kChains16 / kChainsPerTile : k.tpw);
                 if (per_tile < best) {
                     best = per_tile;
                     pick[b] = (int)c;
@@ -2064,7 +2389,8 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
         f.item_us = c.us;
         for (size_t k = 0; k < cands[b].size(); ++k) {
             const Cand &ck = cands[b][k];
-            const char *shape = ck.split == 2 ? "split8"
+            const char *shape = ck.split == 3   ? "tile16"
+                                : ck.split == 2 ? "split8"
                                 : ck.split    ? "split"
                                 : ck.resident ? "resident"
                                               : "streamed";
@@ -2075,6 +2401,21 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
         }
     }
     return hipSuccess;
+}
+
+int fused_items(const FusedBucket &f)
+{
+    return (shape_tiles(f) + f.tpw - 1) / f.tpw;
+}
+
+int fused_tile16_items(const FusedBucket &f)
+{
+    if (!has_tile16(f.RT, f.bf16 != 0)) return -1;
+    FusedBucket t;
+    t.n = f.n;
+    t.split = 3;
+    t.tpw = 1;
+    return fused_items(t);
 }
 
 void fused_force_shape(FusedBucket &f, int table_mode, int tpw)
@@ -2092,6 +2433,12 @@ void fused_force_shape(FusedBucket &f, int table_mode, int tpw)
                has_split(f.RT, table_mode == 4 ? 8 : 4, f.bf16 != 0)) {
         f.resident = 0;
         f.split = table_mode == 4 ? 2 : 1;
+        f.tpw = 1;
+        f.item_us = 0.0;
+    }
+    if (table_mode == kForceTile16 && has_tile16(f.RT, f.bf16 != 0)) {
+        f.resident = 0;
+        f.split = 3;
         f.tpw = 1;
         f.item_us = 0.0;
     }
