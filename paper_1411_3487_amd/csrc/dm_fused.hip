@@ -514,9 +514,10 @@ __device__ __forceinline__ void fused_tiles(const BucketArgs &a, const LaunchArg
                     constexpr int FB = RT >= 14 ? 4 : HALF;
 #pragma unroll
                     for (int i0 = 0; i0 < HALF; i0 += FB) {
+                        // (RT = 14: the second block has 3 row tiles)
                         bf16x8 xoh[FB], xol[FB], xeh[FB], xel[FB];
 #pragma unroll
-                        for (int ii = 0; ii < FB; ++ii) {
+                        for (int ii = 0; ii < FB && i0 + ii < HALF; ++ii) {
                             const f32x4 *fr = xs + ((i0 + ii) * 4) * 64 + lane;
                             xoh[ii] = __builtin_bit_cast(bf16x8, fr[0]);
                             xol[ii] = __builtin_bit_cast(bf16x8, fr[64]);
@@ -525,17 +526,17 @@ __device__ __forceinline__ void fused_tiles(const BucketArgs &a, const LaunchArg
                         }
                         const int I0 = h * HALF + i0;
 #pragma unroll
-                        for (int ii = 0; ii < FB; ++ii) {
+                        for (int ii = 0; ii < FB && i0 + ii < HALF; ++ii) {
                             aS[I0 + ii] = mfma_bf16(xoh[ii], boh, aS[I0 + ii]);
                             aA[I0 + ii] = mfma_bf16(xeh[ii], beh, aA[I0 + ii]);
                         }
 #pragma unroll
-                        for (int ii = 0; ii < FB; ++ii) {
+                        for (int ii = 0; ii < FB && i0 + ii < HALF; ++ii) {
                             aS[I0 + ii] = mfma_bf16(xoh[ii], bol, aS[I0 + ii]);
                             aA[I0 + ii] = mfma_bf16(xeh[ii], bel, aA[I0 + ii]);
                         }
 #pragma unroll
-                        for (int ii = 0; ii < FB; ++ii) {
+                        for (int ii = 0; ii < FB && i0 + ii < HALF; ++ii) {
                             aS[I0 + ii] = mfma_bf16(xol[ii], boh, aS[I0 + ii]);
                             aA[I0 + ii] = mfma_bf16(xel[ii], beh, aA[I0 + ii]);
                         }
