@@ -138,7 +138,9 @@ extern "C" {
                                mode tiles divided among 4 wavefronts; 2: among
                                8 (two per SIMD; split-BF16, RT = 8 and 16); 3:
                                one tile of 16 chains per workgroup among 8
-                               (split-BF16, RT = 6 and 8) */
+                               (split-BF16, RT = 6 and 8); 4: small launches,
+                               tpw = 1 or 2 tiles of 5 chains among up to 8
+                               (every length; 2 up to RT = 8) */
 
 typedef struct dm_ctx dm_ctx;
 
@@ -189,15 +191,13 @@ typedef struct {
                                 over 8 wavefronts (split-BF16, RT = 8 and
                                 16), each where that form exists for the
                                 length (it overrides the autotuner).
-                                Automatic without autotune: split tiles
-                                where they exist when the launch has no
-                                more tiles than compute units (of 8
-                                wavefronts when every length has that
-                                form), else tiles of 16 chains where every
-                                length has them (split-BF16, 130..256 beads)
-                                and they need fewer rounds of the GPU's
-                                compute units, else resident tables where
-                                they fit.  Results do not depend on the tile
+                                Automatic without autotune: the shortest
+                                schedule, at measured times, of resident or
+                                streamed tables, small-launch tiles (one or
+                                two per workgroup) and tiles of 16 chains;
+                                tiles_per_wg with it keeps resident tables
+                                where the launch has more tiles than compute
+                                units.  Results do not depend on the tile
                                 shape */
     int32_t corr_lags;       /* 0..14: number of lags of the time
                                 correlations in the accumulators (a ring of

@@ -748,37 +748,16 @@ int dm_set_params(dm_ctx *ctx, const dm_params *p)
             for (Bucket &b : ctx->buckets) fb.push_back(&b.fused);
             DM_HIP(ctx, dm::fused_autotune(fb, ctx->seed, 64, ctx->stream, ctx->tune_report));
         } else if (!p->table_mode) {
-            // untimed: split tiles when a wavefront per tile would leave
-            // compute units idle; of 8 wavefronts when every bucket has that
-            // form (one launch of their kernel), else of 4.  Beyond that,
-            // tiles of 16 chains where every length has them and their
-            // rounds over the compute units, at 0.73 of the time of the
-            // default shape's (5.3 against 7.3 us per step at 256 beads, 0.82
-            // at 192), are fewer
-            size_t tiles = 0, items = 0, items16 = 0;
-            bool has16 = true;
-            for (const Bucket &b : ctx->buckets) {
+            // a tiles_per_wg given with it is one of resident tiles, where
+            // the launch has more tiles than compute units
+            size_t tiles = 0;
+            std::vector<dm::FusedBucket *> fb;
+            for (Bucket &b : ctx->buckets) {
                 tiles += (size_t)b.fused.ntiles;
-                items += (size_t)dm::fused_items(b.fused);
-                const int i16 = dm::fused_tile16_items(b.fused);
-                has16 = has16 && i16 >= 0;
-                items16 += (size_t)std::max(0, i16);
+                fb.push_back(&b.fused);
             }
-            const size_t ncu = (size_t)std::max(1, ctx->ncu);
-            if (ctx->ncu > 0 && tiles <= ncu) {
-                bool wide = true;
-                for (Bucket &b : ctx->buckets) {
-                    dm::fused_force_shape(b.fused, 4, 0);
-                    wide = wide && b.fused.split == 2;
-                }
-                if (!wide)
-                    for (Bucket &b : ctx->buckets) dm::fused_force_shape(b.fused, 3, 0);
-            } else if (ctx->ncu > 0 && !p->tiles_per_wg && has16 &&
-                       0.75 * (double)((items16 + ncu - 1) / ncu) <
-                           (double)((items + ncu - 1) / ncu)) {
-                for (Bucket &b : ctx->buckets)
-                    dm::fused_force_shape(b.fused, dm::kForceTile16, 0);
-            }
+            if (!p->tiles_per_wg || tiles <= (size_t)std::max(0, ctx->ncu))
+                dm::fused_default_shapes(fb, ctx->ncu);
         }
         if (p->tiles_per_wg || p->table_mode)
             for (Bucket &b : ctx->buckets)

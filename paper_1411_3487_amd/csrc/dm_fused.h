@@ -30,7 +30,10 @@ struct FusedBucket {
                              // divided among 4 wavefronts; 2: among 8
                              // (split-BF16, RT = 8 and 16, a kernel of its own);
                              // 3: tiles of 16 chains on 8 wavefronts (split-BF16,
-                             // RT = 6 and 8, a kernel of its own)
+                             // RT = 6 and 8, a kernel of its own); 4: small
+                             // launches, tpw = 1 or 2 tiles on up to 8
+                             // wavefronts (every length and precision, a
+                             // kernel of its own)
     double item_us = 0.0;    // measured time of one workgroup-step (0: model)
     int n = 0;               // chains
     const int32_t *ids = nullptr;  // device: global chain index per local chain
@@ -51,8 +54,9 @@ hipError_t fused_set_coefs(FusedBucket &f, const ModeCoefs &mc, int M, double li
 // One launch over all buckets: a list of workgroup items, longest first.
 struct FusedPlan {
     int bf16 = 0, nitems = 0, nbuckets = 0;
-    int nwide = 0, n16 = 0;  // of these on 8-wavefront split tiles and, last, on
-                             // 16-chain tiles
+    // of these on 8-wavefront split tiles, 16-chain tiles and, last, in the
+    // small-launch kernel
+    int nwide = 0, n16 = 0, nsmall = 0;
     void *d_buckets = nullptr, *d_items = nullptr;
 };
 // Build the launch for the buckets (all of one precision) with their current
@@ -74,14 +78,15 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
 // measured by the autotuner, else the cost model.
 double fused_item_us(const FusedBucket &f);
 // Force a tile shape where it exists: table_mode 1 resident, 2 streamed,
-// 3 split over 4 wavefronts, 4 split over 8, kForceTile16 tiles of 16 chains (0
-// keeps the current); tpw 1..4 where resident (0 keeps the current).
-constexpr int kForceTile16 = 5;
-// Workgroup items of the bucket in its shape, and on 16-chain tiles (-1:
-// the length has none).
-int fused_items(const FusedBucket &f);
-int fused_tile16_items(const FusedBucket &f);
+// 3 split over 4 wavefronts, 4 split over 8, kForceTile16 tiles of 16 chains, kForceSmall
+// the small-launch kernel with tpw = 1 or 2 (0 keeps the current); tpw 1..4
+// where resident (0 keeps the current).
+constexpr int kForceTile16 = 5, kForceSmall = 6;
 void fused_force_shape(FusedBucket &f, int table_mode, int tpw);
+// The shapes of a launch that was not autotuned.
+void fused_default_shapes(const std::vector<FusedBucket *> &bs, int ncu);
+// Workgroup items of the bucket in its shape.
+int fused_items(const FusedBucket &f);
 // Device step counter of replayed graphs: *d_step = value, *d_step += n.
 hipError_t fused_set_step(int64_t *d_step, int64_t value, hipStream_t st);
 hipError_t fused_advance_step(int64_t *d_step, int64_t n, hipStream_t st);

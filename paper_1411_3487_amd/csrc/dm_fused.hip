@@ -47,6 +47,7 @@
 #include <cmath>
 #include <cstdio>
 #include <functional>
+#include <queue>
 #include <string>
 #include <vector>
 
@@ -1528,6 +1529,430 @@ void tile16_kernel(LaunchArgs la)
     }
 }
 
+// ---- Small launches: NT = 1 or 2 tiles of 5 chains per workgroup on up to 8
+// wavefronts, every row-tile count and both precisions, for launches with few
+// workgroups for the GPU's compute units.  Such a step is a chain of latencies
+// (LDS reads, dependent products, forces, barriers), so what can leave the
+// chain does: two barriers a step (forces written, amplitudes written); up to
+// RT = 8 the u = chi R fragments stay in registers, and the even coupling rows
+// are those same fragments (S is symmetric), so only the odd ones are read;
+// the noise is drawn by wavefronts of their own one step ahead (RT = 2 and 4)
+// or, beyond, before the products of u = chi R, where it issues while the
+// products wait for each other.  Beyond RT = 8 the fragments stream from L2
+// (0.5 MB a step at RT = 16) and a workgroup takes one tile: two took twice as
+// long there, and spilled.
+//
+// Wavefront w owns row tile and mode tile w (and w + 8 beyond RT = 8).  Every
+// accumulator sees the products of the other shapes in their order: the
+// states are the same bits.  Time of a step of one workgroup, split-BF16, one
+// tile (before, on the best shape there was): 64 beads 0.92 us (1.61), 128
+// 1.23 (1.40), 160 1.81 (4.8), 256 1.96 (2.25), 300 4.1 (13.1), 384 4.5 (4.5),
+// 440 6.1 (24), 512 6.6 (7.1); FP32 64 beads 1.15 (2.26), 256 3.97 (4.58), 300
+// 7.1 (22.9), 512 14.2 (16.2).  Two tiles take about 1.75 times one.
+constexpr int kLdsSmall = kKinds * 16 * 4 + 4 * 16 * 64 + 12 * 16;  // f32x4
+
+template <int RT, bool BF16, int NT>
+__device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs &la, int tile0,
+                                           int64_t step0, f32x4 *lds)
+{
+    constexpr int KS = RT / 2, SF = 2 * RT, NJ = (RT + 7) / 8;
+    constexpr bool HOLD = RT <= 8;   // u = chi R fragments in registers
+    constexpr bool NW = RT <= 4;     // noise wavefronts
+    constexpr int RL = HOLD ? 1 : 4; // ring of streamed fragments
+    constexpr int BUF = 2 * RT * 64; // f32x4 of one exchange buffer of one tile
+    static_assert(kKinds * RT * 4 + NT * (2 * BUF + (NW ? 4 * RT * 64 : 12 * RT)) <= kLdsSmall,
+                  "LDS of small_tile");
+    const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool on = wave < RT;                           // owns tiles
+    const bool noisy = NW && wave >= RT && wave < 2 * RT;  // draws for tile wave - RT
+    const int JN = NW ? wave % RT : 0;
+    f32x4 *cf = lds;
+    {
+        const f32x4 *c4 = reinterpret_cast<const f32x4 *>(a.coef);
+        for (int i = threadIdx.x; i < kKinds * RT * 4; i += blockDim.x) cf[i] = c4[i];
+    }
+    // per chain tile: amplitudes, forces; then the normals: [tile][step parity]
+    // [J][2][lane] from the noise wavefronts, or normal 0 of every mode tile
+    // [tile][J][16]
+    f32x4 *Rb = lds + kKinds * RT * 4, *Gb = Rb + NT * BUF, *zb = Gb + NT * BUF;
+    float *cz = reinterpret_cast<float *>(zb);
+
+    const int cl = col / 3, alpha = col - 3 * cl;
+    const float xlane = alpha == 0 ? 1.0f : 0.0f;
+    uint32_t chain[NT];
+    f32x4 *Rt[NT];
+    bool com_lane[NT];
+    double r0[NT];
+    f32x4 Ro[NT][NJ], Re[NT][NJ];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int tile = tile0 + t;
+        const bool has = tile < a.ntiles;  // (a tile beyond the last stays zero)
+        const int nvalid = has ? min(kChainsPerTile, a.n - kChainsPerTile * tile) : 0;
+        const bool valid = (col < 15) && (cl < nvalid);
+        chain[t] = valid ? (uint32_t)a.ids[kChainsPerTile * tile + cl] : 0u;
+        Rt[t] = reinterpret_cast<f32x4 *>(a.R) + (size_t)(has ? tile : 0) * 2 * RT * 64;
+#pragma unroll
+        for (int ii = 0; ii < NJ; ++ii) {
+            const int J = wave + 8 * ii;
+            const bool own = has && J < RT;
+            Ro[t][ii] = own ? Rt[t][J * 64 + lane] : f32x4{0.f, 0.f, 0.f, 0.f};
+            Re[t][ii] = own ? Rt[t][(RT + J) * 64 + lane] : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        com_lane[t] = valid && g == 0 && wave == 0;
+        r0[t] = com_lane[t] ? a.R0[(size_t)tile * 16 + col] : 0.0;
+    }
+    const __amdgpu_buffer_rsrc_t xrs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.X), 0, a.x_bytes, 0x00020000);
+    const int lane_bytes = lane * 16;
+    auto frag = [&](int F) {
+        return __builtin_bit_cast(f32x4,
+                                  __builtin_amdgcn_raw_buffer_load_b128(xrs, lane_bytes, F * 1024, 0));
+    };
+
+    // a pair of tiles (odd, even amplitudes or G+, G-) into an exchange buffer
+    auto put = [&](f32x4 *buf, int J, const f32x4 o, const f32x4 e) {
+        if constexpr (BF16) {
+            bf16x4 h, l;
+            split_half(o, h, l);
+            put_half(buf, J, 0, lane, h);
+            put_half(buf, J, 1, lane, l);
+            split_half(e, h, l);
+            put_half(buf, J, 2, lane, h);
+            put_half(buf, J, 3, lane, l);
+        } else {
+            buf[(2 * J) * 64 + lane] = o;
+            buf[(2 * J + 1) * 64 + lane] = e;
+        }
+    };
+    auto draw8 = [&](int t, int J, int64_t k, float (&z)[8]) {
+        scaled_normals4_f32(noise_bits(la.seed, (uint32_t)(8 * J + 2 * g), chain[t], k,
+                                       (uint32_t)alpha, kTagMode),
+                            z);
+        scaled_normals4_f32(noise_bits(la.seed, (uint32_t)(8 * J + 2 * g + 1), chain[t], k,
+                                       (uint32_t)alpha, kTagMode),
+                            z + 4);
+    };
+    auto zslot = [&](int t, int buf, int J) { return zb + (((t * 2 + buf) * RT + J) * 2) * 64; };
+    auto draw_ahead = [&](int64_t k, int buf) {  // noise wavefronts
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            float z[8];
+            draw8(t, JN, k, z);
+            zslot(t, buf, JN)[lane] = f32x4{z[0], z[1], z[2], z[3]};
+            zslot(t, buf, JN)[64 + lane] = f32x4{z[4], z[5], z[6], z[7]};
+        }
+    };
+    [[maybe_unused]] f32x4 xu[HOLD ? KS : 1][4], xr[RL][4];
+    auto load_r = [&](int u) {  // ring entry u = ii KS + q
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+            xr[u % RL][f] = frag((u % KS * RT + wave + 8 * (u / KS)) * 4 + f);
+    };
+    const int nt = wave + 8 < RT ? 2 : 1;  // own tiles
+    if (on && la.nonlinear) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int ii = 0; ii < NJ; ++ii)
+                if (wave + 8 * ii < RT) put(Rb + t * BUF, wave + 8 * ii, Ro[t][ii], Re[t][ii]);
+        if constexpr (HOLD) {
+#pragma unroll
+            for (int q = 0; q < KS; ++q)
+#pragma unroll
+                for (int f = 0; f < 4; ++f) xu[q][f] = frag((q * RT + wave) * 4 + f);
+        } else {
+#pragma unroll
+            for (int u = 0; u < RL; ++u) load_r(u);
+        }
+    }
+    if (noisy) draw_ahead(step0, 0);
+    __syncthreads();
+
+    for (int s = 0; s < la.n_steps; ++s) {
+        const int64_t k = step0 + s;
+        [[maybe_unused]] float z[NT][NJ][8];
+        // odd coupling rows [hi, lo] (FP32: [K slices 2q, 2q + 1]); the even
+        // ones too where u = chi R is streamed
+        constexpr int CF = HOLD ? 2 : 4;
+        constexpr int DC = HOLD ? KS : 2;
+        f32x4 xc[DC][CF];
+        auto load_c = [&](int J, int q) {
+#pragma unroll
+            for (int f = 0; f < CF; ++f)
+                xc[q % DC][f] = frag((RT + J) * SF + (f >> 1) * RT + 2 * q + (f & 1));
+        };
+        if (on) {
+            if constexpr (!NW) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int ii = 0; ii < NJ; ++ii) {
+                        const int J = wave + 8 * ii;
+                        if (J < RT) {
+                            draw8(t, J, k, z[t][ii]);
+                            if (lane < 16) cz[(t * RT + J) * 16 + lane] = z[t][ii][0];
+                        }
+                    }
+            }
+            if (la.nonlinear) {
+                // ---- u = chi R of the own half-bond rows, then their forces
+#pragma unroll
+                for (int ii = 0; ii < NJ; ++ii) {
+                    const int I = wave + 8 * ii;
+                    if (I >= RT) continue;
+                    f32x4 S[NT], A[NT], bn[NT][4];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        S[t] = A[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        slab4(Rb + t * BUF, 0, bn[t], lane);
+                    }
+#pragma unroll
+                    for (int q = 0; q < KS; ++q) {
+                        f32x4 bc[NT][4];
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+#pragma unroll
+                            for (int f = 0; f < 4; ++f) bc[t][f] = bn[t][f];
+                            if (q + 1 < KS) slab4(Rb + t * BUF, q + 1, bn[t], lane);
+                        }
+                        f32x4 xf[4];
+                        const int u = ii * KS + q;
+#pragma unroll
+                        for (int f = 0; f < 4; ++f) {
+                            if constexpr (HOLD)
+                                xf[f] = xu[q][f];
+                            else
+                                xf[f] = xr[u % RL][f];
+                        }
+                        if constexpr (!HOLD) {
+                            if (u + RL < NJ * KS && (u + RL) / KS < nt) load_r(u + RL);
+                        }
+                        if constexpr (BF16) {
+                            // products hi hi, hi lo, lo hi of every tile
+#pragma unroll
+                            for (int m = 0; m < 3; ++m)
+#pragma unroll
+                                for (int t = 0; t < NT; ++t) {
+                                    const int xi = m == 2 ? 1 : 0, bi = m == 1 ? 1 : 0;
+                                    S[t] = mfma_bf16(__builtin_bit_cast(bf16x8, xf[xi]),
+                                                     __builtin_bit_cast(bf16x8, bc[t][bi]), S[t]);
+                                    A[t] = mfma_bf16(__builtin_bit_cast(bf16x8, xf[2 + xi]),
+                                                     __builtin_bit_cast(bf16x8, bc[t][2 + bi]), A[t]);
+                                }
+                        } else {
+#pragma unroll
+                            for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+                                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                                    for (int t = 0; t < NT; ++t) {
+                                        S[t] = mfma_f32(xf[hh][r], bc[t][2 * hh][r], S[t]);
+                                        A[t] = mfma_f32(xf[2 + hh][r], bc[t][2 * hh + 1][r], A[t]);
+                                    }
+                        }
+                        if constexpr (!HOLD) __builtin_amdgcn_sched_barrier(0);
+                    }
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        f32x4 Gp, Gm;
+                        bond_forces(S[t], A[t], alpha, a.lin, Gp, Gm);
+                        put(Gb + t * BUF, I, Gp, Gm);
+                    }
+                }
+                if (wave < a.jc) {
+#pragma unroll
+                    for (int q = 0; q < DC; ++q) load_c(wave, q);
+                }
+            }
+        }
+        if (noisy && s + 1 < la.n_steps) draw_ahead(k + 1, (s + 1) & 1);
+        lds_barrier();  // forces written, amplitudes read, normals 0 written
+        if (on) {
+#pragma unroll
+            for (int ii = 0; ii < NJ; ++ii) {
+                const int J = wave + 8 * ii;
+                if (J >= RT) continue;
+                const bool couple = la.nonlinear && J < a.jc;
+                if (ii > 0 && couple) {
+#pragma unroll
+                    for (int q = 0; q < DC; ++q) load_c(J, q);
+                }
+                const f32x4 Eo = cf[(kEo * RT + J) * 4 + g], Wo = cf[(kWo * RT + J) * 4 + g];
+                const f32x4 Ee = cf[(kEe * RT + J) * 4 + g], We = cf[(kWe * RT + J) * 4 + g];
+                f32x4 ao[NT], ae[NT];
+                float zc[NT];  // normal 0 of the next mode tile, for lane group 3
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    float zz[8];
+                    zc[t] = 0.0f;
+                    if constexpr (NW) {
+                        const f32x4 z0 = zslot(t, s & 1, J)[lane], z1 = zslot(t, s & 1, J)[64 + lane];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            zz[r] = z0[r];
+                            zz[4 + r] = z1[r];
+                        }
+                        if (J + 1 < RT) zc[t] = zslot(t, s & 1, J + 1)[col][0];
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) zz[r] = z[t][ii][r];
+                        if (J + 1 < RT) zc[t] = cz[(t * RT + J + 1) * 16 + col];
+                    }
+                    const float zn = __shfl(zz[0], (lane + 16) & 63, 64);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float ze = r < 3 ? zz[2 * r + 2] : (g < 3 ? zn : 0.0f);
+                        ao[t][r] = __builtin_fmaf(Eo[r], Ro[t][ii][r], Wo[r] * zz[2 * r + 1]);
+                        ae[t][r] = __builtin_fmaf(Ee[r], Re[t][ii][r], We[r] * ze);
+                    }
+                    if (J == 0) {
+                        const double r0y = __shfl(r0[t], (lane + 1) & 63, 64);
+                        double nr0 = __builtin_fma(a.W0, (double)zz[0], r0[t]);
+                        if (alpha == 0) nr0 = __builtin_fma(a.gdt, r0y, nr0);
+                        r0[t] = com_lane[t] ? nr0 : 0.0;
+                    }
+                }
+                if (a.gdt != 0.0) {
+                    const f32x4 Go = cf[(kGo * RT + J) * 4 + g], Ge = cf[(kGe * RT + J) * 4 + g];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            ao[t][r] = __builtin_fmaf(Go[r], xlane * dpp<kRowShl1>(Ro[t][ii][r]),
+                                                      ao[t][r]);
+                            ae[t][r] = __builtin_fmaf(Ge[r], xlane * dpp<kRowShl1>(Re[t][ii][r]),
+                                                      ae[t][r]);
+                        }
+                }
+                if (couple) {
+                    f32x4 ce[NT], ao2[NT], ce2[NT], gn[NT][4];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        ce[t] = ao2[t] = ce2[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        slab4(Gb + t * BUF, 0, gn[t], lane);
+                    }
+#pragma unroll
+                    for (int q = 0; q < KS; ++q) {
+                        f32x4 gc[NT][4], xf[4];
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+#pragma unroll
+                            for (int f = 0; f < 4; ++f) gc[t][f] = gn[t][f];
+                            if (q + 1 < KS) slab4(Gb + t * BUF, q + 1, gn[t], lane);
+                        }
+#pragma unroll
+                        for (int f = 0; f < 4; ++f) {
+                            if constexpr (HOLD)
+                                xf[f] = f < 2 ? xc[q % DC][f] : xu[q][f];
+                            else
+                                xf[f] = xc[q % DC][f % CF];
+                        }
+                        if constexpr (BF16) {
+#pragma unroll
+                            for (int m = 0; m < 3; ++m)
+#pragma unroll
+                                for (int t = 0; t < NT; ++t) {
+                                    const int xi = m == 2 ? 1 : 0, bi = m == 1 ? 1 : 0;
+                                    f32x4 &P = (q & 1) ? ao2[t] : ao[t];
+                                    f32x4 &C = (q & 1) ? ce2[t] : ce[t];
+                                    P = mfma_bf16(__builtin_bit_cast(bf16x8, xf[xi]),
+                                                  __builtin_bit_cast(bf16x8, gc[t][bi]), P);
+                                    C = mfma_bf16(__builtin_bit_cast(bf16x8, xf[2 + xi]),
+                                                  __builtin_bit_cast(bf16x8, gc[t][2 + bi]), C);
+                                }
+                        } else {
+#pragma unroll
+                            for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+                                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                                    for (int t = 0; t < NT; ++t) {
+                                        ao[t] = mfma_f32(xf[hh][r], gc[t][2 * hh][r], ao[t]);
+                                        ce[t] = mfma_f32(xf[2 + hh][r], gc[t][2 * hh + 1][r], ce[t]);
+                                    }
+                        }
+                        if constexpr (DC < KS) {
+                            if (q + DC < KS) load_c(J, q + DC);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                    const f32x4 Ce = cf[(kCe * RT + J) * 4 + g];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        if constexpr (BF16) {
+                            ao[t] += ao2[t];
+                            ce[t] += ce2[t];
+                        }
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            ae[t][r] = __builtin_fmaf(Ce[r], ce[t][r], ae[t][r]);
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    // lane group 3's even slot r = 3 takes normal 0 of the next tile
+                    if (J + 1 < RT)
+                        ae[t][3] = __builtin_fmaf(g == 3 ? We[3] : 0.0f, zc[t], ae[t][3]);
+                    Ro[t][ii] = ao[t];
+                    Re[t][ii] = ae[t];
+                    if (la.nonlinear) put(Rb + t * BUF, J, ao[t], ae[t]);
+                }
+            }
+            if constexpr (!HOLD) {
+                if (la.nonlinear) {
+#pragma unroll
+                    for (int u = 0; u < RL; ++u) load_r(u);
+                }
+            }
+        }
+        lds_barrier();  // amplitudes written
+    }
+    if (!on) return;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        if (tile0 + t >= a.ntiles) continue;
+#pragma unroll
+        for (int ii = 0; ii < NJ; ++ii) {
+            const int J = wave + 8 * ii;
+            if (J < RT) {
+                Rt[t][J * 64 + lane] = Ro[t][ii];
+                Rt[t][(RT + J) * 64 + lane] = Re[t][ii];
+            }
+        }
+        if (com_lane[t]) a.R0[(size_t)(tile0 + t) * 16 + col] = r0[t];
+    }
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void small_kernel(LaunchArgs la)
+{
+    __shared__ f32x4 lds[kLdsSmall];
+    const Item it = la.items[blockIdx.x];
+    const BucketArgs a = la.buckets[it.bucket];
+    const int64_t step0 = la.step ? *la.step : la.step0;
+    switch (a.variant) {
+#define DM_SMALL(RT, NT) \
+    case 11 + 8 * NT + RT / 2: small_tile<RT, BF16, NT>(a, la, it.tile0, step0, lds); break
+        DM_SMALL(2, 1);
+        DM_SMALL(4, 1);
+        DM_SMALL(6, 1);
+        DM_SMALL(8, 1);
+        DM_SMALL(10, 1);
+        DM_SMALL(12, 1);
+        DM_SMALL(14, 1);
+        DM_SMALL(16, 1);
+        DM_SMALL(2, 2);
+        DM_SMALL(4, 2);
+        DM_SMALL(6, 2);
+        DM_SMALL(8, 2);
+#undef DM_SMALL
+    default: break;
+    }
+}
+
 // Kernel variant of a tile shape: resident tables exist for RT <= 8,
 // streamed ones for RT >= 8, split tiles for RT = 4, 8, 12, 16, and split
 // tiles of 8 wavefronts for RT = 8, 16 in split-BF16.
@@ -1540,6 +1965,8 @@ bool has_split(int RT, int waves, bool bf16)
 }
 // Wavefronts of a bucket's split tiles (split = 1: 4, split = 2: 8).
 static int split_waves(const FusedBucket &f) { return f.split == 2 ? 8 : 4; }
+// Tiles per workgroup of the small-launch kernel (split = 4).
+bool has_small(int RT, int tpw) { return tpw == 1 || (tpw == 2 && RT <= 8); }
 // Tiles of 16 chains (split = 3): split-BF16, RT = 6 and 8.
 bool has_tile16(int RT, bool bf16) { return bf16 && (RT == 6 || RT == 8); }
 // Chain tiles of a bucket in its shape, and tiles per workgroup.
@@ -2060,7 +2487,8 @@ static BucketArgs bucket_args(const FusedBucket &f)
     a.ntiles = f.ntiles;
     a.x_bytes = (int)x_bytes(f.RT);
     a.jc = f.JC;
-    a.variant = f.split == 3 ? 14 + f.RT / 2
+    a.variant = f.split == 4   ? 11 + 8 * f.tpw + f.RT / 2
+                : f.split == 3 ? 14 + f.RT / 2
                 : f.split    ? split_variant(f.RT, split_waves(f))
                              : variant_of(f.RT, f.resident != 0);
     a.tpw = f.tpw;
@@ -2070,16 +2498,26 @@ static BucketArgs bucket_args(const FusedBucket &f)
     return a;
 }
 
-// Cost model of one workgroup-step when nothing was measured: the MFMA and
-// table work grow as RT^2, the noise and forces as RT; a split tile takes
-// about a third of a wavefront's time for one tile (a quarter on 8
-// wavefronts), a 16-chain tile 0.7 of a wavefront's.
+// Time of one workgroup-step in microseconds when nothing was measured on the
+// live bucket: as measured on one MI355X, by row tiles RT = 2, 4, ... 16 and
+// precision (split-BF16, FP32).  It orders the items and picks the untimed
+// shapes; the 4- and 8-wavefront split tiles, which only table_mode and the
+// autotuner take, are estimated from the small-launch kernel's.
 static double model_us(const FusedBucket &f)
 {
-    const double rt = f.RT;
-    const double us = 0.12 * rt * rt + 0.3 * rt + (f.resident ? 0.0 : 0.02 * rt * rt);
-    if (f.split == 3) return us / 1.4;
-    return f.split == 2 ? us / 4.0 : f.split ? us / 3.0 : us;
+    static const double res[2][4] = {{1.80, 3.51, 5.72, 8.13}, {2.26, 5.2, 8.9, 14.7}};
+    static const double str[2][5] = {{10.9, 13.1, 17.6, 24.0, 30.9}, {15.8, 22.9, 31.1, 42.5, 55.2}};
+    static const double one[2][8] = {{0.87, 1.16, 1.75, 1.94, 3.81, 4.38, 5.87, 6.62},
+                                     {1.13, 1.79, 3.26, 3.94, 6.95, 8.05, 12.7, 14.3}};
+    static const double two[2][4] = {{1.43, 1.99, 3.01, 3.43}, {1.99, 3.19, 6.12, 7.40}};
+    const int k = f.bf16 ? 0 : 1, i = f.RT / 2 - 1;
+    switch (f.split) {
+    case 1: return 1.3 * one[k][i];
+    case 2: return 1.1 * one[k][i];
+    case 3: return f.RT == 6 ? 4.6 : 5.36;
+    case 4: return f.tpw == 2 ? two[k][i] : one[k][i];
+    default: return f.resident ? res[k][i] : str[k][i - 3];
+    }
 }
 
 double fused_item_us(const FusedBucket &f) { return f.item_us > 0.0 ? f.item_us : model_us(f); }
@@ -2138,10 +2576,11 @@ hipError_t fused_plan(FusedPlan &p, const std::vector<const FusedBucket *> &bs, 
                                                 : reinterpret_cast<const void *>(&fused_kernel<false>));
     if (e != hipSuccess) return e;
     std::vector<BucketArgs> ba;
-    bool wide = false, t16 = false;
+    bool wide = false, t16 = false, small = false;
     for (const FusedBucket *f : bs) {
         if (f->bf16 != p.bf16) return hipErrorInvalidValue;
-        const bool ok = f->split == 3 ? has_tile16(f->RT, f->bf16 != 0) && f->tpw == 1 && !f->resident
+        const bool ok = f->split == 4   ? has_small(f->RT, f->tpw) && !f->resident
+                        : f->split == 3 ? has_tile16(f->RT, f->bf16 != 0) && f->tpw == 1 && !f->resident
                         : f->split ? f->split <= 2 && has_split(f->RT, split_waves(*f), f->bf16 != 0) &&
                                        f->tpw == 1 && !f->resident
                                  : has_variant(f->RT, f->resident != 0) && f->tpw >= 1 &&
@@ -2149,6 +2588,7 @@ hipError_t fused_plan(FusedPlan &p, const std::vector<const FusedBucket *> &bs, 
         if (!ok) return hipErrorInvalidValue;
         wide = wide || f->split == 2;
         t16 = t16 || f->split == 3;
+        small = small || f->split == 4;
         ba.push_back(bucket_args(*f));
     }
     if (wide && (e = check_private_segment(reinterpret_cast<const void *>(&split_wide_kernel))) !=
@@ -2157,10 +2597,16 @@ hipError_t fused_plan(FusedPlan &p, const std::vector<const FusedBucket *> &bs, 
     if (t16 && (e = check_private_segment(reinterpret_cast<const void *>(&tile16_kernel))) !=
                    hipSuccess)
         return e;
+    if (small &&
+        (e = check_private_segment(p.bf16 ? reinterpret_cast<const void *>(&small_kernel<true>)
+                                          : reinterpret_cast<const void *>(&small_kernel<false>))) !=
+            hipSuccess)
+        return e;
     std::vector<Item> items = ordered_items(bs);
     if (max_items > 0 && (int)items.size() > max_items) items.resize(max_items);
-    // the items of 8-wavefront split tiles and of 16-chain tiles go to kernels
-    // of their own, after the others (each part keeps its longest-first order)
+    // the items of 8-wavefront split tiles, of 16-chain tiles and of small
+    // launches go to kernels of their own, after the others (each part keeps
+    // its longest-first order)
     auto part = [&](const Item &it) { return std::max(1, bs[it.bucket]->split); };
     std::stable_sort(items.begin(), items.end(),
                      [&](const Item &x, const Item &y) { return part(x) < part(y); });
@@ -2169,6 +2615,8 @@ hipError_t fused_plan(FusedPlan &p, const std::vector<const FusedBucket *> &bs, 
                                  [&](const Item &it) { return part(it) == 2; });
     p.n16 = (int)std::count_if(items.begin(), items.end(),
                                [&](const Item &it) { return part(it) == 3; });
+    p.nsmall = (int)std::count_if(items.begin(), items.end(),
+                                  [&](const Item &it) { return part(it) == 4; });
     p.nbuckets = (int)bs.size();
     if ((e = hipMalloc(&p.d_buckets, sizeof(BucketArgs) * ba.size())) != hipSuccess) return e;
     if ((e = hipMalloc(&p.d_items, sizeof(Item) * std::max<size_t>(1, items.size()))) !=
@@ -2195,7 +2643,7 @@ hipError_t fused_launch(const FusedPlan &p, uint64_t seed, int64_t step0, const 
     la.seed = seed;
     la.n_steps = n_steps;
     la.nonlinear = nonlinear;
-    const int nmain = p.nitems - p.nwide - p.n16;
+    const int nmain = p.nitems - p.nwide - p.n16 - p.nsmall;
     if (nmain > 0) {
         if (p.bf16)
             hipLaunchKernelGGL(fused_kernel<true>, dim3(nmain), dim3(256), 0, st, la);
@@ -2213,6 +2661,15 @@ hipError_t fused_launch(const FusedPlan &p, uint64_t seed, int64_t step0, const 
     if (p.n16 > 0) {
         la.items = static_cast<const Item *>(p.d_items) + nmain + p.nwide;
         hipLaunchKernelGGL(tile16_kernel, dim3(p.n16), dim3(512), 0, st, la);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (p.nsmall > 0) {
+        la.items = static_cast<const Item *>(p.d_items) + nmain + p.nwide + p.n16;
+        if (p.bf16)
+            hipLaunchKernelGGL(small_kernel<true>, dim3(p.nsmall), dim3(512), 0, st, la);
+        else
+            hipLaunchKernelGGL(small_kernel<false>, dim3(p.nsmall), dim3(512), 0, st, la);
     }
     return hipGetLastError();
 }
@@ -2221,12 +2678,16 @@ hipError_t fused_launch(const FusedPlan &p, uint64_t seed, int64_t step0, const 
 // workgroup per CU: the tables take the LDS).
 static double makespan(const std::vector<double> &cost, int ncu)
 {
-    std::vector<double> load((size_t)std::max(1, ncu), 0.0);
+    std::priority_queue<double, std::vector<double>, std::greater<double>> load;
     double m = 0.0;
     for (double c : cost) {  // cost is sorted longest first
-        auto it = std::min_element(load.begin(), load.end());
-        *it += c;
-        m = std::max(m, *it);
+        double t = c;
+        if ((int)load.size() >= std::max(1, ncu)) {
+            t += load.top();
+            load.pop();
+        }
+        load.push(t);
+        m = std::max(m, t);
     }
     return m;
 }
@@ -2265,17 +2726,18 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
         }
         e = hipMemcpyAsync(t.d_R, f.d_R, nR, hipMemcpyDeviceToDevice, st);
         if (e == hipSuccess) e = hipMemcpyAsync(t.d_R0, f.d_R0, nR0, hipMemcpyDeviceToDevice, st);
+        // (resident tables with fewer than 4 tiles a workgroup and the split
+        // tiles of table_mode 3 and 4 are slower than the small-launch kernel
+        // for the same chains: 7.7 against 3.4 us for two tiles of 256 beads,
+        // 3.0 and 2.3 against 1.9 us for one)
         std::vector<Cand> list;
         for (int res = 1; res >= 0; --res) {
             if (!has_variant(f.RT, res) || (res && !fits_resident(f.RT, f.JC))) continue;
-            for (int tpw : {4, 2, 1}) {
-                if (!res && tpw != 4) continue;
-                list.push_back({res, tpw, 0, 0.0});
-            }
+            list.push_back({res, 4, 0, 0.0});
         }
-        if (has_split(f.RT, 4, f.bf16 != 0)) list.push_back({0, 1, 1, 0.0});
-        if (has_split(f.RT, 8, f.bf16 != 0)) list.push_back({0, 1, 2, 0.0});
         if (has_tile16(f.RT, f.bf16 != 0)) list.push_back({0, 1, 3, 0.0});
+        for (int tpw : {1, 2})
+            if (has_small(f.RT, tpw)) list.push_back({0, tpw, 4, 0.0});
         for (Cand &c : list) {
             if (e != hipSuccess) break;
             t.resident = c.resident;
@@ -2313,7 +2775,7 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
     // the 8-wavefront split tiles and the 16-chain tiles run in kernels of
     // their own after the others: the makespans add
     auto evaluate = [&](const std::vector<int> &sel) {
-        std::vector<double> cost[3];
+        std::vector<double> cost[4];
         for (size_t b = 0; b < bs.size(); ++b) {
             const Cand &c = cands[b][sel[b]];
             FusedBucket f;  // the shape alone
@@ -2347,36 +2809,46 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
             }
         }
     } else {
-        // from each bucket's cheapest shape per tile, change one bucket at a
-        // time while the makespan shrinks
-        for (size_t b = 0; b < bs.size(); ++b) {
-            double best = 1e300;
-            for (size_t c = 0; c < cands[b].size(); ++c) {
-                const Cand &k = cands[b][c];
-                const double per_tile =
-                    k.us / (k.split == 3 ? (double)kChains16 / kChainsPerTile : k.tpw);
-                if (per_tile < best) {
-                    best = per_tile;
-                    pick[b] = (int)c;
-                }
-            }
-        }
-        double cur_m = evaluate(pick);
-        for (int pass = 0; pass < 8; ++pass) {
-            bool improved = false;
-            for (size_t b = 0; b < bs.size(); ++b)
+        // from several starts (the cheapest shape per tile of every bucket,
+        // and of each kernel where the bucket has one there), change one
+        // bucket at a time while the makespan shrinks
+        double best_m = 1e300;
+        for (int kernel = -1; kernel <= 4; ++kernel) {
+            std::vector<int> start(bs.size(), 0);
+            for (size_t b = 0; b < bs.size(); ++b) {
+                double best = 1e300;
                 for (size_t c = 0; c < cands[b].size(); ++c) {
-                    if ((int)c == pick[b]) continue;
-                    std::vector<int> trial = pick;
-                    trial[b] = (int)c;
-                    const double m = evaluate(trial);
-                    if (m < cur_m) {
-                        cur_m = m;
-                        pick = trial;
-                        improved = true;
+                    const Cand &k = cands[b][c];
+                    double per_tile =
+                        k.us / (k.split == 3 ? (double)kChains16 / kChainsPerTile : k.tpw);
+                    if (kernel >= 0 && k.split != kernel) per_tile += 1e6;
+                    if (per_tile < best) {
+                        best = per_tile;
+                        start[b] = (int)c;
                     }
                 }
-            if (!improved) break;
+            }
+            double cur_m = evaluate(start);
+            for (int pass = 0; pass < 8; ++pass) {
+                bool improved = false;
+                for (size_t b = 0; b < bs.size(); ++b)
+                    for (size_t c = 0; c < cands[b].size(); ++c) {
+                        if ((int)c == start[b]) continue;
+                        std::vector<int> trial = start;
+                        trial[b] = (int)c;
+                        const double m = evaluate(trial);
+                        if (m < cur_m) {
+                            cur_m = m;
+                            start = trial;
+                            improved = true;
+                        }
+                    }
+                if (!improved) break;
+            }
+            if (cur_m < best_m) {
+                best_m = cur_m;
+                pick = start;
+            }
         }
     }
     char line[256];
@@ -2390,7 +2862,8 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
         f.item_us = c.us;
         for (size_t k = 0; k < cands[b].size(); ++k) {
             const Cand &ck = cands[b][k];
-            const char *shape = ck.split == 3   ? "tile16"
+            const char *shape = ck.split == 4   ? "small"
+                                : ck.split == 3 ? "tile16"
                                 : ck.split == 2 ? "split8"
                                 : ck.split    ? "split"
                                 : ck.resident ? "resident"
@@ -2409,14 +2882,39 @@ int fused_items(const FusedBucket &f)
     return (shape_tiles(f) + f.tpw - 1) / f.tpw;
 }
 
-int fused_tile16_items(const FusedBucket &f)
+// The untimed shapes: every bucket resident or streamed (tpw as set), in the
+// small-launch kernel on one or two tiles a workgroup, or on 16-chain tiles --
+// the one of these with the shortest list schedule at the model's times.
+void fused_default_shapes(const std::vector<FusedBucket *> &bs, int ncu)
 {
-    if (!has_tile16(f.RT, f.bf16 != 0)) return -1;
-    FusedBucket t;
-    t.n = f.n;
-    t.split = 3;
-    t.tpw = 1;
-    return fused_items(t);
+    if (ncu <= 0) return;
+    static const int kModes[4][2] = {{0, 0}, {kForceSmall, 1}, {kForceSmall, 2}, {kForceTile16, 1}};
+    double best = 1e300;
+    int pick = 0;
+    for (int m = 0; m < 4; ++m) {
+        std::vector<double> cost;
+        bool ok = true;
+        for (const FusedBucket *b : bs) {
+            FusedBucket f;  // the shape alone
+            f.RT = b->RT;
+            f.bf16 = b->bf16;
+            f.n = b->n;
+            f.ntiles = b->ntiles;
+            f.resident = b->resident;
+            f.tpw = b->tpw;
+            fused_force_shape(f, kModes[m][0], kModes[m][1]);
+            ok = ok && (m == 0 || f.split >= 3);
+            cost.insert(cost.end(), (size_t)fused_items(f), model_us(f));
+        }
+        if (!ok) continue;
+        std::sort(cost.begin(), cost.end(), std::greater<double>());
+        const double t = makespan(cost, ncu);
+        if (t < best) {
+            best = t;
+            pick = m;
+        }
+    }
+    for (FusedBucket *b : bs) fused_force_shape(*b, kModes[pick][0], kModes[pick][1]);
 }
 
 void fused_force_shape(FusedBucket &f, int table_mode, int tpw)
@@ -2437,10 +2935,11 @@ void fused_force_shape(FusedBucket &f, int table_mode, int tpw)
         f.tpw = 1;
         f.item_us = 0.0;
     }
-    if (table_mode == kForceTile16 && has_tile16(f.RT, f.bf16 != 0)) {
+    if ((table_mode == kForceTile16 && has_tile16(f.RT, f.bf16 != 0)) ||
+        table_mode == kForceSmall) {
         f.resident = 0;
-        f.split = 3;
-        f.tpw = 1;
+        f.split = table_mode == kForceSmall ? 4 : 3;
+        f.tpw = table_mode == kForceSmall && tpw == 2 && has_small(f.RT, 2) ? 2 : 1;
         f.item_us = 0.0;
     }
     if (tpw >= 1 && tpw <= 4 && f.resident) {

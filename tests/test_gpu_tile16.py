@@ -31,12 +31,12 @@ def run(pos, M, mode, steps=(7, 5), **kw):
 
 @pytest.mark.parametrize("M", [130, 192, 194, 256])
 @pytest.mark.parametrize("B,kw", [
-    (1281, {}), (1296, {"gamma_dot": 1e-5}), (1295, {"nonlinear": False, "gamma_dot": 1e-5}),
-    (1300, {"sample_every": 3, "use_graphs": True})])
+    (2561, {}), (2576, {"gamma_dot": 1e-5}), (2575, {"nonlinear": False, "gamma_dot": 1e-5}),
+    (2580, {"sample_every": 3, "use_graphs": True})])
 def test_same_bits_as_five_chain_tiles(M, B, kw):
     pos = inputs.straight_chains(B, M, B_FAC, seed=M, random_orientation=True)
     got, acc, split = run(pos, M, "auto", **kw)
-    assert split == 3, "more 5-chain tiles than compute units take 16-chain tiles"
+    assert split == 3, "the shortest schedule on 256 compute units"
     want, wacc, split = run(pos, M, "resident", **kw)
     assert split == 0
     assert np.array_equal(got, want)
@@ -45,7 +45,7 @@ def test_same_bits_as_five_chain_tiles(M, B, kw):
 
 
 def test_two_lengths_share_the_launch():
-    beads = np.repeat(np.array([160, 256], dtype=np.int32), [700, 650])
+    beads = np.repeat(np.array([160, 256], dtype=np.int32), [2000, 1900])
     beads = np.random.default_rng(0).permutation(beads)
     chains = inputs.mixed_chains(beads, B_FAC, seed=3)
     out = []
