@@ -63,7 +63,7 @@ extern "C" {
 
 /* Arithmetic of the mode step. */
 #define DM_FP64    0  /* FP64 throughout: a persistent kernel on FP64 MFMA up to
-                         512 beads; for longer chains dense phi products and
+                         513 beads; for longer chains dense phi products and
                          separate force-stencil and mode-update kernels */
 #define DM_FP32    1  /* fused persistent kernel, FP32 MFMA transforms, FP32
                          internal modes, FP64 centre of mass */
@@ -169,7 +169,7 @@ typedef struct {
                                 with the shortest schedule (see
                                 dm_get_tiling); 0: fixed shapes */
     int32_t use_graphs;      /* sample_every > 0 (at most 256 on DM_FP64 with
-                                chains beyond 512 beads), 1: whole sampling
+                                chains beyond 513 beads), 1: whole sampling
                                 blocks (the launches of the steps, the step
                                 counter and the observables) are captured
                                 once as a HIP graph and replayed.  On the fused paths, when the
@@ -359,7 +359,7 @@ int dm_coarse_grain_time(double r, double y, int32_t k, double *c_k);
    chain0 + j, so a call reproduces dm_step_modes on those chains of a
    context.  Reduced units: T_star, nu, dtau (= Delta tau), gamma_dot; tables
    and coefficients are built on the device at every call.  No allocation:
-   the tables, the chain indices and (beyond 512 beads) two work buffers live
+   the tables, the chain indices and (beyond 513 beads) two work buffers live
    in one fixed device array of DM_STATIC_SCRATCH_BYTES per GPU, held from the
    first use until the process ends; a call is admitted if it holds 8 (2 M^2 + 3 M + 6 M n_chains) +
    4 n_chains bytes (each part rounded up to 256), e.g. 4096 chains of 256

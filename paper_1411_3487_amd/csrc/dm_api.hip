@@ -35,7 +35,7 @@ struct Bucket {
     // device
     int32_t *d_ids = nullptr;
     int64_t *d_off = nullptr;
-    double *d_X64 = nullptr;         // tables of the persistent FP64 stepper (M <= 512)
+    double *d_X64 = nullptr;         // tables of the persistent FP64 stepper (M <= 513)
     int jc64 = 0;                    // its coupled mode tiles
     // dense FP64 steps of longer chains
     double *d_Ainv = nullptr;        // phi with column p = 0 zeroed (inverse, internal)

@@ -18,7 +18,7 @@ struct Modes64Args {
     double lin, gdt;        // 1 - 2 nu, gamma_dot dtau
 };
 
-constexpr int kModes64MaxM = 512;
+constexpr int kModes64MaxM = 513;
 inline bool modes64_supports(int M) { return M >= 2 && M <= kModes64MaxM; }
 
 // Transform tables of chains of M beads: bytes, and their construction on
@@ -31,6 +31,7 @@ int modes64_coupled_tiles(int M, double nu, double T_star, double dtau);
 // The launches that advance a set of buckets: groups of one kernel shape.
 struct Modes64Group {
     int shape = 0, nitems = 0;
+    bool odd = false;         // a length whose last mode lies beyond its tiles
     size_t lds = 0;
     bool single = false;      // one bucket, passed by value; item = tile index
     Modes64Args one{};

@@ -28,15 +28,19 @@
 //   NT = 1: 5 chains, column 3 chain + component (the last is unused); bond
 //     lengths are summed over three lanes by DPP.  For launches that would
 //     leave compute units idle at 16 chains per workgroup, and for chains of
-//     257..512 beads, whose 16-chain state does not fit the LDS.
+//     258..513 beads, whose 16-chain state does not fit the LDS.
 // Wavefront w owns mode tile T = w, w + P, ... (32 modes: 16 odd, 16 even)
 // and half-bond row tile I = w, w + P, ....
 //
 // Orders.  A result tile has row l/16 + 4 r, column l%16 in lane l, element r.
 // Row i of a table tile stands for index 16 T + 4 (i % 4) + i / 4, so lane
-// group g = l/16 holds the four consecutive indices 4 g + r: with both
-// parities the eight modes 32 T + 8 g .. + 7, two Philox blocks per
-// component.  The products run over K slab pairs q of 8 indices; lane group g
+// group g = l/16 holds the four consecutive indices 4 g + r.  Slot j stands
+// for the odd mode 2 j + 1 and the even mode 2 j + 2 (the centre of mass, p =
+// 0, takes no part in the products and is kept apart), so a lane holds the
+// modes 32 T + 8 g + 1 .. + 8: two Philox blocks per component but for the
+// last mode, whose normal is the first one of the next lane group or, for the
+// last group, of the next mode tile (exchanged through LDS; where an odd chain
+// fills its tiles, the last tile draws that block too).  The products run over K slab pairs q of 8 indices; lane group g
 // supplies 8 q + 2 g + e for the product e = 0, 1, so both operands are read
 // as 16-byte pairs, and the LDS buffers [parity][t][index/2][column][2] give
 // every wavefront read one contiguous kilobyte.
@@ -70,7 +74,7 @@ struct Launch64 {
     int n_steps, nonlinear;
 };
 
-__host__ __device__ inline int half_tiles(int M) { return ((M + 1) / 2 + 15) / 16; }
+__host__ __device__ inline int half_tiles(int M) { return (M / 2 + 15) / 16; }
 
 // Lane moves inside a 16-lane row, out-of-row sources read 0 (row_shl:n gives
 // lane i the value of lane i + n).
@@ -97,45 +101,60 @@ __device__ __forceinline__ double chain_sum(double v, int alpha)
 
 // One mirror pair of 16-row products: odd and even accumulators of NT column
 // tiles over Q slab pairs.  X: fragments [q][parity][lane]; B: LDS operands,
-// [parity][t] at stride bs, [q][lane] inside.  Both operands are loaded two
-// slab pairs ahead (the fragments come from L2).
+// [parity][t] at stride bs, [q][lane] inside.  The fragments, from L2, are
+// loaded two slab pairs ahead; the LDS operands two ahead for one column tile,
+// and for three each as soon as its products have issued, the other tiles'
+// products (512 cycles) covering the read (two buffers spill).
 template <int NT>
 __device__ __forceinline__ void mirror_product(const f64x2 *__restrict__ X, const f64x2 *B, int bs,
                                                int Q, f64x4 (&so)[NT], f64x4 (&se)[NT])
 {
-    f64x2 x[2][2], b[2][2][NT];
-    auto load = [&](int k, int q) {
+    constexpr int KB = NT == 1 ? 2 : 1;
+    f64x2 x[2][2], b[KB][2][NT];
+    auto load_x = [&](int k, int q) {
 #pragma unroll
-        for (int par = 0; par < 2; ++par) {
-            x[k][par] = X[(size_t)(2 * q + par) * 64];
+        for (int par = 0; par < 2; ++par) x[k][par] = X[(size_t)(2 * q + par) * 64];
+    };
+    auto load_b = [&](int k, int t, int q) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) b[k][par][t] = B[(par * NT + t) * bs + q * 64];
-        }
+        for (int par = 0; par < 2; ++par) b[k][par][t] = B[(par * NT + t) * bs + q * 64];
     };
 #pragma unroll
     for (int t = 0; t < NT; ++t) so[t] = se[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-    load(0, 0);
-    load(1, 1);
+    load_x(0, 0);
+    load_x(1, 1);
+#pragma unroll
+    for (int k = 0; k < KB; ++k)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) load_b(k, t, k);
     for (int q = 0; q < Q; q += 2) {  // Q is even
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
 #pragma unroll
-            for (int e = 0; e < 2; ++e)
+            for (int t = 0; t < NT; ++t) {
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    so[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[k][0][e], b[k][0][t][e], so[t],
-                                                                 0, 0, 0);
-                    se[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[k][1][e], b[k][1][t][e], se[t],
-                                                                 0, 0, 0);
+                for (int e = 0; e < 2; ++e) {
+                    so[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[k][0][e], b[k % KB][0][t][e],
+                                                                 so[t], 0, 0, 0);
+                    se[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[k][1][e], b[k % KB][1][t][e],
+                                                                 se[t], 0, 0, 0);
                 }
-            load(k, min(q + k + 2, Q - 1));
+                load_b(k % KB, t, min(q + k + KB, Q - 1));
+            }
+            load_x(k, min(q + k + 2, Q - 1));
         }
     }
 }
 
-template <int NT, int P, int NU>
+// NOISE: wavefronts RT .. P - 1 draw the normals, one step ahead, for the
+// others (RT <= 4): in a launch with a tile or less per compute unit the step is
+// a chain of latencies, and the FP64 noise of a wavefront's own modes is a
+// third of it (3.2 -> 2.6 us per step of one chain of 64 beads).
+// ODD: some chain's last mode needs the block beyond its tiles.
+template <int NT, int P, int NU, bool NOISE, bool ODD>
 __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
 {
+    static_assert(!NOISE || (NT == 1 && NU == 1), "noise wavefronts: one small tile");
     extern __shared__ double lds[];
     const Item64 it = la.items ? la.items[blockIdx.x] : Item64{0, (int)blockIdx.x};
     const Modes64Args a = la.buckets ? la.buckets[it.bucket] : la.one;
@@ -144,13 +163,19 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
     const int M = a.M, H = M / 2, RT = half_tiles(M), Hp = 16 * RT, Q = 2 * RT;
     const int bs = Hp * 8;  // f64x2 of one (parity, column tile) buffer
     double *cf = lds;                                  // [E, C, W][parity][Hp]
-    f64x2 *Rb = reinterpret_cast<f64x2 *>(lds + 6 * Hp);  // [parity][t][index/2][column]
+    const bool beyond = ODD && 32 * RT < M;  // the last mode's normal is one block further
+    double *r0 = cf + 6 * Hp;         // centre of mass: [t][column]
+    double *cz = r0 + 16 * NT;        // normal 0 of every lane: [t][T][lane]
+    f64x2 *Rb = reinterpret_cast<f64x2 *>(cz + NT * 64 * (RT + 1));  // [parity][t][index/2][column]
     f64x2 *Gb = NT == 1 ? Rb + 2 * bs : Rb;            // [sum, difference][t][index/2][column]
+    double *zb = reinterpret_cast<double *>(Gb + 2 * bs);  // NOISE: [step parity][T][8][lane]
+    const int zs = (RT + 1) * 512;                         // of one step parity
     for (int i = threadIdx.x; i < 6 * Hp; i += 64 * P) {
-        const int kind = i / (2 * Hp), par = (i / Hp) % 2, p = 2 * (i % Hp) + (par == 0 ? 1 : 0);
+        const int kind = i / (2 * Hp), par = (i / Hp) % 2, p = 2 * (i % Hp) + 1 + par;
         const double *src = kind == 0 ? a.E : kind == 1 ? a.C : a.W;
-        cf[i] = p < M && !(kind == 1 && p == 0) ? src[p] : 0.0;
+        cf[i] = p < M ? src[p] : 0.0;
     }
+    const double W0 = a.W[0];
     // chain and component of this lane's column(s)
     const int alpha = NT == 1 ? col % 3 : 0;
     const int j = NT == 1 ? kSmallTile * it.tile + col / 3 : kLargeTile * it.tile + col;
@@ -163,17 +188,19 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
     // amplitudes of the own mode tiles: [parity odd, even][component][r]
     double R[NU][2][NT][4];
 #pragma unroll
-    for (int ii = 0; ii < NU; ++ii)
+    for (int t = 0; t < NT; ++t) {
+        const size_t row = (size_t)(NT == 1 ? alpha : t) * M;
+        if (wave == 0 && g == 0) r0[16 * t + col] = valid ? Rj[row] : 0.0;
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int ii = 0; ii < NU; ++ii)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int par = 0; par < 2; ++par) {
-                    const int p = 32 * (wave + P * ii) + 8 * g + 2 * r + (par == 0 ? 1 : 0);
-                    R[ii][par][t][r] =
-                        valid && p < M ? Rj[(size_t)(NT == 1 ? alpha : t) * M + p] : 0.0;
+                    const int p = 32 * (wave + P * ii) + 8 * g + 2 * r + 1 + par;
+                    R[ii][par][t][r] = valid && p < M ? Rj[row + p] : 0.0;
                 }
+    }
     // values v[r] of index tile T into a buffer
     auto put = [&](f64x2 *buf, int par, int t, int T, const double (&v)[4]) {
         f64x2 *d = buf + (par * NT + t) * bs + (8 * T + 2 * g) * 16 + col;
@@ -191,10 +218,26 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
                     for (int t = 0; t < NT; ++t) put(Rb, par, t, T, R[ii][par][t]);
         }
     };
+    // noise wavefronts: half h of the normals of mode tile T at step k
+    auto draw_ahead = [&](int64_t k, int buf) {
+        for (int u = wave - RT; u < 2 * RT + (beyond ? 1 : 0); u += P - RT) {
+            const int T = u >> 1, h = u & 1;
+            double z[4];
+            normals4_f64(noise_bits(la.seed, (uint32_t)(8 * T + 2 * g + h), chain, k,
+                                    (uint32_t)alpha, kTagMode),
+                         z);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                zb[buf * zs + (T * 8 + 4 * h + e) * 64 + lane] = z[e];
+        }
+    };
+    const int64_t k0 = la.step0 + (la.step ? *la.step : 0);
     if (la.nonlinear) put_state();
+    if constexpr (NOISE) {
+        if (wave >= RT && la.n_steps > 0) draw_ahead(k0, 0);
+    }
     __syncthreads();
 
-    const int64_t k0 = la.step0 + (la.step ? *la.step : 0);
     for (int s = 0; s < la.n_steps; ++s) {
         const int64_t k = k0 + s;
         // ---- bonds of the own half-bond rows and their forces
@@ -250,50 +293,122 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
                     }
             }
         }
-        // ---- E R + W eta (+ shear) of the own modes
+        // ---- E R + W eta (+ shear) of the own modes: the normals of a Philox
+        // block as they come (z of block h; normal 0 of the first belongs to
+        // the lane group before, the last even mode takes its own below)
+        if (a.gdt != 0.0) {  // the x amplitudes drift with R^y before its update
+#pragma unroll
+            for (int ii = 0; ii < NU; ++ii)
+#pragma unroll
+                for (int par = 0; par < 2; ++par)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if constexpr (NT == 1) {
+                            const double y = dpp64<kShl1>(R[ii][par][0][r]);
+                            R[ii][par][0][r] = fma64(alpha == 0 ? a.gdt : 0.0, y, R[ii][par][0][r]);
+                        } else {
+                            R[ii][par][0][r] = fma64(a.gdt, R[ii][par][1][r], R[ii][par][0][r]);
+                        }
+                    }
+        }
+        auto update = [&](int ii, int T, int t, int h, const double (&z)[4]) {
+            const double *Eo = cf + 16 * T + 4 * g, *Ee = Eo + Hp;
+            const double *Wo = Eo + 4 * Hp, *We = Eo + 5 * Hp;
+            double(&o)[4] = R[ii][0][t];
+            double(&e)[4] = R[ii][1][t];
+            if (h == 0) {
+                o[0] = fma64(Eo[0], o[0], Wo[0] * z[1]);
+                e[0] = fma64(Ee[0], e[0], We[0] * z[2]);
+                o[1] = fma64(Eo[1], o[1], Wo[1] * z[3]);
+            } else {
+                e[1] = fma64(Ee[1], e[1], We[1] * z[0]);
+                o[2] = fma64(Eo[2], o[2], Wo[2] * z[1]);
+                e[2] = fma64(Ee[2], e[2], We[2] * z[2]);
+                o[3] = fma64(Eo[3], o[3], Wo[3] * z[3]);
+                e[3] *= Ee[3];
+            }
+        };
+        if constexpr (!NOISE) {
+#pragma unroll
+            for (int ii = 0; ii < NU; ++ii) {
+                const int T = wave + P * ii;
+                if (T >= RT) continue;
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const uint32_t comp = (uint32_t)(NT == 1 ? alpha : t);
+                    double first = 0.0;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        double z[4];
+                        normals4_f64(noise_bits(la.seed, (uint32_t)(8 * T + 2 * g + h), chain, k,
+                                                comp, kTagMode),
+                                     z);
+                        if (h == 0) first = z[0];
+                        update(ii, T, t, h, z);
+                    }
+                    // (written after the updates: an LDS write between them
+                    // keeps every coefficient read above it in registers)
+                    cz[(t * (RT + 1) + T) * 64 + lane] = first;
+                }
+            }
+            if (ODD && beyond && wave == (RT - 1) % P) {
+#pragma unroll 1
+                for (int t = 0; t < NT; ++t) {
+                    double z[2];
+                    normal_pair_f64(noise_bits(la.seed, (uint32_t)(8 * RT), chain, k,
+                                               (uint32_t)(NT == 1 ? alpha : t), kTagMode),
+                                    0, z);
+                    cz[(t * (RT + 1) + RT) * 64 + lane] = z[0];
+                }
+            }
+        } else {
+            if (wave >= RT && s + 1 < la.n_steps) draw_ahead(k + 1, (s + 1) & 1);
+        }
+        __syncthreads();  // forces and normals 0 written (NT = 1: and the amplitudes read)
+        if (wave == P - 1 && lane < 16) {  // centre of mass: a free walk, drift from R_0^y
+            double v[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const double z0 = NOISE ? zb[(s & 1) * zs + lane] : cz[t * (RT + 1) * 64 + lane];
+                v[t] = fma64(W0, z0, r0[16 * t + lane]);
+            }
+            if constexpr (NT == 1)
+                v[0] = fma64(alpha == 0 ? a.gdt : 0.0, r0[lane < 15 ? lane + 1 : 15], v[0]);
+            else
+                v[0] = fma64(a.gdt, r0[16 + lane], v[0]);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) r0[16 * t + lane] = v[t];
+        }
+        // ---- the last even mode's normal, and the coupling of the own modes
 #pragma unroll
         for (int ii = 0; ii < NU; ++ii) {
             const int T = wave + P * ii;
             if (T >= RT) continue;
-            const double *Eo = cf + 16 * T + 4 * g, *Ee = Eo + Hp;
-            const double *Wo = Eo + 4 * Hp, *We = Eo + 5 * Hp;
+            if constexpr (NOISE) {
+                const double *zp = zb + (s & 1) * zs + T * 512 + lane;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const uint32_t comp = (uint32_t)(NT == 1 ? alpha : t);
-                double z[8];
-                normals4_f64(noise_bits(la.seed, (uint32_t)(8 * T + 2 * g), chain, k, comp,
-                                        kTagMode),
-                             z);
-                normals4_f64(noise_bits(la.seed, (uint32_t)(8 * T + 2 * g + 1), chain, k, comp,
-                                        kTagMode),
-                             z + 4);
+                for (int h = 0; h < 2; ++h) {
+                    double z[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    double sh_o = 0.0, sh_e = 0.0;
-                    if (a.gdt != 0.0) {  // R^y before its own update, for the x amplitudes
-                        if constexpr (NT == 1) {
-                            const double yo = dpp64<kShl1>(R[ii][0][0][r]),
-                                         ye = dpp64<kShl1>(R[ii][1][0][r]);
-                            sh_o = alpha == 0 ? a.gdt * yo : 0.0;
-                            sh_e = alpha == 0 ? a.gdt * ye : 0.0;
-                        } else if (t == 0) {
-                            sh_o = a.gdt * R[ii][0][1][r];
-                            sh_e = a.gdt * R[ii][1][1][r];
-                        }
-                    }
-                    R[ii][0][t][r] =
-                        fma64(Eo[r], R[ii][0][t][r] + sh_o, Wo[r] * z[2 * r + 1]);
-                    R[ii][1][t][r] = fma64(Ee[r], R[ii][1][t][r] + sh_e, We[r] * z[2 * r]);
+                    for (int e = 0; e < 4; ++e) z[e] = zp[64 * (4 * h + e)];
+                    update(ii, T, 0, h, z);
                 }
             }
-        }
-        if (la.nonlinear) {
-            __syncthreads();  // forces written (NT = 1: and the amplitudes read)
-            // ---- coupling of the own modes
+            // normal 0 of lane group g + 1, or of the next tile's group 0
+            const double w3 = cf[5 * Hp + 16 * T + 4 * g + 3];
 #pragma unroll
-            for (int ii = 0; ii < NU; ++ii) {
-                const int T = wave + P * ii;
-                if (T >= a.jc) continue;
+            for (int t = 0; t < NT; ++t) {
+                double zl;
+                if constexpr (NOISE) {
+                    const int l = T * 512 + (g < 3 ? lane + 16 : 512 + col);
+                    zl = T + 1 < RT || beyond || g < 3 ? zb[(s & 1) * zs + l] : 0.0;
+                } else {
+                    const int l = T * 64 + lane + 16;
+                    zl = T + 1 < RT || beyond || g < 3 ? cz[t * (RT + 1) * 64 + l] : 0.0;
+                }
+                R[ii][1][t][3] = fma64(w3, zl, R[ii][1][t][3]);
+            }
+            if (la.nonlinear && T < a.jc) {
                 f64x4 so[NT], se[NT];
                 mirror_product<NT>(X2 + (size_t)T * Q * 128, Gb + lane, bs, Q, so, se);
                 const double *Co = cf + 2 * Hp + 16 * T + 4 * g, *Ce = Co + Hp;
@@ -305,23 +420,28 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
                         R[ii][1][t][r] = fma64(Ce[r], se[t][r], R[ii][1][t][r]);
                     }
             }
+        }
+        if (la.nonlinear) {
             if constexpr (NT == 3) __syncthreads();  // every wavefront has read the forces
             put_state();
-            __syncthreads();
         }
+        __syncthreads();  // amplitudes written, normals 0 read
     }
     if (!valid) return;
 #pragma unroll
-    for (int ii = 0; ii < NU; ++ii)
+    for (int t = 0; t < NT; ++t) {
+        const size_t row = (size_t)(NT == 1 ? alpha : t) * M;
+        if (wave == 0 && g == 0) Rj[row] = r0[16 * t + col];
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int ii = 0; ii < NU; ++ii)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int par = 0; par < 2; ++par) {
-                    const int p = 32 * (wave + P * ii) + 8 * g + 2 * r + (par == 0 ? 1 : 0);
-                    if (p < M) Rj[(size_t)(NT == 1 ? alpha : t) * M + p] = R[ii][par][t][r];
+                    const int p = 32 * (wave + P * ii) + 8 * g + 2 * r + 1 + par;
+                    if (p < M) Rj[row + p] = R[ii][par][t][r];
                 }
+    }
 }
 
 // Fragments of both products: [product][tile][q][parity][lane][2].  Product
@@ -338,9 +458,9 @@ __global__ __launch_bounds__(256) void modes64_table_kernel(double *__restrict__
     const int row = lane % 16, ri = 16 * T + 4 * (row % 4) + row / 4;
     const int ki = 8 * q + 2 * (lane / 16) + e;
     const int b = prod == 0 ? ri : ki, jm = prod == 0 ? ki : ri;
-    const int n = b + 1, p = 2 * jm + (par == 0 ? 1 : 0);
+    const int n = b + 1, p = 2 * jm + 1 + par;
     double v = 0.0;
-    if (b < H && p < M && p > 0) {
+    if (b < H && p < M) {
         const int m = (int)((long)p * n % (2L * M));
         const double sigma = -2.0 * sqrt(2.0 / M) * sinpi((double)p / (2.0 * M));
         v = m == 0 || m == M ? 0.0 : sigma * sinpi((double)m / (double)M);
@@ -349,19 +469,27 @@ __global__ __launch_bounds__(256) void modes64_table_kernel(double *__restrict__
     X[i] = v;
 }
 
-// Kernel shapes, and the smallest that holds a chain length at NT = 1.
-enum { kS1x2, kS1x4, kS1x8, kS1x8b, kS3x8, kShapes };
-int small_shape(int M)
+// Kernel shapes, and the smallest that holds a chain length at NT = 1 (with
+// noise wavefronts where the launch leaves compute units to spare).
+enum { kS1n8, kS1x2, kS1x4, kS1x8, kS1x8b, kS3x8, kShapes };
+int small_shape(int M, bool noise)
 {
     const int RT = half_tiles(M);
+    if (noise && RT <= 4) return kS1n8;
     return RT <= 2 ? kS1x2 : RT <= 4 ? kS1x4 : RT <= 8 ? kS1x8 : kS1x8b;
 }
 constexpr int kLargeMaxM = 256;  // RT <= 8: one row tile per wavefront
 
+// Whether the normal of the chain's last mode lies in the block beyond its
+// mode tiles.
+bool beyond_tiles(int M) { return 32 * half_tiles(M) < M; }
+
 size_t lds_bytes(int shape, int M)
 {
     const size_t Hp = 16 * (size_t)half_tiles(M);
-    return sizeof(double) * (6 * Hp + (shape == kS3x8 ? 6 : 4) * Hp * 16);
+    const size_t nt = shape == kS3x8 ? 3 : 1, bufs = shape == kS3x8 ? 6 : 4;
+    return sizeof(double) *
+           (6 * Hp + nt * 16 + nt * 4 * (Hp + 16) + bufs * Hp * 16 + (shape == kS1n8 ? 64 * (Hp + 16) : 0));
 }
 int tile_chains(int shape) { return shape == kS3x8 ? kLargeTile : kSmallTile; }
 
@@ -377,25 +505,28 @@ bool large_tiles_pay(int M, int n, int ncu)
     return 2.6 * r3 < (double)r1;
 }
 
-hipError_t launch_shape(int shape, size_t lds, int nitems, const Launch64 &la, hipStream_t st)
+hipError_t launch_shape(int shape, bool odd, size_t lds, int nitems, const Launch64 &la,
+                        hipStream_t st)
 {
     if (nitems <= 0 || la.n_steps <= 0) return hipSuccess;
-    switch (shape) {
-    case kS1x2:
-        hipLaunchKernelGGL((modes64_kernel<1, 2, 1>), dim3(nitems), dim3(128), lds, st, la);
-        break;
-    case kS1x4:
-        hipLaunchKernelGGL((modes64_kernel<1, 4, 1>), dim3(nitems), dim3(256), lds, st, la);
-        break;
-    case kS1x8:
-        hipLaunchKernelGGL((modes64_kernel<1, 8, 1>), dim3(nitems), dim3(512), lds, st, la);
-        break;
-    case kS1x8b:
-        hipLaunchKernelGGL((modes64_kernel<1, 8, 2>), dim3(nitems), dim3(512), lds, st, la);
-        break;
-    case kS3x8:
-        hipLaunchKernelGGL((modes64_kernel<3, 8, 1>), dim3(nitems), dim3(512), lds, st, la);
-        break;
+    switch (shape + (odd ? kShapes : 0)) {
+#define DM_M64(SHAPE, NT, P, NU, NOISE, ODD)                                                 \
+    case SHAPE:                                                                            \
+        hipLaunchKernelGGL((modes64_kernel<NT, P, NU, NOISE, ODD>), dim3(nitems), dim3(64 * P), \
+                           lds, st, la);                                                   \
+        break
+        DM_M64(kS1n8, 1, 8, 1, true, false);
+        DM_M64(kS1x2, 1, 2, 1, false, false);
+        DM_M64(kS1x4, 1, 4, 1, false, false);
+        DM_M64(kS1x8, 1, 8, 1, false, false);
+        DM_M64(kS1x8b, 1, 8, 2, false, false);
+        DM_M64(kS3x8, 3, 8, 1, false, false);
+        DM_M64(kShapes + kS1n8, 1, 8, 1, true, true);
+        DM_M64(kShapes + kS1x2, 1, 2, 1, false, true);
+        DM_M64(kShapes + kS1x4, 1, 4, 1, false, true);
+        DM_M64(kShapes + kS1x8, 1, 8, 1, false, true);
+        DM_M64(kShapes + kS1x8b, 1, 8, 2, false, true);
+#undef DM_M64
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -465,21 +596,21 @@ void modes64_plan_free(Modes64Plan &p)
 // one launch in the widest of their shapes while it is small (all lengths in
 // flight at once; the spare wavefronts of the shorter chains only wait), and
 // get one launch per shape beyond that, where each fills the GPU by itself.
+// Up to a tile per compute unit the shorter chains have noise wavefronts.
 hipError_t modes64_plan(Modes64Plan &p, const std::vector<Modes64Args> &bs, int ncu,
                         hipStream_t st)
 {
     modes64_plan_free(p);
-    std::vector<int> shape(bs.size());
-    int widest = 0;
+    std::vector<int> shape(bs.size(), kS3x8);
     size_t small_tiles = 0;
+    for (const Modes64Args &a : bs)
+        if (!large_tiles_pay(a.M, a.n, ncu))
+            small_tiles += (size_t)(a.n + kSmallTile - 1) / kSmallTile;
+    int widest = 0;
     for (size_t b = 0; b < bs.size(); ++b) {
-        if (large_tiles_pay(bs[b].M, bs[b].n, ncu)) {
-            shape[b] = kS3x8;
-            continue;
-        }
-        shape[b] = small_shape(bs[b].M);
+        if (large_tiles_pay(bs[b].M, bs[b].n, ncu)) continue;
+        shape[b] = small_shape(bs[b].M, small_tiles <= (size_t)ncu);
         widest = std::max(widest, shape[b]);
-        small_tiles += (size_t)(bs[b].n + kSmallTile - 1) / kSmallTile;
     }
     if (small_tiles <= 2 * (size_t)ncu)
         for (int &s : shape)
@@ -501,6 +632,7 @@ hipError_t modes64_plan(Modes64Plan &p, const std::vector<Modes64Args> &bs, int 
             for (int t = 0; t < nt; ++t) items.push_back({(int)ba.size(), t});
             ba.push_back(bs[b]);
             g.lds = std::max(g.lds, lds_bytes(s, bs[b].M));
+            g.odd = g.odd || beyond_tiles(bs[b].M);
         }
         g.nitems = (int)items.size();
         g.single = ba.size() == 1;
@@ -529,7 +661,7 @@ hipError_t modes64_launch(const Modes64Plan &p, uint64_t seed, int64_t step0,
         la.one = g.one;
         la.buckets = static_cast<const Modes64Args *>(g.d_buckets);
         la.items = static_cast<const Item64 *>(g.d_items);
-        const hipError_t e = launch_shape(g.shape, g.lds, g.nitems, la, st);
+        const hipError_t e = launch_shape(g.shape, g.odd, g.lds, g.nitems, la, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -538,10 +670,12 @@ hipError_t modes64_launch(const Modes64Plan &p, uint64_t seed, int64_t step0,
 hipError_t modes64_launch_one(const Modes64Args &a, int ncu, uint64_t seed, int64_t step0,
                               int n_steps, int nonlinear, hipStream_t st)
 {
-    const int shape = large_tiles_pay(a.M, a.n, ncu) ? kS3x8 : small_shape(a.M);
+    const int shape = large_tiles_pay(a.M, a.n, ncu)
+                          ? kS3x8
+                          : small_shape(a.M, a.n <= kSmallTile * ncu);
     Launch64 la = launch_args(seed, step0, nullptr, n_steps, nonlinear);
     la.one = a;
-    return launch_shape(shape, lds_bytes(shape, a.M),
+    return launch_shape(shape, beyond_tiles(a.M), lds_bytes(shape, a.M),
                         (a.n + tile_chains(shape) - 1) / tile_chains(shape), la, st);
 }
 

@@ -42,7 +42,8 @@ def check(got, pos, ids, M, dtau, seed, gdot=0.0, nonlinear=True):
 @pytest.mark.parametrize("B,M,dtau", [
     (1, 2, 1.0), (4, 3, 1.0), (5, 31, 10.0), (6, 32, 10.0), (5, 33, 10.0), (9, 64, 10.0),
     (11, 65, 10.0), (16, 97, 10.0), (5, 128, 50.0), (6, 129, 50.0), (7, 256, 100.0),
-    (6, 257, 100.0), (4, 511, 100.0), (6, 512, 100.0), (2, 513, 100.0)])
+    (6, 257, 100.0), (4, 511, 100.0), (6, 512, 100.0), (2, 513, 100.0),
+    (2, 514, 100.0)])
 def test_five_chain_tiles(B, M, dtau):
     pos = inputs.straight_chains(B, M, B_FAC, seed=M, random_orientation=True)
     gdot = 1e-4 if B % 2 else 0.0
@@ -68,7 +69,7 @@ def test_sixteen_chain_tiles(M, gdot, nonlinear):
     check(got[ids], pos[ids], ids, M, dtau, 9, gdot, nonlinear)
 
 
-@pytest.mark.parametrize("lens", [[2, 33, 64, 65], [20, 100, 130, 257, 400, 512, 513]])
+@pytest.mark.parametrize("lens", [[2, 33, 64, 65], [20, 100, 130, 257, 400, 513, 514]])
 def test_many_lengths_in_one_launch(lens):
     beads = np.random.default_rng(1).permutation(np.repeat(np.array(lens, dtype=np.int32), 6))
     chains = inputs.mixed_chains(beads, B_FAC, seed=3)
