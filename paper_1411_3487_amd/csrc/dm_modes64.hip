@@ -74,7 +74,7 @@ struct Launch64 {
     int n_steps, nonlinear;
 };
 
-__host__ __device__ inline int half_tiles(int M) { return (M / 2 + 15) / 16; }
+inline __host__ __device__ int half_tiles(int M) { return modes64_half_tiles(M); }
 
 // Lane moves inside a 16-lane row, out-of-row sources read 0 (row_shl:n gives
 // lane i the value of lane i + n).
@@ -105,12 +105,21 @@ __device__ __forceinline__ double chain_sum(double v, int alpha)
 // loaded two slab pairs ahead; the LDS operands two ahead for one column tile,
 // and for three each as soon as its products have issued, the other tiles'
 // products (512 cycles) covering the read (two buffers spill).
+// x holds the first two fragments pairs of each parity on entry (first_pairs).
+__device__ __forceinline__ void first_pairs(const f64x2 *__restrict__ X, f64x2 (&x)[2][2])
+{
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int par = 0; par < 2; ++par) x[k][par] = X[(size_t)(2 * k + par) * 64];
+}
 template <int NT>
-__device__ __forceinline__ void mirror_product(const f64x2 *__restrict__ X, const f64x2 *B, int bs,
-                                               int Q, f64x4 (&so)[NT], f64x4 (&se)[NT])
+__device__ __forceinline__ void mirror_product(const f64x2 *__restrict__ X, f64x2 (&x)[2][2],
+                                               const f64x2 *B, int bs, int Q, f64x4 (&so)[NT],
+                                               f64x4 (&se)[NT])
 {
     constexpr int KB = NT == 1 ? 2 : 1;
-    f64x2 x[2][2], b[KB][2][NT];
+    f64x2 b[KB][2][NT];
     auto load_x = [&](int k, int q) {
 #pragma unroll
         for (int par = 0; par < 2; ++par) x[k][par] = X[(size_t)(2 * q + par) * 64];
@@ -121,8 +130,6 @@ __device__ __forceinline__ void mirror_product(const f64x2 *__restrict__ X, cons
     };
 #pragma unroll
     for (int t = 0; t < NT; ++t) so[t] = se[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-    load_x(0, 0);
-    load_x(1, 1);
 #pragma unroll
     for (int k = 0; k < KB; ++k)
 #pragma unroll
@@ -146,12 +153,52 @@ __device__ __forceinline__ void mirror_product(const f64x2 *__restrict__ X, cons
     }
 }
 
+// The same for one column tile with all fragments in registers (QH >= Q).
+template <int QH>
+__device__ __forceinline__ void held_product(const f64x2 (&x)[QH][2], const f64x2 *B, int bs, int Q,
+                                             f64x4 &so, f64x4 &se)
+{
+    constexpr int D = QH > 4 ? 2 : QH;  // operands read ahead
+    f64x2 b[D][2];
+#pragma unroll
+    for (int q = 0; q < D; ++q)
+#pragma unroll
+        for (int par = 0; par < 2; ++par) b[q][par] = B[par * bs + min(q, Q - 1) * 64];
+    so = se = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < QH; ++q)
+        if (q < Q) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                so = __builtin_amdgcn_mfma_f64_16x16x4f64(x[q][0][e], b[q % D][0][e], so, 0, 0, 0);
+                se = __builtin_amdgcn_mfma_f64_16x16x4f64(x[q][1][e], b[q % D][1][e], se, 0, 0, 0);
+            }
+            if (q + D < QH)
+#pragma unroll
+                for (int par = 0; par < 2; ++par)
+                    b[q % D][par] = B[par * bs + min(q + D, Q - 1) * 64];
+        }
+}
+
+// Workgroup barrier for the LDS exchanges that leaves the fragment loads in
+// flight (__syncthreads() waits for every outstanding vector memory load).
+__device__ __forceinline__ void lds_barrier()
+{
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) alone
+    __builtin_amdgcn_s_barrier();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 // NOISE: wavefronts RT .. P - 1 draw the normals, one step ahead, for the
 // others (RT <= 4): in a launch with a tile or less per compute unit the step is
 // a chain of latencies, and the FP64 noise of a wavefront's own modes is a
 // third of it (3.2 -> 2.6 us per step of one chain of 64 beads).
+// There the fragments of both products stay in registers too (QH slab pairs;
+// 0: streamed, the first two pairs of a product in flight across the barrier
+// before it).
 // ODD: some chain's last mode needs the block beyond its tiles.
-template <int NT, int P, int NU, bool NOISE, bool ODD>
+template <int NT, int P, int NU, bool NOISE, bool ODD, int QH>
 __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
 {
     static_assert(!NOISE || (NT == 1 && NU == 1), "noise wavefronts: one small tile");
@@ -236,6 +283,21 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
     if constexpr (NOISE) {
         if (wave >= RT && la.n_steps > 0) draw_ahead(k0, 0);
     }
+    [[maybe_unused]] f64x2 x1[2][2], x2[2][2], h1[QH > 0 ? QH : 1][2], h2[QH > 0 ? QH : 1][2];
+    if (wave < RT && la.nonlinear) {
+        if constexpr (QH > 0) {
+#pragma unroll
+            for (int q = 0; q < QH; ++q)
+#pragma unroll
+                for (int par = 0; par < 2; ++par) {
+                    const size_t i = ((size_t)wave * Q + min(q, Q - 1)) * 128 + 64 * par;
+                    h1[q][par] = X1[i];
+                    h2[q][par] = X2[i];
+                }
+        } else {
+            first_pairs(X1 + (size_t)wave * Q * 128, x1);
+        }
+    }
     __syncthreads();
 
     for (int s = 0; s < la.n_steps; ++s) {
@@ -248,7 +310,12 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
                 const int I = wave + P * ii;
                 if (I >= RT) continue;
                 f64x4 so[NT], se[NT];
-                mirror_product<NT>(X1 + (size_t)I * Q * 128, Rb + lane, bs, Q, so, se);
+                if constexpr (QH > 0) {
+                    held_product(h1, Rb + lane, bs, Q, so[0], se[0]);
+                } else {
+                    if (ii > 0) first_pairs(X1 + (size_t)I * Q * 128, x1);
+                    mirror_product<NT>(X1 + (size_t)I * Q * 128, x1, Rb + lane, bs, Q, so, se);
+                }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     // rows and columns of padding have u = 0: a small number
@@ -284,7 +351,7 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
         if constexpr (NT == 3) {
             static_assert(NT == 1 || NU == 1, "the forces of one row tile stay in registers");
             if (la.nonlinear) {
-                __syncthreads();  // every wavefront has read the amplitudes
+                lds_barrier();  // every wavefront has read the amplitudes
                 if (wave < RT)
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
@@ -364,7 +431,10 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
         } else {
             if (wave >= RT && s + 1 < la.n_steps) draw_ahead(k + 1, (s + 1) & 1);
         }
-        __syncthreads();  // forces and normals 0 written (NT = 1: and the amplitudes read)
+        if constexpr (QH == 0) {
+            if (la.nonlinear && wave < a.jc) first_pairs(X2 + (size_t)wave * Q * 128, x2);
+        }
+        lds_barrier();  // forces and normals 0 written (NT = 1: and the amplitudes read)
         if (wave == P - 1 && lane < 16) {  // centre of mass: a free walk, drift from R_0^y
             double v[NT];
 #pragma unroll
@@ -410,7 +480,12 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
             }
             if (la.nonlinear && T < a.jc) {
                 f64x4 so[NT], se[NT];
-                mirror_product<NT>(X2 + (size_t)T * Q * 128, Gb + lane, bs, Q, so, se);
+                if constexpr (QH > 0) {
+                    held_product(h2, Gb + lane, bs, Q, so[0], se[0]);
+                } else {
+                    if (ii > 0) first_pairs(X2 + (size_t)T * Q * 128, x2);
+                    mirror_product<NT>(X2 + (size_t)T * Q * 128, x2, Gb + lane, bs, Q, so, se);
+                }
                 const double *Co = cf + 2 * Hp + 16 * T + 4 * g, *Ce = Co + Hp;
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
@@ -422,10 +497,13 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
             }
         }
         if (la.nonlinear) {
-            if constexpr (NT == 3) __syncthreads();  // every wavefront has read the forces
+            if constexpr (QH == 0) {
+                if (wave < RT) first_pairs(X1 + (size_t)wave * Q * 128, x1);
+            }
+            if constexpr (NT == 3) lds_barrier();  // every wavefront has read the forces
             put_state();
         }
-        __syncthreads();  // amplitudes written, normals 0 read
+        lds_barrier();  // amplitudes written, normals 0 read
     }
     if (!valid) return;
 #pragma unroll
@@ -444,38 +522,19 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
     }
 }
 
-// Fragments of both products: [product][tile][q][parity][lane][2].  Product
-// 0 (u = chi R): row = half-bond, K = mode; product 1 (coupling): row = mode,
-// K = half-bond.  chi_{n,p} = sigma_p sin(pi (p n mod 2M) / M), exact zeros
-// at multiples of M.
 __global__ __launch_bounds__(256) void modes64_table_kernel(double *__restrict__ X, int M)
 {
-    const int RT = half_tiles(M), Q = 2 * RT, H = M / 2;
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)2 * RT * Q * 256) return;
-    const int e = (int)(i % 2), lane = (int)(i / 2 % 64), par = (int)(i / 128 % 2);
-    const int q = (int)(i / 256 % Q), T = (int)(i / 256 / Q % RT), prod = (int)(i / 256 / Q / RT);
-    const int row = lane % 16, ri = 16 * T + 4 * (row % 4) + row / 4;
-    const int ki = 8 * q + 2 * (lane / 16) + e;
-    const int b = prod == 0 ? ri : ki, jm = prod == 0 ? ki : ri;
-    const int n = b + 1, p = 2 * jm + 1 + par;
-    double v = 0.0;
-    if (b < H && p < M) {
-        const int m = (int)((long)p * n % (2L * M));
-        const double sigma = -2.0 * sqrt(2.0 / M) * sinpi((double)p / (2.0 * M));
-        v = m == 0 || m == M ? 0.0 : sigma * sinpi((double)m / (double)M);
-        if (prod == 1 && 2 * n == M) v *= 0.5;
-    }
-    X[i] = v;
+    if (i < modes64_table_bytes(M) / sizeof(double)) X[i] = modes64_table_value(i, M);
 }
 
 // Kernel shapes, and the smallest that holds a chain length at NT = 1 (with
 // noise wavefronts where the launch leaves compute units to spare).
-enum { kS1n8, kS1x2, kS1x4, kS1x8, kS1x8b, kS3x8, kShapes };
+enum { kS1n2, kS1n4, kS1x2, kS1x4, kS1x8, kS1x8b, kS3x8, kShapes };
 int small_shape(int M, bool noise)
 {
     const int RT = half_tiles(M);
-    if (noise && RT <= 4) return kS1n8;
+    if (noise && RT <= 4) return RT <= 2 ? kS1n2 : kS1n4;
     return RT <= 2 ? kS1x2 : RT <= 4 ? kS1x4 : RT <= 8 ? kS1x8 : kS1x8b;
 }
 constexpr int kLargeMaxM = 256;  // RT <= 8: one row tile per wavefront
@@ -489,7 +548,7 @@ size_t lds_bytes(int shape, int M)
     const size_t Hp = 16 * (size_t)half_tiles(M);
     const size_t nt = shape == kS3x8 ? 3 : 1, bufs = shape == kS3x8 ? 6 : 4;
     return sizeof(double) *
-           (6 * Hp + nt * 16 + nt * 4 * (Hp + 16) + bufs * Hp * 16 + (shape == kS1n8 ? 64 * (Hp + 16) : 0));
+           (6 * Hp + nt * 16 + nt * 4 * (Hp + 16) + bufs * Hp * 16 + (shape <= kS1n4 ? 64 * (Hp + 16) : 0));
 }
 int tile_chains(int shape) { return shape == kS3x8 ? kLargeTile : kSmallTile; }
 
@@ -510,22 +569,24 @@ hipError_t launch_shape(int shape, bool odd, size_t lds, int nitems, const Launc
 {
     if (nitems <= 0 || la.n_steps <= 0) return hipSuccess;
     switch (shape + (odd ? kShapes : 0)) {
-#define DM_M64(SHAPE, NT, P, NU, NOISE, ODD)                                                 \
+#define DM_M64(SHAPE, NT, P, NU, NOISE, ODD, QH)                                            \
     case SHAPE:                                                                            \
-        hipLaunchKernelGGL((modes64_kernel<NT, P, NU, NOISE, ODD>), dim3(nitems), dim3(64 * P), \
-                           lds, st, la);                                                   \
+        hipLaunchKernelGGL((modes64_kernel<NT, P, NU, NOISE, ODD, QH>), dim3(nitems),          \
+                           dim3(64 * P), lds, st, la);                                     \
         break
-        DM_M64(kS1n8, 1, 8, 1, true, false);
-        DM_M64(kS1x2, 1, 2, 1, false, false);
-        DM_M64(kS1x4, 1, 4, 1, false, false);
-        DM_M64(kS1x8, 1, 8, 1, false, false);
-        DM_M64(kS1x8b, 1, 8, 2, false, false);
-        DM_M64(kS3x8, 3, 8, 1, false, false);
-        DM_M64(kShapes + kS1n8, 1, 8, 1, true, true);
-        DM_M64(kShapes + kS1x2, 1, 2, 1, false, true);
-        DM_M64(kShapes + kS1x4, 1, 4, 1, false, true);
-        DM_M64(kShapes + kS1x8, 1, 8, 1, false, true);
-        DM_M64(kShapes + kS1x8b, 1, 8, 2, false, true);
+        DM_M64(kS1n2, 1, 8, 1, true, false, 4);
+        DM_M64(kS1n4, 1, 8, 1, true, false, 8);
+        DM_M64(kS1x2, 1, 2, 1, false, false, 0);
+        DM_M64(kS1x4, 1, 4, 1, false, false, 0);
+        DM_M64(kS1x8, 1, 8, 1, false, false, 0);
+        DM_M64(kS1x8b, 1, 8, 2, false, false, 0);
+        DM_M64(kS3x8, 3, 8, 1, false, false, 0);
+        DM_M64(kShapes + kS1n2, 1, 8, 1, true, true, 4);
+        DM_M64(kShapes + kS1n4, 1, 8, 1, true, true, 8);
+        DM_M64(kShapes + kS1x2, 1, 2, 1, false, true, 0);
+        DM_M64(kShapes + kS1x4, 1, 4, 1, false, true, 0);
+        DM_M64(kShapes + kS1x8, 1, 8, 1, false, true, 0);
+        DM_M64(kShapes + kS1x8b, 1, 8, 2, false, true, 0);
 #undef DM_M64
     default: return hipErrorInvalidValue;
     }
@@ -545,12 +606,6 @@ Launch64 launch_args(uint64_t seed, int64_t step0, const int64_t *d_step, int n_
 }
 
 }  // namespace
-
-size_t modes64_table_bytes(int M)
-{
-    const size_t RT = half_tiles(M);
-    return sizeof(double) * 2 * RT * 2 * RT * 256;
-}
 
 hipError_t modes64_build_tables(double *X, int M, hipStream_t st)
 {

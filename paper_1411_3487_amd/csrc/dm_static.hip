@@ -79,15 +79,20 @@ __global__ __launch_bounds__(256) void static_phi_kernel(double *__restrict__ Ai
 //   zeta_p = 16 nu s^4, zeta^l_p - zeta_p = (1 - 2 nu) 4 s^2,
 //   E = exp(-zeta dtau), C = -E expm1(-(zeta^l - zeta) dtau) / (zeta^l - zeta),
 //   W = sqrt(-T* expm1(-2 zeta dtau) / zeta), limits C = dtau E, W = sqrt(2 T* dtau).
-// Also the chain indices chain0 + j.
+// Also the chain indices chain0 + j, and the persistent stepper's tables where
+// X is given (one kernel: each of these takes a launch's latency, 4.3 us).
 __global__ __launch_bounds__(256) void static_coef_kernel(double *__restrict__ E,
                                                           double *__restrict__ C,
                                                           double *__restrict__ W,
-                                                          int32_t *__restrict__ ids, int M,
+                                                          int32_t *__restrict__ ids,
+                                                          double *__restrict__ X, int M,
                                                           int nch, double nu, double T_star,
                                                           double dtau, uint32_t chain0)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t ix = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (X && ix < modes64_table_bytes(M) / sizeof(double)) X[ix] = modes64_table_value(ix, M);
+    if (ix >= (size_t)(M > nch ? M : nch)) return;
+    const int i = (int)ix;
     if (i < nch) ids[i] = (int32_t)(chain0 + (uint32_t)i);
     if (i >= M) return;
     if (i == 0) {
@@ -166,15 +171,18 @@ extern "C" int dm_step_modes_f64_static(double *R_dev, int32_t n_chains, int32_t
     double *E = (double *)take(8 * (size_t)M), *C = (double *)take(8 * (size_t)M),
            *W = (double *)take(8 * (size_t)M);
     int32_t *ids = (int32_t *)take(4 * (size_t)n_chains);
-    const int nt = M > n_chains ? M : n_chains;
-    hipLaunchKernelGGL(static_coef_kernel, dim3((nt + 255) / 256), dim3(256), 0, st, E, C, W, ids,
-                       M, n_chains, nu, T_star, dtau, chain0);
+    const bool persistent = modes64_supports(M);
+    // the persistent stepper needs its tables alone (at most 2 MB; with the
+    // coefficients they fit the array beside any chain count that
+    // static_bytes admits)
+    double *X = persistent ? (double *)take(modes64_table_bytes(M)) : nullptr;
+    size_t nt = (size_t)(M > n_chains ? M : n_chains);
+    if (persistent && modes64_table_bytes(M) / sizeof(double) > nt)
+        nt = modes64_table_bytes(M) / sizeof(double);
+    hipLaunchKernelGGL(static_coef_kernel, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, E,
+                       C, W, ids, X, M, n_chains, nu, T_star, dtau, chain0);
     hipError_t e = hipGetLastError();
-    if (modes64_supports(M)) {
-        // the persistent stepper needs its tables alone (at most 2 MB; with the
-        // coefficients they fit the array beside any chain count that
-        // static_bytes admits)
-        double *X = (double *)take(modes64_table_bytes(M));
+    if (persistent) {
         Modes64Args a;
         a.X = X;
         a.E = E;
@@ -191,7 +199,6 @@ extern "C" int dm_step_modes_f64_static(double *R_dev, int32_t n_chains, int32_t
         if (e == hipSuccess) e = hipGetDevice(&dev);
         if (e == hipSuccess)
             e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess) e = modes64_build_tables(X, M, st);
         constexpr int64_t kPerLaunch = 1 << 16;
         for (int64_t s = 0; s < n_steps && e == hipSuccess; s += kPerLaunch)
             e = modes64_launch_one(a, ncu > 0 ? ncu : 1, seed, step0 + s,
