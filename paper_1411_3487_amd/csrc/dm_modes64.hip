@@ -21,7 +21,7 @@
 //
 // Tiles.  The columns of every product are (chain, component) pairs, 16 to a
 // v_mfma_f64_16x16x4_f64.
-//   NT = 3: 16 chains, one column tile per component.  A lane holds x, y, z
+//   NT = 3: 16 chains, one column tile per component (up to 256 beads).  A lane holds x, y, z
 //     of a bond, so bond lengths are lane-local, and each table fragment
 //     serves 48 columns.  The amplitudes and the forces share one LDS buffer
 //     (98 KB at M = 256).
@@ -530,7 +530,7 @@ __global__ __launch_bounds__(256) void modes64_table_kernel(double *__restrict__
 
 // Kernel shapes, and the smallest that holds a chain length at NT = 1 (with
 // noise wavefronts where the launch leaves compute units to spare).
-enum { kS1n2, kS1n4, kS1x2, kS1x4, kS1x8, kS1x8b, kS3x8, kShapes };
+enum { kS1n2, kS1n4, kS1x2, kS1x4, kS1x8, kS1x8b, kS3x2, kS3x4, kS3x8, kShapes };
 int small_shape(int M, bool noise)
 {
     const int RT = half_tiles(M);
@@ -546,22 +546,35 @@ bool beyond_tiles(int M) { return 32 * half_tiles(M) < M; }
 size_t lds_bytes(int shape, int M)
 {
     const size_t Hp = 16 * (size_t)half_tiles(M);
-    const size_t nt = shape == kS3x8 ? 3 : 1, bufs = shape == kS3x8 ? 6 : 4;
+    const size_t nt = shape >= kS3x2 ? 3 : 1, bufs = shape >= kS3x2 ? 6 : 4;
     return sizeof(double) *
            (6 * Hp + nt * 16 + nt * 4 * (Hp + 16) + bufs * Hp * 16 + (shape <= kS1n4 ? 64 * (Hp + 16) : 0));
 }
-int tile_chains(int shape) { return shape == kS3x8 ? kLargeTile : kSmallTile; }
+int tile_chains(int shape) { return shape >= kS3x2 ? kLargeTile : kSmallTile; }
+int large_shape(int M)
+{
+    const int RT = half_tiles(M);
+    return RT <= 2 ? kS3x2 : RT <= 4 ? kS3x4 : kS3x8;
+}
 
-// 16-chain tiles when they fill the GPU as well as 5-chain tiles do: a
-// 16-chain workgroup takes the time of about 2.6 5-chain ones (it reads each
-// table fragment once for 48 columns), so the rounds of the two shapes are
-// compared at that price.
+// 16-chain tiles where their rounds over the compute units take less time.
+// Above 4 row tiles a workgroup of either shape fills a compute unit and a
+// 16-chain one takes the time of about 2.6 5-chain ones (it reads each table
+// fragment once for 48 columns).  Up to 4, several 5-chain workgroups share a
+// compute unit, so their time grows with the chains (microseconds per step
+// and 1000 chains), and a 16-chain workgroup's is its own (two share one at
+// RT <= 2), both measured on 256 compute units: at 4096 x 128 16.1 against 12.8
+// us, at 8192 x 64 11.5 against 8.9, but at 3000 x 128 12.2 against 12.6.
 bool large_tiles_pay(int M, int n, int ncu)
 {
-    if (M > kLargeMaxM || half_tiles(M) <= 4) return false;
+    const int RT = half_tiles(M);
+    if (M > kLargeMaxM || beyond_tiles(M)) return false;
     const int w3 = (n + kLargeTile - 1) / kLargeTile, w1 = (n + kSmallTile - 1) / kSmallTile;
     const int r3 = (w3 + ncu - 1) / ncu, r1 = (w1 + ncu - 1) / ncu;
-    return 2.6 * r3 < (double)r1;
+    if (RT > 4) return 2.6 * r3 < (double)r1;
+    static const double small_us[4] = {0.7, 1.4, 2.9, 4.0}, large_us[4] = {5.7, 8.8, 10.3, 12.7};
+    return large_us[RT - 1] * (RT <= 2 ? (r3 + 1) / 2 : r3) <
+           small_us[RT - 1] * 1e-3 * n * 256.0 / ncu;
 }
 
 hipError_t launch_shape(int shape, bool odd, size_t lds, int nitems, const Launch64 &la,
@@ -580,6 +593,8 @@ hipError_t launch_shape(int shape, bool odd, size_t lds, int nitems, const Launc
         DM_M64(kS1x4, 1, 4, 1, false, false, 0);
         DM_M64(kS1x8, 1, 8, 1, false, false, 0);
         DM_M64(kS1x8b, 1, 8, 2, false, false, 0);
+        DM_M64(kS3x2, 3, 2, 1, false, false, 0);
+        DM_M64(kS3x4, 3, 4, 1, false, false, 0);
         DM_M64(kS3x8, 3, 8, 1, false, false, 0);
         DM_M64(kShapes + kS1n2, 1, 8, 1, true, true, 4);
         DM_M64(kShapes + kS1n4, 1, 8, 1, true, true, 8);
@@ -656,20 +671,23 @@ hipError_t modes64_plan(Modes64Plan &p, const std::vector<Modes64Args> &bs, int 
                         hipStream_t st)
 {
     modes64_plan_free(p);
-    std::vector<int> shape(bs.size(), kS3x8);
+    std::vector<int> shape(bs.size());
     size_t small_tiles = 0;
     for (const Modes64Args &a : bs)
         if (!large_tiles_pay(a.M, a.n, ncu))
             small_tiles += (size_t)(a.n + kSmallTile - 1) / kSmallTile;
     int widest = 0;
     for (size_t b = 0; b < bs.size(); ++b) {
-        if (large_tiles_pay(bs[b].M, bs[b].n, ncu)) continue;
+        if (large_tiles_pay(bs[b].M, bs[b].n, ncu)) {
+            shape[b] = large_shape(bs[b].M);
+            continue;
+        }
         shape[b] = small_shape(bs[b].M, small_tiles <= (size_t)ncu);
         widest = std::max(widest, shape[b]);
     }
     if (small_tiles <= 2 * (size_t)ncu)
         for (int &s : shape)
-            if (s != kS3x8) s = widest;
+            if (s < kS3x2) s = widest;
     for (int s = 0; s < kShapes; ++s) {
         std::vector<size_t> in;
         for (size_t b = 0; b < bs.size(); ++b)
@@ -726,7 +744,7 @@ hipError_t modes64_launch_one(const Modes64Args &a, int ncu, uint64_t seed, int6
                               int n_steps, int nonlinear, hipStream_t st)
 {
     const int shape = large_tiles_pay(a.M, a.n, ncu)
-                          ? kS3x8
+                          ? large_shape(a.M)
                           : small_shape(a.M, a.n <= kSmallTile * ncu);
     Launch64 la = launch_args(seed, step0, nullptr, n_steps, nonlinear);
     la.one = a;

@@ -69,6 +69,18 @@ def test_sixteen_chain_tiles(M, gdot, nonlinear):
     check(got[ids], pos[ids], ids, M, dtau, 9, gdot, nonlinear)
 
 
+@pytest.mark.parametrize("B,M,gdot", [(4090, 128, 0.0), (3700, 96, 1e-4), (6300, 64, 1e-4),
+                                      (8190, 30, 0.0)])
+def test_sixteen_chain_tiles_of_short_chains(B, M, gdot):
+    pos = inputs.straight_chains(B, M, B_FAC, seed=M, random_orientation=True)
+    with Context(pos, seed=9, precision="fp64") as ctx:
+        ctx.set_params([M], [10.0], T_star=TS, nu=NU, gamma_dot=gdot)
+        ctx.step_modes(STEPS)
+        got = ctx.positions()
+    ids = np.array([0, 15, 16, 17, 2000, B - 17, B - 2, B - 1])
+    check(got[ids], pos[ids], ids, M, 10.0, 9, gdot)
+
+
 @pytest.mark.parametrize("lens", [[2, 33, 64, 65], [20, 100, 130, 257, 400, 513, 514]])
 def test_many_lengths_in_one_launch(lens):
     beads = np.random.default_rng(1).permutation(np.repeat(np.array(lens, dtype=np.int32), 6))
