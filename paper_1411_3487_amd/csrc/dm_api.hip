@@ -163,12 +163,14 @@ void free_bucket(Bucket &b)
 
 bool fused_precision(int p) { return p == DM_FP32 || p == DM_BF16X3; }
 
-// Positions of all chains of a bucket (FP64, bucket order) into b.d_r.
-int bucket_positions(dm_ctx *ctx, Bucket &b, hipStream_t st)
+// Positions of all chains of a bucket (FP64): in bucket order into b.d_r, or, with
+// dst (device), in the caller's order.
+int bucket_positions(dm_ctx *ctx, Bucket &b, hipStream_t st, double *dst = nullptr)
 {
     if (fused_precision(ctx->precision))
         DM_HIP(ctx, dm::fused_unpack_modes(b.fused, b.d_R64, b.M, b.n, st));
-    DM_HIP(ctx, dm::launch_gemm_f64(b.d_Apos, b.d_R64, b.d_r, b.M, 3 * b.n, st));
+    DM_HIP(ctx, dm::launch_gemm_f64(b.d_Apos, b.d_R64, dst ? dst : b.d_r, b.M, 3 * b.n, st,
+                                    dst ? b.d_off : nullptr));
     return DM_OK;
 }
 
@@ -1056,12 +1058,9 @@ int dm_get_positions(dm_ctx *ctx, double *dst, int32_t dst_on_device)
     if (ctx->pending_init)
         return fail(ctx, DM_ESTATE, "no state yet: the initial state is built by dm_set_params");
     for (Bucket &b : ctx->buckets) {
-        int rc = bucket_positions(ctx, b, ctx->stream);
+        int rc = bucket_positions(ctx, b, ctx->stream, dst_on_device ? dst : nullptr);
         if (rc) return rc;
-        if (dst_on_device) {
-            DM_HIP(ctx, dm::launch_scatter_chains(b.d_r, dst, b.d_off, 3 * b.M, b.n,
-                                                  ctx->stream));
-        } else {
+        if (!dst_on_device) {
             std::vector<double> h((size_t)3 * b.M * b.n);
             DM_HIP(ctx, hipMemcpyAsync(h.data(), b.d_r, sizeof(double) * h.size(),
                                        hipMemcpyDeviceToHost, ctx->stream));

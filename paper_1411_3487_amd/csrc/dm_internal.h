@@ -46,8 +46,10 @@ void set_ctxless_error(const char *msg);
 // `st` and returns the launch status.
 
 // Y[c][i] = sum_k A[i*M + k] X[c*M + k] for c < ncol, i, k < M (FP64 MFMA).
+// With off (device; one offset per chain of three columns) column c goes to
+// Y + off[c/3] + (c%3)*M instead of Y + c*M.
 hipError_t launch_gemm_f64(const double *A, const double *X, double *Y, int M,
-                           int ncol, hipStream_t st);
+                           int ncol, hipStream_t st, const int64_t *off = nullptr);
 
 // Bead forces of the nonlinear bond term from internal positions r:
 // g_n = u_n (1/|u_n| - lin), F_n = g_n - g_{n+1} (Eqs. e4, e11).
@@ -116,10 +118,5 @@ hipError_t launch_check_finite_f64(const double *x, size_t n, int *flag,
                                    hipStream_t st);
 hipError_t launch_check_finite_f32(const float *x, size_t n, int *flag,
                                    hipStream_t st);
-
-// dst[off[c] + i] = src[c*len + i] for i < len (bucket -> caller order).
-hipError_t launch_scatter_chains(const double *src, double *dst,
-                                 const int64_t *off, int len, int nch,
-                                 hipStream_t st);
 
 }  // namespace dm

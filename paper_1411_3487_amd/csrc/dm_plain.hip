@@ -18,74 +18,85 @@ namespace {
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // --------------------------------------------------------------------------
-// GEMM on FP64 MFMA (v_mfma_f64_16x16x4f64).  Workgroup tile 64 rows x 64
-// columns, 4 waves of 32 x 32 (2 x 2 MFMA tiles), K staged through LDS in
-// chunks of 16.  MFMA operand layout per lane l: A[i = l%16][k = l/16],
-// B[k = l/16][j = l%16]; result D[i = l/16 + 4r][j = l%16], r = 0..3 (the
-// FP64 instruction interleaves its four result rows across the lane groups).
+// GEMM on FP64 MFMA (v_mfma_f64_16x16x4f64).  MFMA operand layout per lane l:
+// A[i = l%16][k = l/16], B[k = l/16][j = l%16]; result D[i = l/16 + 4r][j =
+// l%16], r = 0..3 (the FP64 instruction interleaves its four result rows
+// across the lane groups).
+//
+// Column c of the result goes to Y + c M, or, with off (one offset per chain of
+// three columns), to Y + off[c / 3] + (c % 3) M: positions go straight to the
+// caller's order.
+//
+// Any M: workgroup tile 32 rows x 32 columns, 4 waves of 16 x 16, K in chunks
+// of 32, the next chunk in registers while the current one is multiplied from
+// one of two LDS buffers.  Small tiles, because lengths that are no multiple
+// of 16 come mostly in small launches: 140 chains of 257 beads make 126
+// workgroups, where 64 x 64 tiles without a pipeline made 35 and took 32 us (7
+// us now).
 // --------------------------------------------------------------------------
 constexpr int kGemmBM = 64, kGemmBN = 64, kGemmBK = 16;
 
-__global__ __launch_bounds__(256) void gemm_f64_kernel(const double *__restrict__ A,
-                                                       const double *__restrict__ X,
-                                                       double *__restrict__ Y, int M,
-                                                       int ncol)
+__device__ __forceinline__ double *gemm_column(double *Y, const int64_t *off, int M, int c)
 {
-    __shared__ double As[kGemmBM][kGemmBK + 1];
-    __shared__ double Xs[kGemmBN][kGemmBK + 1];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wi = wave >> 1, wj = wave & 1;
-    const int i0 = blockIdx.x * kGemmBM;
-    const int c0 = blockIdx.y * kGemmBN;
-    f64x4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
-
-    for (int k0 = 0; k0 < M; k0 += kGemmBK) {
-#pragma unroll
-        for (int e = 0; e < (kGemmBM * kGemmBK) / 256; ++e) {
-            const int idx = tid + 256 * e;
-            const int row = idx / kGemmBK, kk = idx % kGemmBK;
-            const int gk = k0 + kk;
-            const int gi = i0 + row, gc = c0 + row;
-            As[row][kk] = (gi < M && gk < M) ? A[(size_t)gi * M + gk] : 0.0;
-            Xs[row][kk] = (gc < ncol && gk < M) ? X[(size_t)gc * M + gk] : 0.0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < kGemmBK; ks += 4) {
-            double a[2], b[2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                a[t] = As[32 * wi + 16 * t + (lane & 15)][ks + (lane >> 4)];
-                b[t] = Xs[32 * wj + 16 * t + (lane & 15)][ks + (lane >> 4)];
-            }
-#pragma unroll
-            for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-                for (int tj = 0; tj < 2; ++tj)
-                    acc[ti][tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ti], b[tj],
-                                                                      acc[ti][tj], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 2; ++tj) {
-            const int c = c0 + 32 * wj + 16 * tj + (lane & 15);
-            const int ib = i0 + 32 * wi + 16 * ti + (lane >> 4);
-            if (c >= ncol) continue;
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (ib + 4 * r < M) Y[(size_t)c * M + ib + 4 * r] = acc[ti][tj][r];
-        }
+    return off ? Y + off[c / 3] + (size_t)(c % 3) * M : Y + (size_t)c * M;
 }
 
-// The same product when M is a multiple of 16 (every chain length the
-// method runs in practice): 16-byte loads of A and X, and a software
+constexpr int kAnyB = 32, kAnyK = 32;
+__global__ __launch_bounds__(256) void gemm_f64_any_kernel(const double *__restrict__ A,
+                                                           const double *__restrict__ X,
+                                                           double *__restrict__ Y,
+                                                           const int64_t *__restrict__ off, int M,
+                                                           int ncol)
+{
+    __shared__ double As[2][kAnyB][kAnyK + 1];
+    __shared__ double Xs[2][kAnyB][kAnyK + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wi = 16 * (wave >> 1), wj = 16 * (wave & 1);
+    const int i0 = blockIdx.x * kAnyB, c0 = blockIdx.y * kAnyB;
+    const int lk = tid & 31, lr = tid >> 5;  // rows lr, lr + 8, + 16, + 24
+    double ra[4], rx[4];
+    auto load = [&](int k0) {
+        const int gk = k0 + lk;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int gi = i0 + lr + 8 * e, gc = c0 + lr + 8 * e;
+            ra[e] = gi < M && gk < M ? A[(size_t)gi * M + gk] : 0.0;
+            rx[e] = gc < ncol && gk < M ? X[(size_t)gc * M + gk] : 0.0;
+        }
+    };
+    auto store = [&](int b) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            As[b][lr + 8 * e][lk] = ra[e];
+            Xs[b][lr + 8 * e][lk] = rx[e];
+        }
+    };
+    f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+    const int nk = (M + kAnyK - 1) / kAnyK;
+    load(0);
+    store(0);
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+        const int b = kt & 1;
+        if (kt + 1 < nk) load((kt + 1) * kAnyK);
+#pragma unroll
+        for (int ks = 0; ks < kAnyK; ks += 4)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(As[b][wi + (lane & 15)][ks + (lane >> 4)],
+                                                       Xs[b][wj + (lane & 15)][ks + (lane >> 4)],
+                                                       acc, 0, 0, 0);
+        if (kt + 1 < nk) store(b ^ 1);
+        __syncthreads();
+    }
+    const int c = c0 + wj + (lane & 15), ib = i0 + wi + (lane >> 4);
+    if (c >= ncol) return;
+    double *y = gemm_column(Y, off, M, c);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (ib + 4 * r < M) y[ib + 4 * r] = acc[r];
+}
+
+// The same product when M is a multiple of 16, workgroup tile 64 rows x BN
+// columns, 4 waves of 32 x BN/2, K in chunks of 16: 16-byte loads of A and X, and a software
 // pipeline over the K chunks -- the next chunk is loaded into registers while
 // the current one is multiplied from the other of two LDS buffers, one
 // barrier per chunk.  The MFMA sequence of every accumulator is the one of
@@ -110,7 +121,8 @@ __device__ __forceinline__ int xcd_local_index(int w, int n)
 template <int BN>
 __global__ __launch_bounds__(256) void gemm_f64_pipe_kernel(const double *__restrict__ A,
                                                             const double *__restrict__ X,
-                                                            double *__restrict__ Y, int M,
+                                                            double *__restrict__ Y,
+                                                            const int64_t *__restrict__ off, int M,
                                                             int ncol)
 {
     static_assert(BN == 64 || BN == 32, "column tile");
@@ -192,9 +204,10 @@ __global__ __launch_bounds__(256) void gemm_f64_pipe_kernel(const double *__rest
             const int c = c0 + (BN / 2) * wj + 16 * tj + (lane & 15);
             const int ib = i0 + 32 * wi + 16 * ti + (lane >> 4);
             if (c >= ncol) continue;
+            double *y = gemm_column(Y, off, M, c);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (ib + 4 * r < M) Y[(size_t)c * M + ib + 4 * r] = acc[ti][tj][r];
+                if (ib + 4 * r < M) y[ib + 4 * r] = acc[ti][tj][r];
         }
 }
 
@@ -1285,21 +1298,12 @@ __global__ void check_finite_kernel(const T *__restrict__ x, size_t n, int *flag
     if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
 }
 
-__global__ void scatter_chains_kernel(const double *__restrict__ src, double *__restrict__ dst,
-                                      const int64_t *__restrict__ off, int len, int nch)
-{
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)nch * len) return;
-    const int c = (int)(idx / len), i = (int)(idx % len);
-    dst[off[c] + i] = src[idx];
-}
-
 inline unsigned blocks_for(size_t n, unsigned t) { return (unsigned)((n + t - 1) / t); }
 
 }  // namespace
 
 hipError_t launch_gemm_f64(const double *A, const double *X, double *Y, int M, int ncol,
-                           hipStream_t st)
+                           hipStream_t st, const int64_t *off)
 {
     if (M <= 0 || ncol <= 0) return hipSuccess;
     dim3 grid((M + kGemmBM - 1) / kGemmBM, (ncol + kGemmBN - 1) / kGemmBN);
@@ -1308,15 +1312,16 @@ hipError_t launch_gemm_f64(const double *A, const double *X, double *Y, int M, i
         // of the GPU two workgroups
         if (grid.x * grid.y < 512) {
             const dim3 g1(grid.x * ((ncol + 31) / 32));
-            hipLaunchKernelGGL(gemm_f64_pipe_kernel<32>, g1, dim3(256), 0, st, A, X, Y, M,
-                               ncol);
+            hipLaunchKernelGGL(gemm_f64_pipe_kernel<32>, g1, dim3(256), 0, st, A, X, Y, off,
+                               M, ncol);
         } else {
             const dim3 g1(grid.x * grid.y);
-            hipLaunchKernelGGL(gemm_f64_pipe_kernel<64>, g1, dim3(256), 0, st, A, X, Y, M,
-                               ncol);
+            hipLaunchKernelGGL(gemm_f64_pipe_kernel<64>, g1, dim3(256), 0, st, A, X, Y, off,
+                               M, ncol);
         }
     } else {
-        hipLaunchKernelGGL(gemm_f64_kernel, grid, dim3(256), 0, st, A, X, Y, M, ncol);
+        const dim3 g((M + kAnyB - 1) / kAnyB, (ncol + kAnyB - 1) / kAnyB);
+        hipLaunchKernelGGL(gemm_f64_any_kernel, g, dim3(256), 0, st, A, X, Y, off, M, ncol);
     }
     return hipGetLastError();
 }
@@ -1458,16 +1463,6 @@ hipError_t launch_check_finite_f32(const float *x, size_t n, int *flag, hipStrea
     unsigned b = blocks_for(n, 256);
     if (b > 2048) b = 2048;
     hipLaunchKernelGGL(check_finite_kernel<float>, dim3(b), dim3(256), 0, st, x, n, flag);
-    return hipGetLastError();
-}
-
-hipError_t launch_scatter_chains(const double *src, double *dst, const int64_t *off, int len,
-                                 int nch, hipStream_t st)
-{
-    const size_t n = (size_t)nch * len;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(scatter_chains_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, src,
-                       dst, off, len, nch);
     return hipGetLastError();
 }
 
