@@ -1538,18 +1538,19 @@ void tile16_kernel(LaunchArgs la)
 // are those same fragments (S is symmetric), so only the odd ones are read;
 // the noise is drawn by wavefronts of their own one step ahead (RT = 2 and 4)
 // or, beyond, before the products of u = chi R, where it issues while the
-// products wait for each other.  Beyond RT = 8 the fragments stream from L2
-// (0.5 MB a step at RT = 16) and a workgroup takes one tile: two took twice as
-// long there, and spilled.
+// products wait for each other.  Beyond RT = 8 what does not fit the registers
+// and the LDS streams from L2 (0.38 MB a step at RT = 16; all of it, 0.69 MB,
+// kept the L1 busy for 10.8 of 15.7 thousand cycles: 6.6 us against 5.9), and a
+// workgroup takes one tile: two took twice as long there, and spilled.
 //
 // Wavefront w owns row tile and mode tile w (and w + 8 beyond RT = 8).  Every
 // accumulator sees the products of the other shapes in their order: the
 // states are the same bits.  Time of a step of one workgroup, split-BF16, one
-// tile (before, on the best shape there was): 64 beads 0.92 us (1.61), 128
-// 1.23 (1.40), 160 1.81 (4.8), 256 1.96 (2.25), 300 4.1 (13.1), 384 4.5 (4.5),
-// 440 6.1 (24), 512 6.6 (7.1); FP32 64 beads 1.15 (2.26), 256 3.97 (4.58), 300
-// 7.1 (22.9), 512 14.2 (16.2).  Two tiles take about 1.75 times one.
-constexpr int kLdsSmall = kKinds * 16 * 4 + 4 * 16 * 64 + 12 * 16;  // f32x4
+// tile (before, on the best shape there was): 64 beads 0.87 us (1.61), 128
+// 1.16 (1.40), 160 1.75 (4.8), 256 1.94 (2.25), 300 3.3 (13.1), 384 3.8 (4.5),
+// 440 4.9 (24), 512 5.9 (7.1); FP32 64 beads 1.13 (2.26), 256 3.94 (4.58), 300
+// 6.4 (22.9), 512 13.5 (16.2).  Two tiles take about 1.75 times one.
+constexpr int kLdsSmall = kKinds * 16 * 4 + 4 * 16 * 64 + 12 * 16 + 8 * 5 * 2 * 64;  // f32x4
 
 template <int RT, bool BF16, int NT>
 __device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs &la, int tile0,
@@ -1558,10 +1559,16 @@ __device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs
     constexpr int KS = RT / 2, SF = 2 * RT, NJ = (RT + 7) / 8;
     constexpr bool HOLD = RT <= 8;   // u = chi R fragments in registers
     constexpr bool NW = RT <= 4;     // noise wavefronts
-    constexpr int RL = HOLD ? 1 : 4; // ring of streamed fragments
+    // Beyond RT = 8, of the first own tile: the even fragments in registers (they
+    // serve the coupling too) and the odd ones of the first LQ slabs in LDS.
+    // The others stream through a ring of RL entries: slabs LQ .. of the first
+    // tile (odd), then the second tile's (all four).
+    constexpr int RL = HOLD ? 1 : 3;
+    constexpr int LQ = HOLD ? 0 : (KS < 5 ? KS : 5);
+    constexpr int NS0 = HOLD ? 0 : KS - LQ;  // ring entries of the first tile
     constexpr int BUF = 2 * RT * 64; // f32x4 of one exchange buffer of one tile
-    static_assert(kKinds * RT * 4 + NT * (2 * BUF + (NW ? 4 * RT * 64 : 12 * RT)) <= kLdsSmall,
-                  "LDS of small_tile");
+    constexpr int EXCH = NT * (2 * BUF + (NW ? 4 * RT * 64 : 12 * RT));
+    static_assert(kKinds * RT * 4 + EXCH + 8 * LQ * 2 * 64 <= kLdsSmall, "LDS of small_tile");
     const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool on = wave < RT;                           // owns tiles
@@ -1577,6 +1584,7 @@ __device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs
     // [tile][J][16]
     f32x4 *Rb = lds + kKinds * RT * 4, *Gb = Rb + NT * BUF, *zb = Gb + NT * BUF;
     float *cz = reinterpret_cast<float *>(zb);
+    f32x4 *xl = lds + kKinds * RT * 4 + EXCH + wave * LQ * 2 * 64;  // own odd fragments
 
     const int cl = col / 3, alpha = col - 3 * cl;
     const float xlane = alpha == 0 ? 1.0f : 0.0f;
@@ -1644,13 +1652,18 @@ __device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs
             zslot(t, buf, JN)[64 + lane] = f32x4{z[4], z[5], z[6], z[7]};
         }
     };
-    [[maybe_unused]] f32x4 xu[HOLD ? KS : 1][4], xr[RL][4];
-    auto load_r = [&](int u) {  // ring entry u = ii KS + q
-#pragma unroll
-        for (int f = 0; f < 4; ++f)
-            xr[u % RL][f] = frag((u % KS * RT + wave + 8 * (u / KS)) * 4 + f);
-    };
+    [[maybe_unused]] f32x4 xu[HOLD ? KS : 1][4], xr[RL][4], xe[HOLD ? 1 : KS][2];
     const int nt = wave + 8 < RT ? 2 : 1;  // own tiles
+    auto load_r = [&](int u) {             // ring entry u
+        if (u < NS0) {
+#pragma unroll
+            for (int f = 0; f < 2; ++f) xr[u % RL][f] = frag(((LQ + u) * RT + wave) * 4 + f);
+        } else if (u < NS0 + KS && nt == 2) {
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+                xr[u % RL][f] = frag(((u - NS0) * RT + wave + 8) * 4 + f);
+        }
+    };
     if (on && la.nonlinear) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -1664,6 +1677,13 @@ __device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs
                 for (int f = 0; f < 4; ++f) xu[q][f] = frag((q * RT + wave) * 4 + f);
         } else {
 #pragma unroll
+            for (int q = 0; q < KS; ++q)
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {
+                    xe[q][f] = frag((q * RT + wave) * 4 + 2 + f);
+                    if (q < LQ) xl[(2 * q + f) * 64 + lane] = frag((q * RT + wave) * 4 + f);
+                }
+#pragma unroll
             for (int u = 0; u < RL; ++u) load_r(u);
         }
     }
@@ -1673,15 +1693,15 @@ __device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs
     for (int s = 0; s < la.n_steps; ++s) {
         const int64_t k = step0 + s;
         [[maybe_unused]] float z[NT][NJ][8];
-        // odd coupling rows [hi, lo] (FP32: [K slices 2q, 2q + 1]); the even
-        // ones too where u = chi R is streamed
-        constexpr int CF = HOLD ? 2 : 4;
+        // odd coupling rows [hi, lo] (FP32: [K slices 2q, 2q + 1]), and the
+        // even ones of a second tile
         constexpr int DC = HOLD ? KS : 2;
-        f32x4 xc[DC][CF];
-        auto load_c = [&](int J, int q) {
+        f32x4 xc[DC][HOLD ? 2 : 4];
+        auto load_c = [&](int ii, int q) {
 #pragma unroll
-            for (int f = 0; f < CF; ++f)
-                xc[q % DC][f] = frag((RT + J) * SF + (f >> 1) * RT + 2 * q + (f & 1));
+            for (int f = 0; f < (ii == 0 ? 2 : 4); ++f)
+                xc[q % DC][f] =
+                    frag((RT + wave + 8 * ii) * SF + (f >> 1) * RT + 2 * q + (f & 1));
         };
         if (on) {
             if constexpr (!NW) {
@@ -1718,16 +1738,20 @@ __device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs
                             if (q + 1 < KS) slab4(Rb + t * BUF, q + 1, bn[t], lane);
                         }
                         f32x4 xf[4];
-                        const int u = ii * KS + q;
+                        const int u = ii == 0 ? q - LQ : NS0 + q;  // ring entry
 #pragma unroll
                         for (int f = 0; f < 4; ++f) {
                             if constexpr (HOLD)
                                 xf[f] = xu[q][f];
+                            else if (ii == 0 && f >= 2)
+                                xf[f] = xe[q][f & 1];
+                            else if (ii == 0 && q < LQ)
+                                xf[f] = xl[(2 * q + f) * 64 + lane];
                             else
-                                xf[f] = xr[u % RL][f];
+                                xf[f] = xr[(u < 0 ? 0 : u) % RL][f];
                         }
                         if constexpr (!HOLD) {
-                            if (u + RL < NJ * KS && (u + RL) / KS < nt) load_r(u + RL);
+                            if (u >= 0) load_r(u + RL);
                         }
                         if constexpr (BF16) {
                             // products hi hi, hi lo, lo hi of every tile
@@ -1763,7 +1787,7 @@ __device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs
                 }
                 if (wave < a.jc) {
 #pragma unroll
-                    for (int q = 0; q < DC; ++q) load_c(wave, q);
+                    for (int q = 0; q < DC; ++q) load_c(0, q);
                 }
             }
         }
@@ -1777,7 +1801,7 @@ __device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs
                 const bool couple = la.nonlinear && J < a.jc;
                 if (ii > 0 && couple) {
 #pragma unroll
-                    for (int q = 0; q < DC; ++q) load_c(J, q);
+                    for (int q = 0; q < DC; ++q) load_c(ii, q);
                 }
                 const f32x4 Eo = cf[(kEo * RT + J) * 4 + g], Wo = cf[(kWo * RT + J) * 4 + g];
                 const f32x4 Ee = cf[(kEe * RT + J) * 4 + g], We = cf[(kWe * RT + J) * 4 + g];
@@ -1844,10 +1868,12 @@ __device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs
                         }
 #pragma unroll
                         for (int f = 0; f < 4; ++f) {
-                            if constexpr (HOLD)
-                                xf[f] = f < 2 ? xc[q % DC][f] : xu[q][f];
+                            if (f < 2 || ii > 0)
+                                xf[f] = xc[q % DC][f];
+                            else if constexpr (HOLD)
+                                xf[f] = xu[q][f];
                             else
-                                xf[f] = xc[q % DC][f % CF];
+                                xf[f] = xe[q][f & 1];
                         }
                         if constexpr (BF16) {
 #pragma unroll
@@ -1874,7 +1900,7 @@ __device__ __forceinline__ void small_tile(const BucketArgs &a, const LaunchArgs
                                     }
                         }
                         if constexpr (DC < KS) {
-                            if (q + DC < KS) load_c(J, q + DC);
+                            if (q + DC < KS) load_c(ii, q + DC);
                             __builtin_amdgcn_sched_barrier(0);
                         }
                     }
@@ -2507,8 +2533,8 @@ static double model_us(const FusedBucket &f)
 {
     static const double res[2][4] = {{1.80, 3.51, 5.72, 8.13}, {2.26, 5.2, 8.9, 14.7}};
     static const double str[2][5] = {{10.9, 13.1, 17.6, 24.0, 30.9}, {15.8, 22.9, 31.1, 42.5, 55.2}};
-    static const double one[2][8] = {{0.87, 1.16, 1.75, 1.94, 3.81, 4.38, 5.87, 6.62},
-                                     {1.13, 1.79, 3.26, 3.94, 6.95, 8.05, 12.7, 14.3}};
+    static const double one[2][8] = {{0.87, 1.16, 1.75, 1.94, 3.28, 3.75, 4.86, 5.85},
+                                     {1.13, 1.79, 3.26, 3.94, 6.43, 7.51, 12.1, 13.5}};
     static const double two[2][4] = {{1.43, 1.99, 3.01, 3.43}, {1.99, 3.19, 6.12, 7.40}};
     const int k = f.bf16 ? 0 : 1, i = f.RT / 2 - 1;
     switch (f.split) {
