@@ -1245,20 +1245,22 @@ void split_wide_kernel(LaunchArgs la)
 // each (RT = 8; RT = 6 leaves two wavefronts idle).  For launches of about as
 // many such workgroups as the GPU has compute units: 4096 chains of 256 beads
 // make exactly 256, where tiles of 5 chains are 820 wavefronts for 1024 SIMDs
-// (5.3 against 7.3 us per step; 4.3 against 5.3 at 192 beads).  Shorter chains
+// (4.9 against 7.3 us per step; 4.2 against 5.3 at 192 beads).  Shorter chains
 // leave wavefronts idle and are slower than 5-chain tiles (at RT = 4, with two
 // tiles per workgroup, 4.5 us for 32 chains against 3.5 us for 20).
 //
 // Every wavefront keeps the u = chi R fragments of its row tile in registers
-// for the launch and reads its coupling rows from L2; the amplitudes and the
+// for the launch; the amplitudes and the
 // forces go through LDS as in the split tiles, [K slab][odd hi, odd lo, even
 // hi, even lo][component][lane].  The step is bound by vector issue (noise,
-// forces, splits); the matrix products of one wavefront hide behind the
-// vector work of the other on its SIMD, so the two draw their noise at
-// different times: wavefronts 0..3 before the products of u = chi R,
-// wavefronts 4..7 after their update, for the next step.  Normal 0 of a mode
-// tile (for lane group 3 of the tile before) is exchanged in cz, two buffers
-// by step parity, so two barriers a step do.
+// forces, splits), behind which the matrix products of the other wavefront on
+// the SIMD hide in part: the noise of the next step is drawn after the update,
+// beside the products of the coupled mode tiles (4.94 us a step at 4096 x 256;
+// before the products of u = chi R 5.24, half of the wavefronts so and half so
+// 4.97, between the products 4.97 to 5.08).  Normal 0 of a mode tile (for lane
+// group 3 of the tile before) is exchanged in cz, two buffers by step parity,
+// so two barriers a step do.  Only the odd coupling rows are read (from L2):
+// the even ones are the even fragments of u = chi R.
 //
 // Every accumulator sees the products of the other shapes in their order and
 // every amplitude the same operations: the states are the same bits.
@@ -1276,7 +1278,6 @@ __device__ __forceinline__ void tile16(const BucketArgs &a, const LaunchArgs &la
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int J = wave % RT, c0 = kChains16 * tile0;
     const bool on = wave < RT;  // this wavefront has a row tile and a mode tile
-    const bool early = wave < 4;
     f32x4 *cf = lds;
     {
         const f32x4 *c4 = reinterpret_cast<const f32x4 *>(a.coef);
@@ -1346,12 +1347,11 @@ __device__ __forceinline__ void tile16(const BucketArgs &a, const LaunchArgs &la
 #pragma unroll
             for (int f = 0; f < 4; ++f) xu[q][f] = frag((q * RT + J) * 4 + f);
     }
-    if (on && !early) draw(step0, 0);
+    if (on) draw(step0, 0);
     __syncthreads();
 
     for (int s = 0; s < la.n_steps; ++s) {
         const int64_t k = step0 + s;
-        if (on && early) draw(k, s & 1);
         if (on && la.nonlinear) {
             // ---- u = chi R of the own half-bond rows, component by component
             // in each K slab, the next operands read one component ahead
@@ -1413,15 +1413,15 @@ __device__ __forceinline__ void tile16(const BucketArgs &a, const LaunchArgs &la
                 put(Gb, 2, c, Gm[c]);
             }
         }
-        // coupling rows of the own modes, [odd hi, odd lo, even hi, even lo]
+        // odd coupling rows of the own modes, [hi, lo]; the even ones are the
+        // even fragments of u = chi R (S is symmetric)
         const bool couple = on && la.nonlinear && J < a.jc;
-        f32x4 xc[KS][4];
+        f32x4 xc[KS][2];
         if (couple) {
 #pragma unroll
             for (int q = 0; q < KS; ++q)
 #pragma unroll
-                for (int f = 0; f < 4; ++f)
-                    xc[q][f] = frag((RT + J) * SF + (f >> 1) * RT + 2 * q + (f & 1));
+                for (int f = 0; f < 2; ++f) xc[q][f] = frag((RT + J) * SF + 2 * q + f);
         }
         lds_barrier();  // forces and normals 0 written, amplitudes read
         if (on) {
@@ -1477,11 +1477,11 @@ __device__ __forceinline__ void tile16(const BucketArgs &a, const LaunchArgs &la
                         f32x4 &P = (q & 1) ? ao2 : ao[c];
                         f32x4 &C = (q & 1) ? ce2 : ce;
                         P = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][0]), gph, P);
-                        C = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][2]), gmh, C);
+                        C = mfma_bf16(__builtin_bit_cast(bf16x8, xu[q][2]), gmh, C);
                         P = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][0]), gpl, P);
-                        C = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][2]), gml, C);
+                        C = mfma_bf16(__builtin_bit_cast(bf16x8, xu[q][2]), gml, C);
                         P = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][1]), gph, P);
-                        C = mfma_bf16(__builtin_bit_cast(bf16x8, xc[q][3]), gmh, C);
+                        C = mfma_bf16(__builtin_bit_cast(bf16x8, xu[q][3]), gmh, C);
                     }
                     ao[c] += ao2;
                     ce += ce2;
@@ -1500,7 +1500,7 @@ __device__ __forceinline__ void tile16(const BucketArgs &a, const LaunchArgs &la
                 Re[c] = ae[c];
             }
             if (la.nonlinear) put_state();
-            if (!early && s + 1 < la.n_steps) draw(k + 1, (s + 1) & 1);
+            if (s + 1 < la.n_steps) draw(k + 1, (s + 1) & 1);
         }
         lds_barrier();  // amplitudes written
     }
@@ -2540,7 +2540,7 @@ static double model_us(const FusedBucket &f)
     switch (f.split) {
     case 1: return 1.3 * one[k][i];
     case 2: return 1.1 * one[k][i];
-    case 3: return f.RT == 6 ? 4.6 : 5.36;
+    case 3: return f.RT == 6 ? 4.3 : 4.95;
     case 4: return f.tpw == 2 ? two[k][i] : one[k][i];
     default: return f.resident ? res[k][i] : str[k][i - 3];
     }
