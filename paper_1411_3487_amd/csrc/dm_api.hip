@@ -181,14 +181,16 @@ int observe(dm_ctx *ctx, int accumulate, hipStream_t st, bool captured = false,
             bool from_snapshot = false, int max_wg = 0)
 {
     if (accumulate && !captured) DM_HIP(ctx, dm::fused_set_step(ctx->d_step, ctx->step, st));
+    if (fused_precision(ctx->precision)) {
+        std::vector<dm::FusedObs> list;
+        for (auto b = ctx->buckets.rbegin(); b != ctx->buckets.rend(); ++b)  // longest first
+            list.push_back({&b->fused, b->M, b->d_obs, b->d_m2, b->d_acc, b->d_cm0, b->d_tumble,
+                            b->d_tumble + b->n, b->d_ring, b->d_ccount});
+        DM_HIP(ctx, dm::fused_observe(list, ctx->d_step, ctx->corr_lags, accumulate, st,
+                                      from_snapshot, max_wg));
+        return DM_OK;
+    }
     for (Bucket &b : ctx->buckets) {
-        if (fused_precision(ctx->precision)) {
-            DM_HIP(ctx, dm::fused_observe(b.fused, b.M, b.d_obs, b.d_m2, b.d_acc, b.d_cm0,
-                                          b.d_tumble, b.d_tumble + b.n, ctx->d_step, b.d_ring,
-                                          b.d_ccount, ctx->corr_lags, accumulate, st,
-                                          from_snapshot, max_wg));
-            continue;
-        }
         int rc = bucket_positions(ctx, b, st);
         if (rc) return rc;
         DM_HIP(ctx, dm::launch_chain_obs(b.d_r, b.d_R64, b.d_obs, b.d_m2, b.d_acc, b.d_cm0,

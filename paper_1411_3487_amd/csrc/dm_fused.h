@@ -91,13 +91,18 @@ int fused_items(const FusedBucket &f);
 hipError_t fused_set_step(int64_t *d_step, int64_t value, hipStream_t st);
 hipError_t fused_advance_step(int64_t *d_step, int64_t n, hipStream_t st);
 // Per-chain observables, |R_p|^2 and (accumulate != 0) the FP64 accumulators
-// and tumbling state of the bucket, in the layout of launch_chain_obs, from
-// the fused state directly (positions in FP32 MFMA, sums in FP64).
-// from_snapshot: read the state saved by fused_snapshot instead of the live
-// one; max_wg > 0 caps the grid (each workgroup then loops over tiles).
-hipError_t fused_observe(const FusedBucket &f, int M, double *obs, double *m2, double *acc,
-                         const double *cm0, double *tstate, double *tlast,
-                         const int64_t *d_step, double *ring, double *ccount, int K,
+// and tumbling state of the buckets, in the layout of launch_chain_obs, from
+// the fused states directly (positions in FP32 MFMA, sums in FP64).
+// from_snapshot: read the states saved by fused_snapshot instead of the live
+// ones; max_wg > 0 caps the grid (each workgroup then loops over tiles).
+struct FusedObs {
+    const FusedBucket *f;
+    int M;
+    double *obs, *m2, *acc;
+    const double *cm0;
+    double *tstate, *tlast, *ring, *ccount;
+};
+hipError_t fused_observe(const std::vector<FusedObs> &buckets, const int64_t *d_step, int K,
                          int accumulate, hipStream_t st, bool from_snapshot = false,
                          int max_wg = 0);
 // Copy of the state (d_R, d_R0 -> d_Rs, d_R0s) for observables taken while

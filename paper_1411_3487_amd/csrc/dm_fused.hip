@@ -2013,18 +2013,29 @@ __device__ __forceinline__ size_t state_slot(int j, int alpha, int p, int RT)
     return (((size_t)T * 2 + set) * RT + t) * 256 + (size_t)lane * 4 + (rho % 4);
 }
 
-// Observables of the fused state, one workgroup of 4 wavefronts per tile.  Positions
+// Observables of the fused state, one workgroup of 8 wavefronts per tile.  Positions
 // relative to the centre of mass, r_n - r_cm = sum_{p >= 1} phi_{n,p} R_p
 // (Eq. c1; the internal modes sum to zero over the beads), in the mirror
-// halves of Sec. V.A (the 4 wavefronts share the row tiles): for beads n < H
+// halves of Sec. V.A: for beads n < H
 //   O_n = sum_{p odd} phi_{n,p} R_p,  E_n = sum_{p even} phi_{n,p} R_p,
 //   r_n = E_n + O_n,  r_{M-1-n} = E_n - O_n,
 // as FP32 MFMA products with the tables P (odd: phi_{n,2j+1}; even:
 // phi_{n,2j+2} / sigma_{2j+2}, undoing the scaling of the stored even
 // amplitudes), fragment (I, t, kind) holding rows 16 I + l%16 and K slots
-// 16 t + 4 (l/16) + r.  The positions go to LDS; then 8 lanes per chain
-// reduce bond lengths, end-to-end vector and extent in FP64, and the
-// per-chain outputs and accumulators follow the FP64 path's layout.
+// 16 t + 4 (l/16) + r.  Even wavefronts take the even modes and odd ones the
+// odd modes, so each holds one set of amplitudes; E_n and O_n go to LDS.  Then one wavefront per chain reduces bond
+// lengths, end-to-end vector and extent in FP64, two mirrored bonds per lane
+// and pass, and the per-chain outputs and accumulators follow the FP64
+// path's layout.
+//
+// The kernel is bound by the latency of a tile (about 18 us), of which only
+// a few are in flight on a compute unit: each reads, multiplies once and
+// writes.  So the fragments of P stay two groups ahead of their products,
+// everything that the end adds to (accumulators, tumbling state) is read in
+// one go before the |R_p|^2 and the barrier, and the head of the accumulators
+// is one lane per entry, not a chain of read-modify-writes in one lane.  Odd
+// row stride of the positions: the 16 columns of a store in different banks.
+// 1024 chains of 512 beads: 44 -> 23 us; 4096 of 256: 28 -> 28 us.
 struct ObsArgs {
     const float *R;
     const double *R0;
@@ -2035,175 +2046,279 @@ struct ObsArgs {
     double *tstate, *tlast;
     const int64_t *step;
     double *ring, *ccount;
-    int K, M, n, ntiles, accumulate;
+    int K, M, n, ntiles, accumulate, RT;
 };
 
-// Observables of one tile.  LDS: pos [16][M] floats (positions about the
-// centre of mass, column = 3 chain + component), then msq [5][M] floats
-// (|R_p|^2 of each chain).
+constexpr int kObsWaves = 8;
+
+// LDS of one tile: E, O of the columns (3 chain + component), then |R_p|^2.
+__host__ __device__ inline int obs_lds_floats(int RT)
+{
+    return 2 * 16 * (16 * RT + 1) + kChainsPerTile * 32 * RT;
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 template <int RT>
 __device__ __forceinline__ void obs_tile(const ObsArgs &a, int tile, float *pos)
 {
-    const int M = a.M, H = M / 2;
-    float *msq = pos + 16 * M;
-    const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    constexpr int S = 16 * RT + 1, kMsq = 32 * RT;  // row strides
+    const int M = a.M, H = M / 2, W = acc_width(M);
+    float *posO = pos + 16 * S, *msq = posO + 16 * S;
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // its multiples are not held across the tiles of a workgroup
+    const int col = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int cl = col / 3, alpha = col - 3 * cl;
     const int nvalid = min(kChainsPerTile, a.n - kChainsPerTile * tile);
     const size_t c0 = (size_t)kChainsPerTile * tile;
-    f32x4 Ro[RT], Re[RT];
-    const f32x4 *Rt = reinterpret_cast<const f32x4 *>(a.R) + (size_t)tile * 2 * RT * 64;
+    const int odd = wave & 1;  // this wavefront's set of modes
+    f32x4 Rs[RT];
+    const f32x4 *Rt = reinterpret_cast<const f32x4 *>(a.R) +
+                      ((size_t)tile * 2 + (1 - odd)) * RT * 64;
 #pragma unroll
-    for (int t = 0; t < RT; ++t) {
-        Ro[t] = Rt[(0 * RT + t) * 64 + lane];
-        Re[t] = Rt[(1 * RT + t) * 64 + lane];
+    for (int t = 0; t < RT; ++t) Rs[t] = Rt[t * 64 + lane];
+    // the products, the next few fragments of P in flight behind each group
+    constexpr int kG = 2, kGroups = RT / kG;
+    const f32x4 *P = reinterpret_cast<const f32x4 *>(a.P) + (1 - odd) * 64 + lane;
+    f32x4 pn[kG];
+    int I = wave >> 1;
+    if (I < RT) {
+#pragma unroll
+        for (int i = 0; i < kG; ++i) pn[i] = P[(I * RT + i) * 128];
     }
-    const f32x4 *P = reinterpret_cast<const f32x4 *>(a.P);
-    for (int I = wave; I < RT; I += 4) {
-        f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f}, e = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (; I < RT; I += kObsWaves / 2) {
+        const int In = I + kObsWaves / 2 < RT ? I + kObsWaves / 2 : I;
+        f32x4 x = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < RT; ++t) {
-            const f32x4 po = P[((I * RT + t) * 2) * 64 + lane];
-            const f32x4 pe = P[((I * RT + t) * 2 + 1) * 64 + lane];
+        for (int q = 0; q < kGroups; ++q) {
+            f32x4 p[kG];
+            const f32x4 *next = P + (q + 1 < kGroups ? I * RT + (q + 1) * kG : In * RT) * 128;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                o = mfma_f32(po[r], Ro[t][r], o);
-                e = mfma_f32(pe[r], Re[t][r], e);
+            for (int i = 0; i < kG; ++i) {
+                p[i] = pn[i];
+                pn[i] = next[i * 128];
             }
-        }
+            __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the products
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int nb = 16 * I + 4 * g + r;
-            if (nb < H) {
-                pos[col * M + nb] = e[r] + o[r];
-                pos[col * M + M - 1 - nb] = e[r] - o[r];
-            }
+            for (int i = 0; i < kG; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x = mfma_f32(p[i][r], Rs[q * kG + i][r], x);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        float *y = (odd ? posO : pos) + col * S + 16 * I + 4 * g;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[r] = x[r];
     }
+    // the sums and the state that the end of the tile adds to
+    const bool reducer = wave < nvalid;  // wavefront c reduces chain c
+    const size_t c = c0 + wave;
+    constexpr int kIt = RT / 2;
+    double msum[kIt];
+#pragma unroll
+    for (int it = 0; it < kIt; ++it) {
+        const int p = 64 * it + lane;
+        msum[it] = reducer && a.accumulate && p < M ? a.acc[c * W + DM_NACC_HEAD + p] : 0.0;
+    }
+    double head = 0.0, state = 0.0;  // one entry per lane
+    if (reducer) {
+        const double *q = a.R0 + (size_t)tile * 16 + 3 * wave + lane;  // lanes 0..2
+        if (lane >= 3) q = a.cm0 + 3 * c + (lane - 3);                 // 3..5
+        if (lane == 6) q = a.tstate + c;
+        if (lane == 7) q = a.tlast + c;
+        if (lane < (a.accumulate ? 8 : 3)) state = *q;
+        if (a.accumulate && lane < DM_NACC_HEAD) head = a.acc[c * W + lane];
+    }
+    __builtin_amdgcn_sched_barrier(0);
     // |R_p|^2 of p >= 1, summed over the chain's three component lanes: the
     // mode tiles spread over the wavefronts, staged in LDS
-    for (int t = wave; t < RT; t += 4) {
+#pragma unroll 1
+    for (int t = wave >> 1; t < RT; t += kObsWaves / 2) {
+        const f32x4 R = Rt[t * 64 + lane];
+        double sg[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int j = 16 * t + 4 * g + r;
-            const float vo = Ro[t][r];
-            const float ve = j < H - 1 ? (float)((double)Re[t][r] / a.sig[j]) : 0.0f;
-            const float so = comp_sum(vo * vo, alpha), se = comp_sum(ve * ve, alpha);
-            if (alpha == 0 && col < 15) {
-                const int po = 2 * j + 1, pe = 2 * j + 2;
-                if (po < M) msq[cl * M + po] = so;
-                if (pe < M) msq[cl * M + pe] = se;
-            }
+            sg[r] = j < H - 1 ? a.sig[j] : 1.0;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = 16 * t + 4 * g + r;
+            const int p = odd ? 2 * j + 1 : 2 * j + 2;
+            const float v = (float)((double)R[r] / (odd ? 1.0 : sg[r]));
+            const float s = comp_sum(v * v, alpha);
+            if (alpha == 0 && col < 15 && p < M) msq[cl * kMsq + p] = s;
         }
     }
     __syncthreads();
-    // written out chain by chain, consecutive modes in consecutive threads
-    const int W = acc_width(M);
-    for (int i = threadIdx.x; i < nvalid * M; i += blockDim.x) {
-        const int c = i / M, p = i - c * M;
-        if (p == 0) continue;  // the centre of mass, below
-        const float v = msq[c * M + p];
-        a.m2[(c0 + c) * M + p] = v;
-        if (a.accumulate) a.acc[(c0 + c) * W + DM_NACC_HEAD + p] += v;
+    if (!reducer) return;
+    double r0[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r0[k] = lane_value(state, k);
+    const double m20 = r0[0] * r0[0] + r0[1] * r0[1] + r0[2] * r0[2];
+#pragma unroll
+    for (int it = 0; it < kIt; ++it) {
+        const int p = 64 * it + lane;
+        if (p < M) {
+            const double v = p == 0 ? m20 : (double)msq[wave * kMsq + p];
+            a.m2[c * M + p] = v;
+            if (a.accumulate) a.acc[c * W + DM_NACC_HEAD + p] = msum[it] + v;
+        }
     }
-    // 32 lanes per chain (chains 0..4 in threads 0..159): bond lengths and the
-    // x extent
-    const int c8 = threadIdx.x >> 5, part = threadIdx.x & 31;
-    const bool cv = c8 < nvalid;
-    if (c8 >= kChainsPerTile) return;
-    const float *px = pos + 3 * (cv ? c8 : 0) * M, *py = px + M, *pz = py + M;
+    // bonds (n - 1, n) and their mirror images, n < H, and the middle one
+    const float *pe = pos + 3 * wave * S, *po = posO + 3 * wave * S;
     double ls = 0.0, l2s = 0.0, xmin = 1e300, xmax = -1e300;
-    if (cv) {
-        for (int nb = part; nb < M; nb += 32) {
-            const double x = px[nb];
-            xmin = fmin(xmin, x);
-            xmax = fmax(xmax, x);
-            if (nb >= 1) {
-                const double ux = x - px[nb - 1], uy = (double)py[nb] - py[nb - 1],
-                             uz = (double)pz[nb] - pz[nb - 1];
-                const double q = ux * ux + uy * uy + uz * uz;
-                ls += sqrt(q);
-                l2s += q;
+    for (int nb = lane; nb < H; nb += 64) {
+        double q0 = 0.0, q1 = 0.0, qm = 0.0;
+        const int pv = max(nb - 1, 0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const float e = pe[k * S + nb], o = po[k * S + nb];
+            const float e1 = pe[k * S + pv], o1 = po[k * S + pv];
+            const double lo = e + o, hi = e - o, lo1 = e1 + o1, hi1 = e1 - o1;
+            const double d0 = lo - lo1, d1 = hi1 - hi, dm = hi - lo;
+            q0 += d0 * d0;
+            q1 += d1 * d1;
+            qm += dm * dm;
+            if (k == 0) {
+                xmin = fmin(xmin, fmin(lo, hi));
+                xmax = fmax(xmax, fmax(lo, hi));
             }
+        }
+        if (nb >= 1) {
+            ls += sqrt(q0) + sqrt(q1);
+            l2s += q0 + q1;
+        }
+        if (nb == H - 1) {
+            ls += sqrt(qm);
+            l2s += qm;
         }
     }
 #pragma unroll
-    for (int off = 1; off < 32; off <<= 1) {
+    for (int off = 1; off < 64; off <<= 1) {
         ls += __shfl_xor(ls, off, 64);
         l2s += __shfl_xor(l2s, off, 64);
         xmin = fmin(xmin, __shfl_xor(xmin, off, 64));
         xmax = fmax(xmax, __shfl_xor(xmax, off, 64));
     }
-    if (!cv || part != 0) return;
-    const size_t c = c0 + c8;
-    const double *r0 = a.R0 + (size_t)tile * 16 + 3 * c8;
+    // entry k of the sums goes to lane k
+    double inc = 0.0;
+    auto put = [&](int k, double x) { inc = lane == k ? x : inc; };
     const double rs = 1.0 / sqrt((double)M);
-    double o[DM_NCHAIN_OBS];
-    o[DM_CO_BOND] = ls / (M - 1);
-    const double Lx = (double)px[M - 1] - px[0], Ly = (double)py[M - 1] - py[0],
-                 Lz = (double)pz[M - 1] - pz[0];
-    o[DM_CO_L2] = Lx * Lx + Ly * Ly + Lz * Lz;
-    o[DM_CO_LX] = Lx;
-    o[DM_CO_LX + 1] = Ly;
-    o[DM_CO_LX + 2] = Lz;
-    const int m = M / 2, mid = (M - 1) / 2;
-    const float *pc[3] = {px, py, pz};
+    const double bond = ls / (M - 1), bond2 = l2s / (M - 1);
+    double L[3], um[3], dm[3], cm[3], L2 = 0.0, dm2 = 0.0, dcm2 = 0.0;
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
-        o[DM_CO_CM + k] = r0[k] * rs;
-        o[DM_CO_UMID + k] = (double)pc[k][m] - pc[k][m - 1];
-        o[DM_CO_DMID + k] = pc[k][mid];
+        const float e = pe[k * S], q = po[k * S], em = pe[k * S + H - 1], om = po[k * S + H - 1];
+        L[k] = (double)(e - q) - (double)(e + q);
+        um[k] = (double)(em - om) - (double)(em + om);
+        dm[k] = em + om;
+        cm[k] = r0[k] * rs;
+        const double d = cm[k] - lane_value(state, 3 + k);
+        L2 += L[k] * L[k];
+        dm2 += dm[k] * dm[k];
+        dcm2 += d * d;
     }
-    o[DM_CO_XSPAN] = xmax - xmin;
-    o[DM_CO_BOND2] = l2s / (M - 1);
-    for (int k = 0; k < DM_NCHAIN_OBS; ++k) a.obs[c * DM_NCHAIN_OBS + k] = o[k];
-    const double m20 = r0[0] * r0[0] + r0[1] * r0[1] + r0[2] * r0[2];
-    a.m2[c * M] = m20;
+    if (lane == 0) {
+        double *o = a.obs + c * DM_NCHAIN_OBS;
+        o[DM_CO_BOND] = bond;
+        o[DM_CO_L2] = L2;
+        for (int k = 0; k < 3; ++k) {
+            o[DM_CO_LX + k] = L[k];
+            o[DM_CO_CM + k] = cm[k];
+            o[DM_CO_UMID + k] = um[k];
+            o[DM_CO_DMID + k] = dm[k];
+        }
+        o[DM_CO_XSPAN] = xmax - xmin;
+        o[DM_CO_BOND2] = bond2;
+    }
     if (!a.accumulate) return;
     double *ac = a.acc + c * W;
-    const double dx = o[DM_CO_CM] - a.cm0[3 * c], dy = o[DM_CO_CM + 1] - a.cm0[3 * c + 1],
-                 dz = o[DM_CO_CM + 2] - a.cm0[3 * c + 2];
-    ac[DM_NACC_HEAD] += m20;
-    ac[DM_ACC_NSAMPLES] += 1.0;
-    ac[DM_ACC_BOND] += o[DM_CO_BOND];
-    ac[DM_ACC_BOND2] += o[DM_CO_BOND2];
-    ac[DM_ACC_L2] += o[DM_CO_L2];
-    ac[DM_ACC_MSDCM] += dx * dx + dy * dy + dz * dz;
-    ac[DM_ACC_DMID2] += o[DM_CO_DMID] * o[DM_CO_DMID] + o[DM_CO_DMID + 1] * o[DM_CO_DMID + 1] +
-                        o[DM_CO_DMID + 2] * o[DM_CO_DMID + 2];
-    ac[DM_ACC_XSPAN] += o[DM_CO_XSPAN];
+    put(DM_ACC_NSAMPLES, 1.0);
+    put(DM_ACC_BOND, bond);
+    put(DM_ACC_BOND2, bond2);
+    put(DM_ACC_L2, L2);
+    put(DM_ACC_MSDCM, dcm2);
+    put(DM_ACC_DMID2, dm2);
+    put(DM_ACC_XSPAN, xmax - xmin);
     // tumbling in the flow plane, with hysteresis (as the FP64 path)
-    const double rho = sqrt(Lx * Lx + Ly * Ly);
-    const double s0 = a.tstate[c];
-    const double s1 = Lx > 0.5 * rho ? 1.0 : (Lx < -0.5 * rho ? -1.0 : s0);
-    if (s0 != 0.0 && s1 != s0) {
+    const double ts = lane_value(state, 6), tl = lane_value(state, 7);
+    const double rho = sqrt(L[0] * L[0] + L[1] * L[1]);
+    const double s1 = L[0] > 0.5 * rho ? 1.0 : (L[0] < -0.5 * rho ? -1.0 : ts);
+    if (ts != 0.0 && s1 != ts) {
         const double k = (double)*a.step;
-        ac[DM_ACC_TUMBLES] += 1.0;
-        if (a.tlast[c] > 0.0) {
-            const double tau = k - (a.tlast[c] - 1.0);
-            ac[DM_ACC_TAU] += tau;
-            ac[DM_ACC_TAU2] += tau * tau;
-            ac[DM_ACC_NTAU] += 1.0;
-            ac[DM_NACC_HEAD + M + min(DM_NTUMBLE_BINS - 1, max(0, ilogb(tau)))] += 1.0;
+        put(DM_ACC_TUMBLES, 1.0);
+        if (tl > 0.0) {
+            const double tau = k - (tl - 1.0);
+            put(DM_ACC_TAU, tau);
+            put(DM_ACC_TAU2, tau * tau);
+            put(DM_ACC_NTAU, 1.0);
+            if (lane == 0)
+                ac[DM_NACC_HEAD + M + min(DM_NTUMBLE_BINS - 1, max(0, ilogb(tau)))] += 1.0;
         }
-        a.tlast[c] = k + 1.0;
+        if (lane == 0) a.tlast[c] = k + 1.0;
     }
-    a.tstate[c] = s1;
-    if (a.K > 0) {
-        const double v[9] = {Lx, Ly, Lz, o[DM_CO_UMID], o[DM_CO_UMID + 1], o[DM_CO_UMID + 2],
-                             o[DM_CO_DMID], o[DM_CO_DMID + 1], o[DM_CO_DMID + 2]};
-        corr_update(a.ring + c * ((size_t)9 << (a.K - 1)), a.ccount + c,
-                    ac + DM_NACC_HEAD + M + DM_NTUMBLE_BINS, v, a.K);
+    if (lane < DM_NACC_HEAD) ac[lane] = head + inc;
+    if (lane == 0) {
+        a.tstate[c] = s1;
+        if (a.K > 0) {
+            const double v[9] = {L[0],  L[1],  L[2],  um[0], um[1],
+                                 um[2], dm[0], dm[1], dm[2]};
+            corr_update(a.ring + c * ((size_t)9 << (a.K - 1)), a.ccount + c,
+                        ac + DM_NACC_HEAD + M + DM_NTUMBLE_BINS, v, a.K);
+        }
     }
 }
 
+// The tiles of up to kObsBuckets length buckets, bucket after bucket: those
+// of bucket i end before tile0[i + 1].
+constexpr int kObsBuckets = 8;
+struct ObsList {
+    ObsArgs b[kObsBuckets];
+    int tile0[kObsBuckets + 1];
+    int n;
+};
+
 // One workgroup per tile, or a smaller grid looping over the tiles (to leave
-// most compute units to a fused launch running at the same time).
+// most compute units to a fused launch running at the same time).  RT = 0:
+// buckets of several RT in one launch, whose few workgroups each would leave
+// most of the chip idle one after another (8192 chains of seven lengths, 237
+// or so tiles each: 135 us in seven launches, 52 us in one).  A launch of one RT keeps
+// its own kernel: up to 256 beads 64 registers do and 4 workgroups of a
+// compute unit hide each other's latency, beyond it 128 and 2.
 template <int RT>
-__global__ __launch_bounds__(256) void fused_obs_kernel(ObsArgs a)
+__global__ __launch_bounds__(64 * kObsWaves, RT == 0 || RT > 8 ? 4 : 8)
+void fused_obs_kernel(ObsList l)
 {
-    extern __shared__ float pos[];  // [16][M]
-    for (int tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
-        obs_tile<RT>(a, tile, pos);
+    extern __shared__ float pos[];
+    const int total = l.tile0[l.n];
+    for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+        int i = 0;
+        while (tile >= l.tile0[i + 1]) ++i;
+        const ObsArgs &a = l.b[i];
+        const int t = tile - l.tile0[i];
+        if constexpr (RT != 0) {
+            obs_tile<RT>(a, t, pos);
+        } else {
+            switch (a.RT) {
+            case 2: obs_tile<2>(a, t, pos); break;
+            case 4: obs_tile<4>(a, t, pos); break;
+            case 6: obs_tile<6>(a, t, pos); break;
+            case 8: obs_tile<8>(a, t, pos); break;
+            case 10: obs_tile<10>(a, t, pos); break;
+            case 12: obs_tile<12>(a, t, pos); break;
+            case 14: obs_tile<14>(a, t, pos); break;
+            case 16: obs_tile<16>(a, t, pos); break;
+            default: break;
+            }
+        }
         __syncthreads();  // pos is rewritten for the next tile
     }
 }
@@ -2992,10 +3107,9 @@ hipError_t fused_advance_step(int64_t *d_step, int64_t n, hipStream_t st)
 }
 
 template <int RT>
-static void launch_obs(const ObsArgs &a, int nwg, hipStream_t st)
+static void launch_obs(const ObsList &l, int nwg, size_t lds, hipStream_t st)
 {
-    hipLaunchKernelGGL(fused_obs_kernel<RT>, dim3(nwg), dim3(256),
-                       sizeof(float) * (16 + kChainsPerTile) * (size_t)a.M, st, a);
+    hipLaunchKernelGGL(fused_obs_kernel<RT>, dim3(nwg), dim3(64 * kObsWaves), lds, st, l);
 }
 
 hipError_t fused_snapshot_alloc(FusedBucket &f)
@@ -3020,45 +3134,65 @@ hipError_t fused_snapshot(const FusedBucket &f, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t fused_observe(const FusedBucket &f, int M, double *obs, double *m2, double *acc,
-                         const double *cm0, double *tstate, double *tlast,
-                         const int64_t *d_step, double *ring, double *ccount, int K,
+hipError_t fused_observe(const std::vector<FusedObs> &buckets, const int64_t *d_step, int K,
                          int accumulate, hipStream_t st, bool from_snapshot, int max_wg)
 {
-    if (f.n <= 0) return hipSuccess;
-    if (from_snapshot && (!f.d_Rs || !f.d_R0s)) return hipErrorInvalidValue;
-    ObsArgs a;
-    a.R = from_snapshot ? f.d_Rs : f.d_R;
-    a.R0 = from_snapshot ? f.d_R0s : f.d_R0;
-    a.P = f.d_P;
-    a.sig = f.d_sig;
-    a.obs = obs;
-    a.m2 = m2;
-    a.acc = acc;
-    a.cm0 = cm0;
-    a.tstate = tstate;
-    a.tlast = tlast;
-    a.step = d_step;
-    a.ring = ring;
-    a.ccount = ccount;
-    a.K = K;
-    a.M = M;
-    a.n = f.n;
-    a.ntiles = f.ntiles;
-    a.accumulate = accumulate;
-    const int nwg = max_wg > 0 ? std::min(f.ntiles, max_wg) : f.ntiles;
-    switch (f.RT) {
-    case 2: launch_obs<2>(a, nwg, st); break;
-    case 4: launch_obs<4>(a, nwg, st); break;
-    case 6: launch_obs<6>(a, nwg, st); break;
-    case 8: launch_obs<8>(a, nwg, st); break;
-    case 10: launch_obs<10>(a, nwg, st); break;
-    case 12: launch_obs<12>(a, nwg, st); break;
-    case 14: launch_obs<14>(a, nwg, st); break;
-    case 16: launch_obs<16>(a, nwg, st); break;
-    default: return hipErrorInvalidValue;
+    size_t at = 0;
+    while (at < buckets.size()) {
+        ObsList l;
+        l.n = 0;
+        l.tile0[0] = 0;
+        size_t lds = 0;
+        int RT = -1;  // of all buckets of the launch; 0: several
+        for (; at < buckets.size() && l.n < kObsBuckets; ++at) {
+            const FusedObs &o = buckets[at];
+            const FusedBucket &f = *o.f;
+            if (f.n <= 0) continue;
+            if (from_snapshot && (!f.d_Rs || !f.d_R0s)) return hipErrorInvalidValue;
+            if (f.RT < 2 || f.RT > 16 || f.RT % 2) return hipErrorInvalidValue;
+            ObsArgs &a = l.b[l.n];
+            a.R = from_snapshot ? f.d_Rs : f.d_R;
+            a.R0 = from_snapshot ? f.d_R0s : f.d_R0;
+            a.P = f.d_P;
+            a.sig = f.d_sig;
+            a.obs = o.obs;
+            a.m2 = o.m2;
+            a.acc = o.acc;
+            a.cm0 = o.cm0;
+            a.tstate = o.tstate;
+            a.tlast = o.tlast;
+            a.step = d_step;
+            a.ring = o.ring;
+            a.ccount = o.ccount;
+            a.K = K;
+            a.M = o.M;
+            a.n = f.n;
+            a.ntiles = f.ntiles;
+            a.accumulate = accumulate;
+            a.RT = f.RT;
+            l.tile0[l.n + 1] = l.tile0[l.n] + f.ntiles;
+            ++l.n;
+            lds = std::max(lds, sizeof(float) * obs_lds_floats(f.RT));
+            RT = RT < 0 || RT == f.RT ? f.RT : 0;
+        }
+        if (l.n == 0) break;
+        const int total = l.tile0[l.n];
+        const int nwg = max_wg > 0 ? std::min(total, max_wg) : total;
+        switch (RT) {
+        case 2: launch_obs<2>(l, nwg, lds, st); break;
+        case 4: launch_obs<4>(l, nwg, lds, st); break;
+        case 6: launch_obs<6>(l, nwg, lds, st); break;
+        case 8: launch_obs<8>(l, nwg, lds, st); break;
+        case 10: launch_obs<10>(l, nwg, lds, st); break;
+        case 12: launch_obs<12>(l, nwg, lds, st); break;
+        case 14: launch_obs<14>(l, nwg, lds, st); break;
+        case 16: launch_obs<16>(l, nwg, lds, st); break;
+        default: launch_obs<0>(l, nwg, lds, st); break;
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 hipError_t fused_check_finite(const FusedBucket &f, int M, int n, int *flag, hipStream_t st)
