@@ -261,9 +261,10 @@ int dm_step_euler(dm_ctx *ctx, int64_t n_steps, double dtau);
    u' = u and is repeated until it converges: at most iters times, and with
    tol > 0 it stops after the first cycle that changes no component of any
    u'_n by more than tol (tol = 0: exactly iters cycles; 8 cycles hold the
-   bonds at unit length to ~1e-12 per step at dt_bar = 1e-3).  FP64: one
-   wavefront per chain with the chain in registers up to M = 64 and in LDS
-   up to M = 341 (tensions by cyclic reduction), one thread per chain beyond
+   bonds at unit length to ~1e-12 per step at dt_bar = 1e-3).  FP64: the
+   chain in registers on 16, 32 or 64 lanes (4 bonds each) up to M = 256, one
+   wavefront per chain in LDS up to M = 341 (tensions by cyclic reduction in
+   both), one thread per chain beyond
    (Thomas sweep, global scratch allocated on first use); noise tag 3
    (index = bead).  midpoint != 0: forces and tensions at the midpoint
    bonds u^m_n as above (Eq. y14, the time-symmetric form); midpoint == 0:
