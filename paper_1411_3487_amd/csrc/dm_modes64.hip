@@ -321,18 +321,23 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
                     // rows and columns of padding have u = 0: a small number
                     // under their root (a true bond of length 0 gives NaN)
                     const double pad = valid && 16 * I + 4 * g + r < H ? 0.0 : 1e-300;
-                    double up[NT], um[NT], qp = pad, qm = pad;
+                    // |u|^2 = (x^2 + y^2) + z^2 with rounded squares in either
+                    // tile: a chain's bits do not depend on its tile
+                    double up[NT], um[NT], vp[NT], vm[NT], qp, qm;
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
                         up[t] = so[t][r] + se[t][r];
                         um[t] = so[t][r] - se[t][r];
-                        qp = fma64(up[t], up[t], qp);
-                        qm = fma64(um[t], um[t], qm);
+                        vp[t] = fma64(up[t], up[t], pad);
+                        vm[t] = fma64(um[t], um[t], pad);
                     }
                     if constexpr (NT == 1) {
-                        qp = chain_sum(qp, alpha);
-                        qm = chain_sum(qm, alpha);
+                        qp = chain_sum(vp[0], alpha);
+                        qm = chain_sum(vm[0], alpha);
                         if (!valid) qp = qm = 1.0;
+                    } else {
+                        qp = (vp[0] + vp[1]) + vp[2];
+                        qm = (vm[0] + vm[1]) + vm[2];
                     }
                     const double fp = rsqrt64(qp) - a.lin, fm = rsqrt64(qm) - a.lin;
 #pragma unroll
