@@ -376,8 +376,10 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         if constexpr (NT == 1) {
+                            // (selected, not scaled by 0: the lane after a
+                            // chain's z is the next chain's x, which may be NaN)
                             const double y = dpp64<kShl1>(R[ii][par][0][r]);
-                            R[ii][par][0][r] = fma64(alpha == 0 ? a.gdt : 0.0, y, R[ii][par][0][r]);
+                            R[ii][par][0][r] = fma64(a.gdt, alpha == 0 ? y : 0.0, R[ii][par][0][r]);
                         } else {
                             R[ii][par][0][r] = fma64(a.gdt, R[ii][par][1][r], R[ii][par][0][r]);
                         }
@@ -447,10 +449,12 @@ __global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
                 const double z0 = NOISE ? zb[(s & 1) * zs + lane] : cz[t * (RT + 1) * 64 + lane];
                 v[t] = fma64(W0, z0, r0[16 * t + lane]);
             }
-            if constexpr (NT == 1)
-                v[0] = fma64(alpha == 0 ? a.gdt : 0.0, r0[lane < 15 ? lane + 1 : 15], v[0]);
-            else
+            if constexpr (NT == 1) {
+                const double y = r0[lane < 15 ? lane + 1 : 15];
+                v[0] = fma64(a.gdt, alpha == 0 ? y : 0.0, v[0]);
+            } else {
                 v[0] = fma64(a.gdt, r0[16 + lane], v[0]);
+            }
 #pragma unroll
             for (int t = 0; t < NT; ++t) r0[16 * t + lane] = v[t];
         }
