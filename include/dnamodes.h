@@ -229,7 +229,9 @@ int dm_init_chains(dm_ctx **out, int32_t n_chains, const int32_t *beads,
    tables of Eqs. (c8), (c9), (e9), (d3), (d6), (f2) in FP64 on the host for
    every chain length and uploads them.  May be called again to change
    parameters.  Errors: DM_EINVAL for nu outside [0, 1/2) (stability of
-   Eq. a2), T* <= 0, dt <= 0, or a chain length missing from lengths[]. */
+   Eq. a2), T* <= 0, dt <= 0, or a chain length missing from lengths[]; the
+   parameters before it then stay in force.  After DM_ENOMEM or DM_EHIP there
+   are none: dm_step_* return DM_ESTATE until a call succeeds. */
 int dm_set_params(dm_ctx *ctx, const dm_params *p);
 
 /* Advance every chain by n_steps mode steps (Sec. IV, Eqs. e10, d3, d6, f2):

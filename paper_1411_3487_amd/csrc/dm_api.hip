@@ -701,6 +701,9 @@ int dm_set_params(dm_ctx *ctx, const dm_params *p)
         int rc = config_state(ctx, nu);
         if (rc) return rc;
     }
+    // from here on a failure leaves tables, rings and plan of different
+    // parameters: nothing is stepped with them
+    ctx->have_params = false;
     for (size_t i = 0; i < ctx->buckets.size(); ++i) {
         Bucket &b = ctx->buckets[i];
         dm::ModeCoefs mc;
@@ -778,7 +781,7 @@ int dm_set_params(dm_ctx *ctx, const dm_params *p)
 int dm_step_modes(dm_ctx *ctx, int64_t n_steps)
 {
     if (!ctx) return DM_EINVAL;
-    if (!ctx->have_params) return fail(ctx, DM_ESTATE, "dm_set_params has not been called");
+    if (!ctx->have_params) return fail(ctx, DM_ESTATE, "no parameters: dm_set_params has not been called, or failed");
     if (n_steps < 0) return fail(ctx, DM_EINVAL, "n_steps must be >= 0");
     int64_t done = 0;
     const bool fused = fused_precision(ctx->precision);
@@ -852,7 +855,7 @@ int dm_step_modes(dm_ctx *ctx, int64_t n_steps)
 int dm_step_euler(dm_ctx *ctx, int64_t n_steps, double dtau)
 {
     if (!ctx) return DM_EINVAL;
-    if (!ctx->have_params) return fail(ctx, DM_ESTATE, "dm_set_params has not been called");
+    if (!ctx->have_params) return fail(ctx, DM_ESTATE, "no parameters: dm_set_params has not been called, or failed");
     if (!(dtau > 0.0) || !std::isfinite(dtau)) return fail(ctx, DM_EINVAL, "dtau must be > 0");
     if (n_steps < 0 || n_steps > (1 << 30)) return fail(ctx, DM_EINVAL, "bad n_steps");
     if (n_steps == 0) return DM_OK;
@@ -907,7 +910,7 @@ int dm_step_wlc(dm_ctx *ctx, int64_t n_steps, double dt_bar, double T_bar, int32
 int dm_step_mc(dm_ctx *ctx, int64_t n_sweeps, double step_scale, int64_t *accepted)
 {
     if (!ctx) return DM_EINVAL;
-    if (!ctx->have_params) return fail(ctx, DM_ESTATE, "dm_set_params has not been called");
+    if (!ctx->have_params) return fail(ctx, DM_ESTATE, "no parameters: dm_set_params has not been called, or failed");
     if (n_sweeps < 0 || n_sweeps > (1 << 30)) return fail(ctx, DM_EINVAL, "bad n_sweeps");
     if (!(step_scale >= 0.0) || !std::isfinite(step_scale))
         return fail(ctx, DM_EINVAL, "step_scale must be finite and >= 0");

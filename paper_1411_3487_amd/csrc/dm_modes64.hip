@@ -730,7 +730,10 @@ hipError_t modes64_plan(Modes64Plan &p, const std::vector<Modes64Args> &bs, int 
                 e = hipStreamSynchronize(st);  // the host vectors die here
         }
         p.groups.push_back(g);
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess) {  // no launch of a part of the buckets
+            modes64_plan_free(p);
+            return e;
+        }
     }
     return hipSuccess;
 }
