@@ -52,7 +52,10 @@ __global__ __launch_bounds__(256) void gemm_f64_any_kernel(const double *__restr
     __shared__ double Xs[2][kAnyB][kAnyK + 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wi = 16 * (wave >> 1), wj = 16 * (wave & 1);
-    const int i0 = blockIdx.x * kAnyB, c0 = blockIdx.y * kAnyB;
+    // row tiles fastest, in one grid dimension: the second one ends at 65536
+    // workgroups, which 699051 chains exceed
+    const int nrow = (M + kAnyB - 1) / kAnyB;
+    const int i0 = (int)(blockIdx.x % nrow) * kAnyB, c0 = (int)(blockIdx.x / nrow) * kAnyB;
     const int lk = tid & 31, lr = tid >> 5;  // rows lr, lr + 8, + 16, + 24
     double ra[4], rx[4];
     auto load = [&](int k0) {
@@ -1320,7 +1323,7 @@ hipError_t launch_gemm_f64(const double *A, const double *X, double *Y, int M, i
                                M, ncol);
         }
     } else {
-        const dim3 g((M + kAnyB - 1) / kAnyB, (ncol + kAnyB - 1) / kAnyB);
+        const dim3 g((unsigned)((M + kAnyB - 1) / kAnyB) * ((ncol + kAnyB - 1) / kAnyB));
         hipLaunchKernelGGL(gemm_f64_any_kernel, g, dim3(256), 0, st, A, X, Y, off, M, ncol);
     }
     return hipGetLastError();
