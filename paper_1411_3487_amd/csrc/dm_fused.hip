@@ -2640,24 +2640,30 @@ static BucketArgs bucket_args(const FusedBucket &f)
 }
 
 // Time of one workgroup-step in microseconds when nothing was measured on the
-// live bucket: as measured on one MI355X, by row tiles RT = 2, 4, ... 16 and
-// precision (split-BF16, FP32).  It orders the items and picks the untimed
-// shapes; the 4- and 8-wavefront split tiles, which only table_mode and the
-// autotuner take, are estimated from the small-launch kernel's.
+// live bucket: as measured on one MI355X in launches of 100 and 500 steps (the
+// difference, without the launch itself) that fill the compute units, by row
+// tiles RT = 2, 4, ... 16 and precision (split-BF16, FP32).  It orders the
+// items and picks the untimed shapes; the 4- and 8-wavefront split tiles,
+// which only table_mode takes, are estimated from the small-launch kernel's.
+// With resident tables a wavefront does all its coupled mode tiles one after
+// another, so their number JC counts (the first figure and the second per
+// tile); the other shapes divide them among the wavefronts.
 static double model_us(const FusedBucket &f)
 {
-    static const double res[2][4] = {{1.80, 3.51, 5.72, 8.13}, {2.26, 5.2, 8.9, 14.7}};
+    static const double res[2][4][2] = {{{1.41, 0.145}, {2.87, 0.20}, {4.50, 0.24}, {6.30, 0.28}},
+                                        {{1.68, 0.33}, {4.15, 0.49}, {7.25, 0.74}, {11.6, 0.95}}};
     static const double str[2][5] = {{10.9, 13.1, 17.6, 24.0, 30.9}, {15.8, 22.9, 31.1, 42.5, 55.2}};
-    static const double one[2][8] = {{0.87, 1.16, 1.75, 1.94, 3.28, 3.75, 4.86, 5.85},
-                                     {1.13, 1.79, 3.26, 3.94, 6.43, 7.51, 12.1, 13.5}};
-    static const double two[2][4] = {{1.43, 1.99, 3.01, 3.43}, {1.99, 3.19, 6.12, 7.40}};
+    static const double one[2][8] = {{0.82, 1.18, 1.80, 2.05, 3.28, 3.75, 4.86, 5.85},
+                                     {1.07, 1.78, 3.28, 3.98, 6.43, 7.51, 12.1, 13.5}};
+    static const double two[2][4] = {{1.46, 2.05, 3.12, 3.65}, {1.94, 3.28, 5.95, 7.15}};
     const int k = f.bf16 ? 0 : 1, i = f.RT / 2 - 1;
     switch (f.split) {
     case 1: return 1.3 * one[k][i];
     case 2: return 1.1 * one[k][i];
-    case 3: return f.RT == 6 ? 4.3 : 4.95;
+    case 3: return f.RT == 6 ? 4.1 : 4.95;
     case 4: return f.tpw == 2 ? two[k][i] : one[k][i];
-    default: return f.resident ? res[k][i] : str[k][i - 3];
+    // (the other shapes' figures are for JC >= 1 as well)
+    default: return f.resident ? res[k][i][0] + res[k][i][1] * std::max(1, f.JC) : str[k][i - 3];
     }
 }
 
@@ -3041,6 +3047,7 @@ void fused_default_shapes(const std::vector<FusedBucket *> &bs, int ncu)
             f.bf16 = b->bf16;
             f.n = b->n;
             f.ntiles = b->ntiles;
+            f.JC = b->JC;
             f.resident = b->resident;
             f.tpw = b->tpw;
             fused_force_shape(f, kModes[m][0], kModes[m][1]);
