@@ -828,11 +828,15 @@ __host__ __device__ inline size_t wlc_lds_doubles(int M)
     return 9 * (N + 2) + 6 * (N + 1) + 8 * N + (N + 2);
 }
 
-__global__ __launch_bounds__(64) void wlc_wave_kernel(double *__restrict__ pos,
-                                                      const int32_t *__restrict__ ids, int M,
-                                                      double T_bar, double dt, int iters,
-                                                      double tol, int midpoint, uint64_t seed,
-                                                      int64_t step0, int n_steps)
+// Registers for at most 4 wavefronts a SIMD: the LDS (49 KB at 257 beads, the
+// shortest) lets no more than 3 chains onto a compute unit, and with the
+// compiler's own choice of 5 (93 registers for 113) fewer LDS reads are in
+// flight: 1024 chains of 257 beads 1198 us for 4 steps of 8 cycles, 1084 so; of
+// 341 beads 1797 and 1621.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 4)))
+void wlc_wave_kernel(double *__restrict__ pos, const int32_t *__restrict__ ids, int M,
+                     double T_bar, double dt, int iters, double tol, int midpoint, uint64_t seed,
+                     int64_t step0, int n_steps)
 {
     extern __shared__ double lds[];
     const int c = blockIdx.x, t = threadIdx.x;
