@@ -163,11 +163,14 @@ typedef struct {
                                 mode steps (0 = never) */
     int32_t check_finite;    /* 1: after each dm_step_* call check the state
                                 for NaN/Inf and return DM_ENONFINITE */
-    int32_t autotune;        /* fused paths, 1: dm_set_params times every tile
-                                shape of every length bucket on a scratch
-                                copy of the state and keeps the combination
-                                with the shortest schedule (see
-                                dm_get_tiling); 0: fixed shapes */
+    int32_t autotune;        /* fused paths, 1: dm_set_params times the tile
+                                shapes of every length bucket on a scratch
+                                copy of the state (resident tables with 4
+                                tiles per workgroup, streamed tables, tiles
+                                of 16 chains and small-launch tiles; not the
+                                split tiles) and keeps the combination with
+                                the shortest schedule (see dm_get_tiling);
+                                0: by modelled times, see table_mode */
     int32_t use_graphs;      /* sample_every > 0 (at most 256 on DM_FP64 with
                                 chains beyond 513 beads), 1: whole sampling
                                 blocks (the launches of the steps, the step

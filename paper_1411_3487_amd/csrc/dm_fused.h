@@ -69,8 +69,10 @@ void fused_plan_free(FusedPlan &p);
 // replayed graphs), else step0.
 hipError_t fused_launch(const FusedPlan &p, uint64_t seed, int64_t step0, const int64_t *d_step,
                         int n_steps, int nonlinear, hipStream_t st);
-// Time every tile shape of every bucket on a scratch copy of its state and
-// keep the combination with the shortest list-schedule makespan.  One line
+// Time the tile shapes that can win (resident tables with 4 tiles a workgroup,
+// streamed, 16-chain and small-launch tiles) of every bucket on a scratch copy
+// of its state and keep the combination with the shortest list-schedule
+// makespan.  One line
 // per candidate goes to report.
 hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int steps,
                           hipStream_t st, std::string &report);

@@ -2850,7 +2850,7 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
         return e;
     if (steps < 1) steps = 64;
     struct Cand {
-        int resident, tpw, split;
+        int resident, tpw, split;  // split: 0, 3 (16-chain tiles) or 4 (small launches)
         double us;  // per workgroup-step
     };
     std::vector<std::vector<Cand>> cands(bs.size());
@@ -2915,14 +2915,14 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
     (void)hipEventDestroy(e1);
     if (e != hipSuccess) return e;
     // choose one shape per bucket: exhaustive over small products, otherwise
-    // each bucket's cheapest shape per tile
+    // by single changes from several starts
     size_t combos = 1;
     for (auto &l : cands) combos = std::min<size_t>(combos * std::max<size_t>(1, l.size()), 1 << 20);
     std::vector<int> pick(bs.size(), 0), cur(bs.size(), 0);
-    // the 8-wavefront split tiles and the 16-chain tiles run in kernels of
-    // their own after the others: the makespans add
+    // the 16-chain tiles and the small-launch tiles run in kernels of their
+    // own after the others: the makespans add
     auto evaluate = [&](const std::vector<int> &sel) {
-        std::vector<double> cost[4];
+        std::vector<double> cost[3];
         for (size_t b = 0; b < bs.size(); ++b) {
             const Cand &c = cands[b][sel[b]];
             FusedBucket f;  // the shape alone
@@ -2931,7 +2931,7 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
             f.split = c.split;
             f.tpw = c.tpw;
             const int ni = fused_items(f);
-            std::vector<double> &v = cost[std::max(0, c.split - 1)];
+            std::vector<double> &v = cost[std::max(0, c.split - 2)];
             v.insert(v.end(), (size_t)ni, c.us);
         }
         double sum = 0.0;
@@ -2960,7 +2960,7 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
         // and of each kernel where the bucket has one there), change one
         // bucket at a time while the makespan shrinks
         double best_m = 1e300;
-        for (int kernel = -1; kernel <= 4; ++kernel) {
+        for (int kernel : {-1, 0, 3, 4}) {
             std::vector<int> start(bs.size(), 0);
             for (size_t b = 0; b < bs.size(); ++b) {
                 double best = 1e300;
@@ -3011,13 +3011,10 @@ hipError_t fused_autotune(std::vector<FusedBucket *> &bs, uint64_t seed, int ste
             const Cand &ck = cands[b][k];
             const char *shape = ck.split == 4   ? "small"
                                 : ck.split == 3 ? "tile16"
-                                : ck.split == 2 ? "split8"
-                                : ck.split    ? "split"
-                                : ck.resident ? "resident"
-                                              : "streamed";
+                                : ck.resident   ? "resident"
+                                                : "streamed";
             snprintf(line, sizeof line, "RT=%d %s tpw=%d: %.2f us/step%s\n", f.RT, shape, ck.tpw,
-                     ck.us,
-                     (int)k == pick[b] ? "  <- chosen" : "");
+                     ck.us, (int)k == pick[b] ? "  <- chosen" : "");
             report += line;
         }
     }
