@@ -17,7 +17,10 @@
 // What bounds it: FP64 matrix products and vector work share the FP64 units
 // of a SIMD (78.6 TFLOP/s either way), so a step costs the products of u =
 // chi R (3 M^2 flops per chain), those of the coupled mode tiles and the
-// noise in series, about 9 + 5 + 5 us of a step at 4096 chains of 256 beads.
+// noise in series.  At 4096 chains of 256 beads and dtau = 100 (4 of 8 mode
+// tiles coupled) a step takes 23.6 us: noise and update 5.1, measured alone,
+// the products 10.2 + 5.1 at that rate, and 3.2 for bond forces, operand reads
+// and barriers.
 //
 // Tiles.  The columns of every product are (chain, component) pairs, 16 to a
 // v_mfma_f64_16x16x4_f64.
@@ -198,8 +201,9 @@ __device__ __forceinline__ void lds_barrier()
 // 0: streamed, the first two pairs of a product in flight across the barrier
 // before it).
 // ODD: some chain's last mode needs the block beyond its tiles.
-template <int NT, int P, int NU, bool NOISE, bool ODD, int QH>
-__global__ __launch_bounds__(64 * P) void modes64_kernel(Launch64 la)
+// LEAN: 128 registers, for two workgroups of 8 wavefronts on a compute unit.
+template <int NT, int P, int NU, bool NOISE, bool ODD, int QH, bool LEAN = false>
+__global__ __launch_bounds__(64 * P, LEAN ? 4 : 1) void modes64_kernel(Launch64 la)
 {
     static_assert(!NOISE || (NT == 1 && NU == 1), "noise wavefronts: one small tile");
     extern __shared__ double lds[];
@@ -539,12 +543,21 @@ __global__ __launch_bounds__(256) void modes64_table_kernel(double *__restrict__
 
 // Kernel shapes, and the smallest that holds a chain length at NT = 1 (with
 // noise wavefronts where the launch leaves compute units to spare).
-enum { kS1n2, kS1n4, kS1x2, kS1x4, kS1x8, kS1x8b, kS3x2, kS3x4, kS3x8, kShapes };
+enum { kS1n2, kS1n4, kS1x2, kS1x4, kS1x8, kS1x8b, kS1x8l, kS3x2, kS3x4, kS3x8, kShapes };
 int small_shape(int M, bool noise)
 {
     const int RT = half_tiles(M);
     if (noise && RT <= 4) return RT <= 2 ? kS1n2 : kS1n4;
     return RT <= 2 ? kS1x2 : RT <= 4 ? kS1x4 : RT <= 8 ? kS1x8 : kS1x8b;
+}
+// 5-chain tiles of 130 to 256 beads (of odd lengths with their last mode inside
+// the tiles) share a compute unit in pairs where a launch has more tiles than
+// units: 1285 to 2560 chains of 160 beads 11.2 to 12.0 us a step against 14.0 to
+// 14.6, of 256 beads 21.4 to 22.8 against 23.1 to 24.0.  A tile with a unit to
+// itself is 3 to 4 % faster with the registers it likes (7.1 against 7.4).
+int paired_shape(int shape, bool odd, int nitems, int ncu)
+{
+    return shape == kS1x8 && !odd && nitems > ncu ? kS1x8l : shape;
 }
 constexpr int kLargeMaxM = 256;  // RT <= 8: one row tile per wavefront
 
@@ -567,8 +580,8 @@ int large_shape(int M)
 }
 
 // 16-chain tiles where their rounds over the compute units take less time.
-// Above 4 row tiles a workgroup of either shape fills a compute unit and a
-// 16-chain one takes the time of about 2.6 5-chain ones (it reads each table
+// Above 4 row tiles a 16-chain workgroup fills a compute unit and takes the
+// time of about 2.6 5-chain ones one after another (it reads each table
 // fragment once for 48 columns).  Up to 4, several 5-chain workgroups share a
 // compute unit, so their time grows with the chains (microseconds per step
 // and 1000 chains), and a 16-chain workgroup's is its own (two share one at
@@ -591,9 +604,9 @@ hipError_t launch_shape(int shape, bool odd, size_t lds, int nitems, const Launc
 {
     if (nitems <= 0 || la.n_steps <= 0) return hipSuccess;
     switch (shape + (odd ? kShapes : 0)) {
-#define DM_M64(SHAPE, NT, P, NU, NOISE, ODD, QH)                                            \
+#define DM_M64(SHAPE, NT, P, NU, ...)                                                      \
     case SHAPE:                                                                            \
-        hipLaunchKernelGGL((modes64_kernel<NT, P, NU, NOISE, ODD, QH>), dim3(nitems),          \
+        hipLaunchKernelGGL((modes64_kernel<NT, P, NU, __VA_ARGS__>), dim3(nitems),         \
                            dim3(64 * P), lds, st, la);                                     \
         break
         DM_M64(kS1n2, 1, 8, 1, true, false, 4);
@@ -602,6 +615,7 @@ hipError_t launch_shape(int shape, bool odd, size_t lds, int nitems, const Launc
         DM_M64(kS1x4, 1, 4, 1, false, false, 0);
         DM_M64(kS1x8, 1, 8, 1, false, false, 0);
         DM_M64(kS1x8b, 1, 8, 2, false, false, 0);
+        DM_M64(kS1x8l, 1, 8, 1, false, false, 0, true);
         DM_M64(kS3x2, 3, 2, 1, false, false, 0);
         DM_M64(kS3x4, 3, 4, 1, false, false, 0);
         DM_M64(kS3x8, 3, 8, 1, false, false, 0);
@@ -717,6 +731,7 @@ hipError_t modes64_plan(Modes64Plan &p, const std::vector<Modes64Args> &bs, int 
             g.odd = g.odd || beyond_tiles(bs[b].M);
         }
         g.nitems = (int)items.size();
+        g.shape = paired_shape(s, g.odd, g.nitems, ncu);
         g.single = ba.size() == 1;
         g.one = ba[0];
         hipError_t e = hipSuccess;
@@ -755,13 +770,13 @@ hipError_t modes64_launch(const Modes64Plan &p, uint64_t seed, int64_t step0,
 hipError_t modes64_launch_one(const Modes64Args &a, int ncu, uint64_t seed, int64_t step0,
                               int n_steps, int nonlinear, hipStream_t st)
 {
-    const int shape = large_tiles_pay(a.M, a.n, ncu)
-                          ? large_shape(a.M)
-                          : small_shape(a.M, a.n <= kSmallTile * ncu);
+    int shape = large_tiles_pay(a.M, a.n, ncu) ? large_shape(a.M)
+                                               : small_shape(a.M, a.n <= kSmallTile * ncu);
+    const int nitems = (a.n + tile_chains(shape) - 1) / tile_chains(shape);
+    shape = paired_shape(shape, beyond_tiles(a.M), nitems, ncu);
     Launch64 la = launch_args(seed, step0, nullptr, n_steps, nonlinear);
     la.one = a;
-    return launch_shape(shape, beyond_tiles(a.M), lds_bytes(shape, a.M),
-                        (a.n + tile_chains(shape) - 1) / tile_chains(shape), la, st);
+    return launch_shape(shape, beyond_tiles(a.M), lds_bytes(shape, a.M), nitems, la, st);
 }
 
 }  // namespace dm
