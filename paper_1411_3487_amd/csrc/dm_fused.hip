@@ -720,6 +720,7 @@ __device__ __forceinline__ void fused_tiles(const BucketArgs &a, const LaunchArg
 // ---- Split tile: one tile of 5 chains per workgroup, its work divided
 // among P = 4 (or 8) wavefronts, for launches with fewer tiles than the GPU
 // has SIMDs (with one wavefront per tile, 1024 chains make 205 wavefronts).
+// Only table_mode picks it: the small-launch tiles below are faster.
 // Wavefront w owns the mode tiles J = w, w + P, ... (their amplitudes, noise
 // and update) and the half-bond row tiles I = w, w + P, ... (their rows of
 // u = chi R and their bond forces); the round-robin spreads the few coupled
@@ -1242,7 +1243,8 @@ void split_wide_kernel(LaunchArgs la)
 // ---- Tiles of 16 chains: one column tile of 16 chains per component, so a
 // lane holds x, y and z of a bond and bond lengths need no lane moves; 8
 // wavefronts per workgroup, two per SIMD, one half-bond row tile and mode tile
-// each (RT = 8; RT = 6 leaves two wavefronts idle).  For launches of about as
+// each (RT = 8, 194 to 256 beads; RT = 6, 130 to 192, leaves two wavefronts
+// idle).  For launches of about as
 // many such workgroups as the GPU has compute units: 4096 chains of 256 beads
 // make exactly 256, where tiles of 5 chains are 820 wavefronts for 1024 SIMDs
 // (4.9 against 7.3 us per step; 4.2 against 5.3 at 192 beads).  Shorter chains
@@ -2290,9 +2292,10 @@ struct ObsList {
 // most compute units to a fused launch running at the same time).  RT = 0:
 // buckets of several RT in one launch, whose few workgroups each would leave
 // most of the chip idle one after another (8192 chains of seven lengths, 237
-// or so tiles each: 135 us in seven launches, 52 us in one).  A launch of one RT keeps
-// its own kernel: up to 256 beads 64 registers do and 4 workgroups of a
-// compute unit hide each other's latency, beyond it 128 and 2.
+// or so tiles each: 135 us in seven launches, 52 us in one).  A launch of one RT
+// keeps its own kernel: up to 256 beads in 64 registers (2 spilled at RT = 6
+// and 7 at RT = 8), so that up to 4 workgroups of a compute unit hide each
+// other's latency, beyond it in 128 for 2.
 template <int RT>
 __global__ __launch_bounds__(64 * kObsWaves, RT == 0 || RT > 8 ? 4 : 8)
 void fused_obs_kernel(ObsList l)

@@ -32,7 +32,9 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // one of two LDS buffers.  Small tiles, because lengths that are no multiple
 // of 16 come mostly in small launches: 140 chains of 257 beads make 126
 // workgroups, where 64 x 64 tiles without a pipeline made 35 and took 32 us (7
-// us now).
+// us now).  Full launches gain as well, by the pipeline: a call that reads the
+// positions of 4000 chains of 257, 513 or 1025 beads takes 74, 196 and 691 us
+// (102, 304 and 1038 with those tiles); of 16000 chains of 33 beads 31 (38).
 // --------------------------------------------------------------------------
 constexpr int kGemmBM = 64, kGemmBN = 64, kGemmBK = 16;
 
@@ -589,7 +591,9 @@ __device__ __forceinline__ double wave_total(double v)
 // Bound by the chain of dependent proposals: 0.22 us each at 128 beads, most
 // of it the latency of the square root and of the sum over the wavefront
 // (1.2 us with the bonds in LDS, every lane drawing the same random numbers,
-// two square roots per bond and the sum over the LDS crossbar).
+// two square roots per bond and the sum over the LDS crossbar); 0.98 us at
+// 1025 beads, 2.8 beyond (BPL = 22: 86 of its registers are spilled), where it
+// was 7 to 9.
 constexpr int kMcBatch = 21;  // modes of a batch
 template <int BPL>
 __global__ __launch_bounds__(64) void mc_kernel(double *__restrict__ R,

@@ -83,11 +83,11 @@ __host__ __device__ __forceinline__ Block4 noise_bits(uint64_t seed, uint32_t bl
 // Box-Muller pair `second` (0: words 0, 1; 1: words 2, 3) of a block in
 // FP64: uniforms (x + 1/2) 2^-32, z = sqrt(-2 ln u_a) (cos, sin)(2 pi u_b).
 // On the device with the functions of dm_math.h, which know their arguments'
-// ranges: within 3.4e-16 of the exact normal relative to its radius (7.1e-16
-// with the C library's functions on 2 pi u_b).  The kernels that draw FP64
-// noise are bound by its arithmetic: a bead-space Euler step of 4096 chains of
-// 256 beads (3.1e6 normals) takes 8.1 us, 24 us with the library functions,
-// a mode update of the same ensemble 14 us, 20.6 us.
+// ranges: within 3.8e-16 of the exact normal relative to its radius over 2e7
+// pairs (7.1e-16 with the C library's functions on 2 pi u_b).  The kernels that
+// draw FP64 noise are bound by its arithmetic: a bead-space Euler step of 4096
+// chains of 256 beads (3.1e6 normals) takes 8.7 us, 24 us with the library
+// functions.
 __host__ __device__ __forceinline__ void normal_pair_f64(const Block4 &b, int second, double z[2])
 {
 #if defined(__HIP_DEVICE_COMPILE__)
