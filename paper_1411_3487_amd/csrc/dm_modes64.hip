@@ -91,6 +91,17 @@ __device__ __forceinline__ double dpp64(double v)
         (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
+// The same, 0 in lanes whose mask is 0 (otherwise ~0), whatever the source holds.
+template <int CTRL>
+__device__ __forceinline__ double dpp64_masked(double v, uint32_t mask)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo =
+        mask & (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = mask & (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32),
+                                                                    CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
 constexpr int kShl1 = 0x101, kShl2 = 0x102, kShr1 = 0x111, kShr2 = 0x112;
 
 // Sum over the three component lanes of this lane's chain, in one order for
@@ -373,6 +384,10 @@ __global__ __launch_bounds__(64 * P, LEAN ? 4 : 1) void modes64_kernel(Launch64 
         // block as they come (z of block h; normal 0 of the first belongs to
         // the lane group before, the last even mode takes its own below)
         if (a.gdt != 0.0) {  // the x amplitudes drift with R^y before its update
+            // (opaque: a select of 0 costs two moves more at every use, and a
+            // mask held through the step a register that spills)
+            [[maybe_unused]] uint32_t xmask = alpha == 0 ? ~0u : 0u;
+            if constexpr (NT == 1) asm("" : "+v"(xmask) : "s"(s));
 #pragma unroll
             for (int ii = 0; ii < NU; ++ii)
 #pragma unroll
@@ -380,10 +395,11 @@ __global__ __launch_bounds__(64 * P, LEAN ? 4 : 1) void modes64_kernel(Launch64 
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         if constexpr (NT == 1) {
-                            // (selected, not scaled by 0: the lane after a
+                            // (masked, not scaled by 0: the lane after a
                             // chain's z is the next chain's x, which may be NaN)
-                            const double y = dpp64<kShl1>(R[ii][par][0][r]);
-                            R[ii][par][0][r] = fma64(a.gdt, alpha == 0 ? y : 0.0, R[ii][par][0][r]);
+                            const double y =
+                                dpp64_masked<kShl1>(R[ii][par][0][r], xmask);
+                            R[ii][par][0][r] = fma64(a.gdt, y, R[ii][par][0][r]);
                         } else {
                             R[ii][par][0][r] = fma64(a.gdt, R[ii][par][1][r], R[ii][par][0][r]);
                         }
@@ -454,8 +470,10 @@ __global__ __launch_bounds__(64 * P, LEAN ? 4 : 1) void modes64_kernel(Launch64 
                 v[t] = fma64(W0, z0, r0[16 * t + lane]);
             }
             if constexpr (NT == 1) {
-                const double y = r0[lane < 15 ? lane + 1 : 15];
-                v[0] = fma64(a.gdt, alpha == 0 ? y : 0.0, v[0]);
+                // (0 times its own coordinate for y and z, not the next lane's,
+                // which may be another chain's)
+                v[0] = fma64(alpha == 0 ? a.gdt : 0.0, r0[alpha == 0 && lane < 15 ? lane + 1 : lane],
+                             v[0]);
             } else {
                 v[0] = fma64(a.gdt, r0[16 + lane], v[0]);
             }
